@@ -99,6 +99,16 @@ int32_t cbd_graph_free(cbd_graph *g);
 int32_t cbd_context_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, int32_t n_seq,
                                int32_t *arcs, int32_t capacity, int32_t *n_arcs);
 
+/*
+ * The same for many biasing lists at once, shared out over host threads (a server's channels, each with its own
+ * list).  List i has the sequences [list_offsets[i], list_offsets[i+1]) (list_offsets HOST [n_lists+1], seq_offsets
+ * HOST [list_offsets[n_lists]+1]).  Its arcs are written to arcs[arc_offsets[i] .. arc_offsets[i+1]) (arc_offsets HOST
+ * [n_lists+1]), the layout cbd_set_contexts and cbd_contexts_create take.  CBD_E_BUFFER if capacity is too small
+ * (arc_offsets[n_lists] = needed size).
+ */
+int32_t cbd_context_lists_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets,
+                                     int32_t n_lists, int32_t *arcs, int32_t capacity, int32_t *arc_offsets);
+
 typedef struct cbd_config {
   int32_t num_channels;       /* >= 1 */
   float beam;                 /* >= 0; may be +inf */

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from itertools import chain
 from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
@@ -20,7 +21,7 @@ CBD_OK, CBD_E_INVALID, CBD_E_CAPACITY, CBD_E_EPS_DIVERGED = 0, -1, -2, -3
 CBD_E_NO_TOKENS, CBD_E_BUFFER, CBD_E_HIP, CBD_E_NOMEM = -4, -5, -6, -7
 
 EXPORTS = [
-    "cbd_graph_load", "cbd_graph_free", "cbd_context_from_words", "cbd_decoder_create", "cbd_decoder_free", "cbd_reset_channels",
+    "cbd_graph_load", "cbd_graph_free", "cbd_context_from_words", "cbd_context_lists_from_words", "cbd_decoder_create", "cbd_decoder_free", "cbd_reset_channels",
     "cbd_set_context", "cbd_set_contexts", "cbd_contexts_create", "cbd_context_destroy", "cbd_use_contexts", "cbd_advance", "cbd_compact_records", "cbd_best_path", "cbd_best_paths", "cbd_best_paths_static", "cbd_best_paths_begin", "cbd_best_paths_finish", "cbd_best_tails", "cbd_best_tails_begin", "cbd_best_tails_finish",
     "cbd_get_fixed", "cbd_get_tokens",
     "cbd_get_records", "cbd_get_stats", "cbd_decoder_info", "cbd_synchronize", "cbd_selftest", "cbd_strerror", "cbd_last_error",
@@ -75,6 +76,8 @@ def lib():
     L.cbd_graph_free.argtypes = [vp]
     L.cbd_context_from_words.restype = i32
     L.cbd_context_from_words.argtypes = [vp, vp, vp, i32, vp, i32, vp]
+    L.cbd_context_lists_from_words.restype = i32
+    L.cbd_context_lists_from_words.argtypes = [vp, vp, vp, vp, i32, vp, i32, vp]
     L.cbd_decoder_create.restype = i32
     L.cbd_decoder_create.argtypes = [vp, C.POINTER(cbd_config), vp, C.POINTER(vp)]
     L.cbd_decoder_free.restype = i32
@@ -185,6 +188,26 @@ def cbd_context_from_words(g, sequences) -> np.ndarray:
             continue
         _check(rc, "cbd_context_from_words")
         return arcs[:n.value].copy()
+
+
+def cbd_context_lists_from_words(g, lists) -> Tuple[np.ndarray, np.ndarray]:
+    """Algorithm 1 for many lists of word-id sequences -> (arc_idx, list_offsets), packed as cbd_set_contexts takes them."""
+    seqs = list(chain.from_iterable(lists))
+    words = np.fromiter(chain.from_iterable(seqs), np.int32)
+    offs = np.zeros(len(seqs) + 1, np.int32)
+    np.cumsum(np.fromiter(map(len, seqs), np.int32, len(seqs)), out=offs[1:])
+    lo = np.zeros(len(lists) + 1, np.int32)
+    np.cumsum(np.fromiter(map(len, lists), np.int32, len(lists)), out=lo[1:])
+    ao = np.zeros(len(lists) + 1, np.int32)
+    cap = max(1 << 14, len(lists) << 10)
+    while True:
+        arcs = np.empty(cap, np.int32)
+        rc = lib().cbd_context_lists_from_words(g, _p(words), _p(offs), _p(lo), int(len(lists)), _p(arcs), cap, _p(ao))
+        if rc == CBD_E_BUFFER:
+            cap = int(ao[-1])
+            continue
+        _check(rc, "cbd_context_lists_from_words")
+        return arcs[:ao[-1]].copy(), ao
 
 
 def cbd_decoder_create(g, num_channels, beam, max_active, max_frames, max_context_arcs, lookup_mode=0,

@@ -9,12 +9,14 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <stdexcept>
 #include <string>
 #include <vector>
 
 #include "cbd_device.hpp"
+#include "word_index.hpp"
 
 // Device-side result rows of cbd_best_paths_static (headers, words, arcs): a fixed array in the code object instead
 // of buffers from hipMalloc, for callers that must not allocate.  Every GPU the library runs on holds its own copy
@@ -131,11 +133,7 @@ struct cbd_graph {
   std::vector<int32_t> pub2int, int2pub;
   // host copy in the caller's numbering, for building contexts from word sequences
   std::vector<int32_t> h_row, h_dst, h_olabel;
-  std::vector<int32_t> word_arcs;   // arcs that carry a word, ordered by (word, arc); built on first use
-  std::vector<int32_t> word_first;  // [num_words + 2] start of each word's run in word_arcs
-  std::vector<int32_t> visit;       // [S] search stamps
-  int32_t visit_stamp = 0;
-  int32_t max_word = 0;
+  std::unique_ptr<cbd::WordIndex> words;   // built on first use
   int32_t unstored_closures = 0;    // states whose epsilon closure is not stored as a list (too deep or too long)
   std::vector<int4> long_rows;      // states with more than kBigRowArcs emitting arcs: (state, first arc, arcs, 0), by state
   size_t bytes = 0;
@@ -640,81 +638,17 @@ int32_t cbd_graph_load(const cbd_graph_desc *desc, cbd_graph **out) try {
 
 namespace {
 
-// source state of an arc in the caller's numbering
-int32_t arc_source(const cbd_graph *g, int32_t a) {
-  return (int32_t)(std::upper_bound(g->h_row.begin(), g->h_row.end(), a) - g->h_row.begin()) - 1;
-}
-
-void build_word_index(cbd_graph *g) {
-  if (!g->word_first.empty()) return;
-  int32_t mw = 0;
-  for (int32_t w : g->h_olabel) mw = std::max(mw, w);
-  g->max_word = mw;
-  g->word_first.assign((size_t)mw + 2, 0);
-  for (int32_t w : g->h_olabel)
-    if (w > 0) g->word_first[(size_t)w + 1]++;
-  for (size_t w = 1; w < g->word_first.size(); ++w) g->word_first[w] += g->word_first[w - 1];
-  g->word_arcs.resize((size_t)g->word_first.back());
-  std::vector<int32_t> fill(g->word_first.begin(), g->word_first.end() - 1);
-  for (int32_t a = 0; a < g->A; ++a) {
-    int32_t w = g->h_olabel[(size_t)a];
-    if (w > 0) g->word_arcs[(size_t)fill[(size_t)w]++] = a;
-  }
-  g->visit.assign((size_t)g->S, 0);
-}
-
-bool state_outputs(const cbd_graph *g, int32_t s, int32_t w) {
-  for (int32_t a = g->h_row[(size_t)s]; a < g->h_row[(size_t)s + 1]; ++a)
-    if (g->h_olabel[(size_t)a] == w) return true;
-  return false;
-}
-
-// Algorithm 1 for one word sequence; arcs are appended to `out` (duplicates possible).
-void arcs_for_sequence(cbd_graph *g, const int32_t *words, int32_t k, std::vector<int32_t> &out) {
-  if (k <= 0) return;
-  auto run = [&](int32_t w, const int32_t **b, const int32_t **e) {
-    if (w <= 0 || w > g->max_word) { *b = *e = nullptr; return; }
-    *b = g->word_arcs.data() + g->word_first[(size_t)w];
-    *e = g->word_arcs.data() + g->word_first[(size_t)w + 1];
-  };
-  // states that output w_1: the sequence may start anywhere (Sec. 4.1)
-  std::vector<int32_t> reached, next, stack;
-  const int32_t *b, *e;
-  run(words[0], &b, &e);
-  for (const int32_t *p = b; p != e; ++p) reached.push_back(arc_source(g, *p));
-  std::sort(reached.begin(), reached.end());
-  reached.erase(std::unique(reached.begin(), reached.end()), reached.end());
-  for (int32_t t = 1; t < k; ++t) {
-    const int32_t w_prev = words[t - 1], w_next = words[t];
-    next.clear();
-    if (++g->visit_stamp == 0x7FFFFFFF) { std::fill(g->visit.begin(), g->visit.end(), 0); g->visit_stamp = 1; }
-    const int32_t stamp = g->visit_stamp;
-    for (int32_t s_p : reached) {
-      // leave s_p through an arc that outputs the previous word, then follow arcs without output
-      // label; states on the way that can output the next word are where the sequence continues
-      for (int32_t a = g->h_row[(size_t)s_p]; a < g->h_row[(size_t)s_p + 1]; ++a) {
-        if (g->h_olabel[(size_t)a] != w_prev) continue;
-        out.push_back(a);
-        stack.push_back(g->h_dst[(size_t)a]);
-      }
-      while (!stack.empty()) {
-        int32_t q = stack.back();
-        stack.pop_back();
-        if (g->visit[(size_t)q] == stamp) continue;   // shared by all s_p of this step: the result is a union
-        g->visit[(size_t)q] = stamp;
-        if (state_outputs(g, q, w_next)) next.push_back(q);
-        for (int32_t a = g->h_row[(size_t)q]; a < g->h_row[(size_t)q + 1]; ++a)
-          if (g->h_olabel[(size_t)a] == 0) stack.push_back(g->h_dst[(size_t)a]);
-      }
-    }
-    std::sort(next.begin(), next.end());
-    next.erase(std::unique(next.begin(), next.end()), next.end());
-    reached.swap(next);
-  }
-  const int32_t w_last = words[k - 1];
-  for (int32_t s : reached)
-    for (int32_t a = g->h_row[(size_t)s]; a < g->h_row[(size_t)s + 1]; ++a)
-      if (g->h_olabel[(size_t)a] == w_last) out.push_back(a);
+// Checks the sequences and lists of a request and makes the lists (out[i]: sorted arcs of list i).
+int32_t lists_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, int32_t n_seq, const int32_t *list_offsets,
+                         int32_t n_lists, std::vector<std::vector<int32_t>> &out, const char *who) {
+  const std::string w(who);
+  if (n_seq < 0 || seq_offsets[0] != 0) return fail(CBD_E_INVALID, w + ": bad sequence offsets");
+  for (int32_t i = 0; i < n_seq; ++i)
+    if (seq_offsets[i + 1] < seq_offsets[i]) return fail(CBD_E_INVALID, w + ": offsets not monotone");
+  if (n_seq > 0 && seq_offsets[n_seq] > 0 && !words) return fail(CBD_E_INVALID, w + ": null words");
+  if (!g->words) g->words.reset(new cbd::WordIndex(g->S, g->h_row.data(), g->h_dst.data(), g->h_olabel.data()));
+  g->words->lists(words, seq_offsets, list_offsets, n_lists, out);
+  return CBD_OK;
 }
 
 }  // namespace
@@ -722,16 +656,11 @@ void arcs_for_sequence(cbd_graph *g, const int32_t *words, int32_t k, std::vecto
 int32_t cbd_context_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, int32_t n_seq,
                                int32_t *arcs, int32_t capacity, int32_t *n_arcs) try {
   if (!g || !seq_offsets || !n_arcs) return fail(CBD_E_INVALID, "context_from_words: null argument");
-  if (n_seq < 0 || seq_offsets[0] != 0) return fail(CBD_E_INVALID, "context_from_words: bad sequence offsets");
-  for (int32_t i = 0; i < n_seq; ++i)
-    if (seq_offsets[i + 1] < seq_offsets[i]) return fail(CBD_E_INVALID, "context_from_words: offsets not monotone");
-  if (n_seq > 0 && seq_offsets[n_seq] > 0 && !words) return fail(CBD_E_INVALID, "context_from_words: null words");
-  build_word_index(g);
-  std::vector<int32_t> out;
-  for (int32_t i = 0; i < n_seq; ++i)
-    arcs_for_sequence(g, words + seq_offsets[i], seq_offsets[i + 1] - seq_offsets[i], out);
-  std::sort(out.begin(), out.end());
-  out.erase(std::unique(out.begin(), out.end()), out.end());
+  const int32_t list_offsets[2] = {0, n_seq};
+  std::vector<std::vector<int32_t>> lists;
+  int32_t rc = lists_from_words(g, words, seq_offsets, n_seq, list_offsets, 1, lists, "context_from_words");
+  if (rc != CBD_OK) return rc;
+  const std::vector<int32_t> &out = lists[0];
   *n_arcs = (int32_t)out.size();
   if ((int32_t)out.size() > capacity) return CBD_E_BUFFER;
   if (!out.empty()) {
@@ -743,6 +672,31 @@ int32_t cbd_context_from_words(cbd_graph *g, const int32_t *words, const int32_t
   return fail(CBD_E_NOMEM, "context_from_words: host allocation failed");
 } catch (const std::exception &e) {
   return fail(CBD_E_HIP, std::string("context_from_words: ") + e.what());
+}
+
+int32_t cbd_context_lists_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets,
+                                     int32_t n_lists, int32_t *arcs, int32_t capacity, int32_t *arc_offsets) try {
+  if (!g || !seq_offsets || !list_offsets || !arc_offsets) return fail(CBD_E_INVALID, "context_lists_from_words: null argument");
+  if (n_lists < 0 || list_offsets[0] != 0) return fail(CBD_E_INVALID, "context_lists_from_words: bad list offsets");
+  for (int32_t i = 0; i < n_lists; ++i)
+    if (list_offsets[i + 1] < list_offsets[i]) return fail(CBD_E_INVALID, "context_lists_from_words: offsets not monotone");
+  std::vector<std::vector<int32_t>> lists;
+  int32_t rc = lists_from_words(g, words, seq_offsets, list_offsets[n_lists], list_offsets, n_lists, lists, "context_lists_from_words");
+  if (rc != CBD_OK) return rc;
+  int64_t total = 0;
+  for (int32_t i = 0; i < n_lists; ++i) total += (int64_t)lists[(size_t)i].size();
+  if (total > 0x7FFFFFFF) return fail(CBD_E_INVALID, "context_lists_from_words: more arcs than the offsets can count");
+  arc_offsets[0] = 0;
+  for (int32_t i = 0; i < n_lists; ++i) arc_offsets[i + 1] = arc_offsets[i] + (int32_t)lists[(size_t)i].size();
+  if (total > capacity) return CBD_E_BUFFER;
+  if (total > 0 && !arcs) return fail(CBD_E_INVALID, "context_lists_from_words: null output");
+  for (int32_t i = 0; i < n_lists; ++i)
+    if (!lists[(size_t)i].empty()) memcpy(arcs + arc_offsets[i], lists[(size_t)i].data(), sizeof(int32_t) * lists[(size_t)i].size());
+  return CBD_OK;
+} catch (const std::bad_alloc &) {
+  return fail(CBD_E_NOMEM, "context_lists_from_words: host allocation failed");
+} catch (const std::exception &e) {
+  return fail(CBD_E_HIP, std::string("context_lists_from_words: ") + e.what());
 }
 
 int32_t cbd_graph_free(cbd_graph *g) {

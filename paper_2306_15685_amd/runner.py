@@ -62,11 +62,12 @@ def contexts_from_words(graph_handle, sequences: list):
     offsets) per segment that the decoder takes, and the host time the calls took."""
     out, n, t0 = [], 0, time.perf_counter()
     for per_channel, offs in sequences:
-        out.append(([B.cbd_context_from_words(graph_handle, seqs) for seqs in per_channel], offs))
+        arcs, lo = B.cbd_context_lists_from_words(graph_handle, per_channel)
+        out.append((np.split(arcs, lo[1:-1]) if len(per_channel) else [], offs))
         n += len(per_channel)
     dt = time.perf_counter() - t0
     arcs = sum(int(x.size) for lists, _ in out for x in lists)
-    return out, {"lists": n, "ms_per_list": 1e3 * dt / max(n, 1), "arcs_per_list": arcs / max(n, 1), "threads": 1}
+    return out, {"lists": n, "ms_per_list": 1e3 * dt / max(n, 1), "arcs_per_list": arcs / max(n, 1)}
 
 
 class Session:
