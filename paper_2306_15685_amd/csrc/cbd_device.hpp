@@ -400,6 +400,43 @@ __device__ __forceinline__ bool ctx_contains(const Ctx &cx, int32_t a) {
   return sorted_contains(cx.g_list, cx.n, a);
 }
 
+// The same test for up to two arcs per lane, by a whole wave.  in: what this lane wants tested; out: what is listed.
+// second: some lane has a second arc (uniform).  A wave waits for LDS once per step for both arcs, and the number of
+// steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with no lanes
+// dropping out.  (One arc after the other with a search that ends per lane: a wave waited twice per step and for the
+// arc records before its second test.  2,048 channels with 1,000-arc lists 10.33 -> 10.14 ms, 32 channels x 333
+// frames behind the plain search 2.414 -> 2.393 ms, 8 channels x 1,000 frames 8.59 -> 8.50 ms.)
+__device__ __forceinline__ void ctx_contains_pair(const Ctx &cx, const int (&a)[2], bool second, bool (&in)[2]) {
+  if (cx.n == 0) { in[0] = in[1] = false; return; }
+  if (cx.use_bitmap) {
+    const uint32_t h0 = bloom_hash(a[0]), h1 = bloom_hash(a[1]);
+    const uint32_t m0 = bloom_mask(h0), m1 = bloom_mask(h1);
+    const uint32_t w0 = cx.bitmap[bloom_word(h0)], w1 = second ? cx.bitmap[bloom_word(h1)] : 0u;
+    in[0] = in[0] && (w0 & m0) == m0;
+    in[1] = in[1] && (w1 & m1) == m1;
+    if (__ballot(in[0] || in[1]) == 0) return;   // uniform
+  }
+  if (!cx.in_lds) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) if (in[q]) in[q] = sorted_contains(cx.g_list, cx.n, a[q]);
+    return;
+  }
+  // the last entry <= a lies in [b, b + len), if there is one
+  int b0 = 0, b1 = 0;
+  for (int len = __builtin_amdgcn_readfirstlane(cx.n); len > 1;) {
+    const int half = len >> 1;
+    const int v0 = cx.lds_list[b0 + half];
+    if (second) {
+      const int v1 = cx.lds_list[b1 + half];
+      b1 = v1 <= a[1] ? b1 + half : b1;
+    }
+    b0 = v0 <= a[0] ? b0 + half : b0;
+    len -= half;
+  }
+  in[0] = in[0] && cx.lds_list[b0] == a[0];
+  in[1] = in[1] && cx.lds_list[b1] == a[1];
+}
+
 // A token's arc row as another wave of the workgroup stored it to device memory: read past the L1.
 __device__ __forceinline__ int2 load_row_fe(const int4 *row) {
   unsigned long long v = __hip_atomic_load((const unsigned long long *)row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -178,17 +178,26 @@ __device__ __forceinline__ uint32_t lean_candidates(const AdvanceParams &p, cons
       if (E.act[q]) E.rec[q] = p.arcs[E.arc[q]];
     }
   }
+  // the bias test needs the arc's number only: it runs while the records are on their way
+  const bool second = jb + 64 < T.total;   // uniform
+  bool listed[2] = {E.act[0], E.act[1]};
+  ctx_contains_pair(cx, E.arc, second, listed);
+  // both slots' scores are asked for before either is used
+  float ll[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    if (jb + q * 64 < T.total && E.act[q]) {
-      float w = E.rec[q].weight;
-      if (ctx_contains(cx, E.arc[q])) w = w + cx.offset;   // Sec. 4.1: boosted weight = weight + discount
+    if (E.act[q]) {
       const uint32_t pdf = (E.rec[q].meta & 0xFFFFu) - 1u;
-      const float ll = kRowFromLds ? Lrow.at(pdf) : Lrow.glob[pdf];
-      E.cand[q] = (c_own[q] + w) - ll;
-      const uint32_t o = f2ord(E.cand[q]);
-      lmin = o < lmin ? o : lmin;
+      ll[q] = kRowFromLds ? Lrow.at(pdf) : Lrow.glob[pdf];
     }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float w = E.rec[q].weight;
+    w = listed[q] ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
+    E.cand[q] = (c_own[q] + w) - ll[q];
+    const uint32_t o = E.act[q] ? f2ord(E.cand[q]) : 0xFFFFFFFFu;
+    lmin = o < lmin ? o : lmin;
   }
   return lmin;
 }
@@ -340,8 +349,11 @@ __device__ __forceinline__ void lean_closure_end(const AdvanceParams &p, const M
   const ArcRec &rec = C.rec;
   const int depth = C.act ? (int)(rec.meta & 0xFu) : 0;   // 1..kClosureMaxDepth
   const int plane = (C.plane + (int)((rec.meta >> 4) & 0x3Fu)) & 63;   // the lane that holds the parent record
+  const int can[2] = {C.can, 0};
+  bool listed[2] = {C.act, false};
+  ctx_contains_pair(cx, can, false, listed);
   float w = rec.weight;
-  if (C.act && ctx_contains(cx, C.can)) w = w + cx.offset;   // Sec. 4.1: boosted weight = weight + discount
+  w = listed[0] ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
   const float beam = p.beam;
   float c = __builtin_inff();
   bool ok = false;
