@@ -94,7 +94,8 @@ int32_t cbd_graph_free(cbd_graph *g);
  * leaves a state reached from a w_{t-1} arc of the sequence so far through arcs without output label.
  * The union over the sequences is written to arcs (HOST [capacity]) sorted and without duplicates,
  * ready for cbd_set_context; *n_arcs receives its size.  CBD_E_BUFFER if capacity is too small
- * (*n_arcs = needed size).  Unknown words contribute nothing.  Not thread-safe per graph.
+ * (*n_arcs = needed size).  Unknown words contribute nothing.  A 0 after the first word stands for the arcs without
+ * output label; a sequence that begins with 0 contributes nothing.  Not thread-safe per graph.
  */
 int32_t cbd_context_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, int32_t n_seq,
                                int32_t *arcs, int32_t capacity, int32_t *n_arcs);

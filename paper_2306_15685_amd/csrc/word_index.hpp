@@ -26,7 +26,9 @@ namespace cbd {
 
 class WordIndex {
  public:
-  WordIndex(int32_t S, const int32_t *row, const int32_t *dst, const int32_t *olabel) {
+  // The arrays are the graph's own and outlive the index.
+  WordIndex(int32_t S, const int32_t *row, const int32_t *dst, const int32_t *olabel)
+      : S_(S), row_(row), dst_(dst), olabel_(olabel) {
     const int64_t A = row[S];
     // record of a state (32-bit words, padded to an even number): arcs without label, arcs with one; (record it leads
     // to, that state's signature) per arc of the former; (label, arc, record of the destination) per arc of the latter
@@ -208,6 +210,10 @@ class WordIndex {
       out.insert(out.end(), arc_.begin() + b, arc_.begin() + e);
       return;
     }
+    if (std::find(words + 1, words + k, 0) != words + k) {
+      sequence_with_zeros(words, k, s, out);
+      return;
+    }
     // states that output w_1 (a state's arcs lie together)
     s.reached.clear();
     for (int64_t i = b; i < e; ++i)
@@ -255,6 +261,41 @@ class WordIndex {
     }
   }
 
+  // The same for a sequence with a 0 after its first word: the 0 stands for the arcs without label, which a search
+  // follows as well.  Neither signatures nor records tell which arcs those are: this reads the graph's own arrays.
+  void sequence_with_zeros(const int32_t *words, int32_t k, Search &s, std::vector<int32_t> &out) const {
+    auto outputs = [&](uint32_t q, int32_t w) {
+      return std::find(olabel_ + row_[q], olabel_ + row_[q + 1], w) != olabel_ + row_[q + 1];
+    };
+    s.reached.clear();
+    for (int64_t i = first_[(size_t)words[0]]; i < first_[(size_t)words[0] + 1]; ++i) {   // (k > 1: a word of the graph)
+      const uint32_t src = (uint32_t)(std::upper_bound(row_, row_ + S_ + 1, arc_[(size_t)i]) - row_) - 1;
+      if (s.reached.empty() || s.reached.back() != src) s.reached.push_back(src);
+    }
+    for (int32_t t = 0; t < k; ++t) {
+      s.queue.clear();
+      for (uint32_t q : s.reached)
+        for (int32_t a = row_[q]; a < row_[q + 1]; ++a) {
+          if (olabel_[a] != words[t]) continue;
+          out.push_back(a);
+          s.queue.push_back((uint32_t)dst_[a]);
+        }
+      if (t + 1 == k) return;
+      s.next.clear();
+      s.seen.clear();
+      for (size_t head = 0; head < s.queue.size(); ++head) {
+        const uint32_t q = s.queue[head];
+        if (!s.seen.insert(q)) continue;
+        if (outputs(q, words[t + 1])) s.next.push_back(q);
+        for (int32_t a = row_[q]; a < row_[q + 1]; ++a)
+          if (olabel_[a] == 0) s.queue.push_back((uint32_t)dst_[a]);
+      }
+      s.reached.swap(s.next);
+    }
+  }
+
+  int32_t S_;
+  const int32_t *row_, *dst_, *olabel_;
   std::vector<uint32_t> rec_;
   std::vector<int64_t> first_;       // [words + 2] start of each word's run in state_ / arc_
   std::vector<uint32_t> state_;      // records of the states the word's arcs leave, and

@@ -1,0 +1,70 @@
+"""Algorithm 1's word index (csrc/word_index.hpp) on the host, compiled by itself, against the checker."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import arcs_for_sequence
+from paper_2306_15685_amd import binding as B
+from paper_2306_15685_amd import synth
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SRC = os.path.join(HERE, "word_index_host.cpp")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("word_index") / "libword_index.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-shared", "-fPIC", "-pthread", "-o", lib, SRC], check=True)
+    L = C.CDLL(lib)
+    L.word_index_make.restype = C.c_void_p
+    L.word_index_make.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+    L.word_index_free.restype = None
+    L.word_index_free.argtypes = [C.c_void_p]
+    L.word_index_lists.restype = C.c_int64
+    L.word_index_lists.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
+    return L
+
+
+class Index:
+    def __init__(self, host, g):
+        self.L, self.keep = host, [np.ascontiguousarray(x, np.int32) for x in (g.row_offsets, g.dst, g.olabel)]
+        self.h = host.word_index_make(g.num_states, *(x.ctypes.data for x in self.keep))
+
+    def lists(self, lists):
+        words, offs = B.pack_lists([np.asarray(q, np.int32) for seqs in lists for q in seqs])
+        lo = np.cumsum([0] + [len(x) for x in lists]).astype(np.int32)
+        ao = np.zeros(len(lists) + 1, np.int64)
+        args = (self.h, words.ctypes.data, offs.ctypes.data, lo.ctypes.data, len(lists))
+        arcs = np.zeros(max(1, self.L.word_index_lists(*args, None, -1, ao.ctypes.data)), np.int32)
+        self.L.word_index_lists(*args, arcs.ctypes.data, arcs.size, ao.ctypes.data)
+        return [arcs[ao[i]:ao[i + 1]] for i in range(len(lists))]
+
+    def close(self):
+        self.L.word_index_free(self.h)
+
+
+GRAPHS = [(4, 0.0, 300), (0, 0.3, 40), (0, 0.0, 2_000)]
+
+
+@pytest.mark.parametrize("period,loops,words", GRAPHS)
+def test_word_0_stands_for_arcs_without_word(host, period, loops, words):
+    """A 0 after the first word is followed like a word, through the arcs that carry none (as the checker does it); a
+    sequence that begins with one contributes nothing, nor does an id below 0 or above the graph's."""
+    g = synth.make_graph(300, 50, words, 0.1, seed_stream=(78, period), self_loop_frac=loops, word_period=period)
+    rng = np.random.default_rng(6)
+    seqs = []
+    for q in synth.word_sequences_on_walks(g, 8, 3, rng):
+        for at in range(len(q) + 1):
+            seqs.append(q[:at] + [0] + q[at:])
+            seqs.append(q[:at] + [int(rng.choice([-1, -2**31, words + 9, 2**31 - 1]))] + q[at:])
+    seqs += [[0], [0, 0], [seqs[0][-1], 0, 0], []]
+    want = [np.array(sorted(arcs_for_sequence(g, q)) if q and q[0] > 0 else [], np.int32) for q in seqs]
+    assert sum(x.size for x, q in zip(want, seqs) if 0 in q) > 0
+    index = Index(host, g)
+    got = index.lists([[q] for q in seqs])
+    index.close()
+    for q, x, y in zip(seqs, want, got):
+        assert np.array_equal(x, y), q
