@@ -18,7 +18,6 @@
 #include <algorithm>
 #include <atomic>
 #include <stdexcept>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -102,11 +101,12 @@ class WordIndex {
     // a thread costs about as much as half a list to start
     const int n_threads = std::max(1, std::min({(int)n_lists / 4, 16, (int)std::thread::hardware_concurrency()}));
     std::vector<std::thread> pool;
+    pool.reserve((size_t)n_threads);   // (before the first of them runs: nothing is thrown past a running thread)
     for (int t = 1; t < n_threads; ++t) {
       try {
         pool.emplace_back(work);
-      } catch (const std::system_error &) {
-        break;   // (no more threads to be had: fewer do it)
+      } catch (...) {
+        break;   // (no more threads or no memory for one: fewer do it)
       }
     }
     work();

@@ -68,3 +68,12 @@ def test_word_0_stands_for_arcs_without_word(host, period, loops, words):
     index.close()
     for q, x, y in zip(seqs, want, got):
         assert np.array_equal(x, y), q
+
+
+def test_every_failing_allocation_is_reported(tmp_path):
+    """Whatever allocation of a request fails, on whatever thread and after threads were started, the request ends in
+    bad_alloc or is served by fewer threads; the process lives on."""
+    exe = str(tmp_path / "no_memory")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-DNO_MEMORY", "-pthread", "-o", exe, SRC], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
