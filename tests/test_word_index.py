@@ -23,6 +23,8 @@ def host(tmp_path_factory):
     L.word_index_make.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
     L.word_index_free.restype = None
     L.word_index_free.argtypes = [C.c_void_p]
+    L.word_index_laid_out.restype = C.c_int32
+    L.word_index_laid_out.argtypes = [C.c_void_p]
     L.word_index_lists.restype = C.c_int64
     L.word_index_lists.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
     return L
@@ -41,6 +43,9 @@ class Index:
         arcs = np.zeros(max(1, self.L.word_index_lists(*args, None, -1, ao.ctypes.data)), np.int32)
         self.L.word_index_lists(*args, arcs.ctypes.data, arcs.size, ao.ctypes.data)
         return [arcs[ao[i]:ao[i + 1]] for i in range(len(lists))]
+
+    def laid_out(self):
+        return bool(self.L.word_index_laid_out(self.h))
 
     def close(self):
         self.L.word_index_free(self.h)
@@ -70,9 +75,53 @@ def test_word_0_stands_for_arcs_without_word(host, period, loops, words):
         assert np.array_equal(x, y), q
 
 
+class Chain:
+    """A ring of S states in random order, a word every `apart` states: the searches' paths have no branches."""
+    def __init__(self, S, apart, words, rng):
+        at = rng.permutation(S)
+        self.num_states, self.src = S, np.arange(S)
+        self.row_offsets, self.dst, self.olabel = np.arange(S + 1), np.zeros(S, np.int32), np.zeros(S, np.int32)
+        self.dst[at] = np.roll(at, -1)
+        self.olabel[at[::apart]] = 1 + rng.integers(0, words, at[::apart].size)
+
+
+@pytest.mark.parametrize("graph", ["small", "several threads", "long chains"])
+def test_layout_comes_when_it_pays_and_changes_nothing(host, graph):
+    """A graph's first lists don't wait for the layout of the whole graph, a request that searches enough of it does, and
+    the lists before, in and after that request equal the checker's.  Graphs above 65,536 states are laid out by several
+    threads; chains of 40 states without word take more sweeps than the signatures are given."""
+    rng = np.random.default_rng(8)
+    g = (synth.make_graph(300, 50, 300, 0.1, seed_stream=(79, 4), word_period=4) if graph == "small" else
+         Chain(70_001, 40 if graph == "long chains" else 4, 5_000, rng))
+    if graph == "small":
+        seqs = synth.word_sequences_on_walks(g, 60, 3, rng)
+    else:
+        seqs = []
+        for s in rng.choice(np.flatnonzero(g.olabel), 400):
+            q, s = [int(g.olabel[s])], g.dst[s]
+            while len(q) < 3:
+                if g.olabel[s]:
+                    q.append(int(g.olabel[s]))
+                s = g.dst[s]
+            seqs.append(q)
+    want = [np.array(sorted(arcs_for_sequence(g, q)), np.int32) for q in seqs]
+    index = Index(host, g)
+    assert np.array_equal(index.lists([[seqs[0]]])[0], want[0]) and not index.laid_out()
+    requests = 0
+    while not index.laid_out():
+        for x, y in zip(index.lists([[q] for q in seqs]), want):
+            assert np.array_equal(x, y)
+        requests += 1
+        assert requests < 50
+    for x, y in zip(index.lists([[q] for q in seqs]), want):
+        assert np.array_equal(x, y)
+    assert np.array_equal(index.lists([seqs])[0], np.unique(np.concatenate(want)))
+    index.close()
+
+
 def test_every_failing_allocation_is_reported(tmp_path):
     """Whatever allocation of a request fails, on whatever thread and after threads were started, the request ends in
-    bad_alloc or is served by fewer threads; the process lives on."""
+    bad_alloc or is served by fewer threads or without the layout; the process lives on."""
     exe = str(tmp_path / "no_memory")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-DNO_MEMORY", "-pthread", "-o", exe, SRC], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=100)

@@ -17,8 +17,10 @@ cbd::WordIndex *word_index_make(int32_t S, const int32_t *row, const int32_t *ds
 
 void word_index_free(cbd::WordIndex *w) { delete w; }
 
+int32_t word_index_laid_out(const cbd::WordIndex *w) { return w->laid_out(); }
+
 // Arcs of all lists back to back; returns their number (nothing is written to arcs if it is above capacity).
-int64_t word_index_lists(const cbd::WordIndex *w, const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets,
+int64_t word_index_lists(cbd::WordIndex *w, const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets,
                          int32_t n_lists, int32_t *arcs, int64_t capacity, int64_t *arc_offsets) {
   std::vector<std::vector<int32_t>> out;
   w->lists(words, seq_offsets, list_offsets, n_lists, out);
@@ -56,7 +58,8 @@ int main() {
     seqs.push_back((int32_t)words.size());
     lists.push_back(i + 1);
   }
-  long failed = 0;
+  long failed = 0, served = 0;
+  bool laid_out = false;
   std::vector<std::vector<int32_t>> want;
   for (long k = -1;; ++k) {
     bool thrown = false;
@@ -65,16 +68,20 @@ int main() {
     try {
       cbd::WordIndex w(1000, row.data(), dst.data(), olabel.data());
       w.lists(words.data(), seqs.data(), lists.data(), 64, out);
+      laid_out = w.laid_out();
     } catch (const std::bad_alloc &) {
       thrown = true;
     }
     const bool reached = k >= 0 && g_left.exchange(-1) < 0;
-    if (k < 0) want = out;
-    else if (!thrown && out != want) { printf("allocation %ld: other lists\n", k); return 1; }
+    if (k < 0) {
+      if (!laid_out) { printf("no layout\n"); return 1; }
+      want = out;
+    } else if (!thrown && out != want) { printf("allocation %ld: other lists\n", k); return 1; }
     failed += thrown;
+    served += reached && !thrown;
     if (k >= 0 && !reached) break;   // (fewer allocations than that)
   }
-  printf("%ld requests ended in bad_alloc\n", failed);
-  return failed > 0 ? 0 : 1;
+  printf("%ld requests ended in bad_alloc, %ld were served all the same\n", failed, served);
+  return failed > 0 && served > 0 ? 0 : 1;
 }
 #endif
