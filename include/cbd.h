@@ -114,6 +114,8 @@ int32_t cbd_context_from_words(cbd_graph *g, const int32_t *words, const int32_t
  */
 int32_t cbd_context_lists_from_words(cbd_graph *g, const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets,
                                      int32_t n_lists, int32_t *arcs, int32_t capacity, int32_t *arc_offsets);
+/* The host threads that a request of n_lists lists is shared out over (>= 1; fewer where they cannot be had). */
+int32_t cbd_context_lists_threads(int32_t n_lists);
 
 typedef struct cbd_config {
   int32_t num_channels;       /* >= 1 */

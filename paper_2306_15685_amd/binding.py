@@ -21,7 +21,7 @@ CBD_OK, CBD_E_INVALID, CBD_E_CAPACITY, CBD_E_EPS_DIVERGED = 0, -1, -2, -3
 CBD_E_NO_TOKENS, CBD_E_BUFFER, CBD_E_HIP, CBD_E_NOMEM = -4, -5, -6, -7
 
 EXPORTS = [
-    "cbd_graph_load", "cbd_graph_free", "cbd_context_from_words", "cbd_context_lists_from_words", "cbd_decoder_create", "cbd_decoder_free", "cbd_reset_channels",
+    "cbd_graph_load", "cbd_graph_free", "cbd_context_from_words", "cbd_context_lists_from_words", "cbd_context_lists_threads", "cbd_decoder_create", "cbd_decoder_free", "cbd_reset_channels",
     "cbd_set_context", "cbd_set_contexts", "cbd_contexts_create", "cbd_context_destroy", "cbd_use_contexts", "cbd_advance", "cbd_compact_records", "cbd_best_path", "cbd_best_paths", "cbd_best_paths_static", "cbd_best_paths_begin", "cbd_best_paths_finish", "cbd_best_tails", "cbd_best_tails_begin", "cbd_best_tails_finish",
     "cbd_get_fixed", "cbd_get_tokens",
     "cbd_get_records", "cbd_get_stats", "cbd_decoder_info", "cbd_synchronize", "cbd_selftest", "cbd_strerror", "cbd_last_error",
@@ -78,6 +78,8 @@ def lib():
     L.cbd_context_from_words.argtypes = [vp, vp, vp, i32, vp, i32, vp]
     L.cbd_context_lists_from_words.restype = i32
     L.cbd_context_lists_from_words.argtypes = [vp, vp, vp, vp, i32, vp, i32, vp]
+    L.cbd_context_lists_threads.restype = i32
+    L.cbd_context_lists_threads.argtypes = [i32]
     L.cbd_decoder_create.restype = i32
     L.cbd_decoder_create.argtypes = [vp, C.POINTER(cbd_config), vp, C.POINTER(vp)]
     L.cbd_decoder_free.restype = i32

@@ -699,6 +699,8 @@ int32_t cbd_context_lists_from_words(cbd_graph *g, const int32_t *words, const i
   return fail(CBD_E_HIP, std::string("context_lists_from_words: ") + e.what());
 }
 
+int32_t cbd_context_lists_threads(int32_t n_lists) { return cbd::WordIndex::threads(n_lists); }
+
 int32_t cbd_graph_free(cbd_graph *g) {
   if (!g) return CBD_OK;
   if (g->d_off2) (void)hipFree(g->d_off2);

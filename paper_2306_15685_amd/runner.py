@@ -59,7 +59,8 @@ def make_inputs(w: synth.Workload, g: Optional[synth.Graph] = None, device: str 
 
 def contexts_from_words(graph_handle, sequences: list):
     """Algorithm 1 through the library for every channel's list of word sequences (Sec. 4.1) -> the (arc lists,
-    offsets) per segment that the decoder takes, and the host time the calls took."""
+    offsets) per segment that the decoder takes, and the host time the calls took, with the threads they were shared out
+    over.  (A segment's lists are views of one array.)"""
     out, n, t0 = [], 0, time.perf_counter()
     for per_channel, offs in sequences:
         arcs, lo = B.cbd_context_lists_from_words(graph_handle, per_channel)
@@ -67,7 +68,8 @@ def contexts_from_words(graph_handle, sequences: list):
         n += len(per_channel)
     dt = time.perf_counter() - t0
     arcs = sum(int(x.size) for lists, _ in out for x in lists)
-    return out, {"lists": n, "ms_per_list": 1e3 * dt / max(n, 1), "arcs_per_list": arcs / max(n, 1)}
+    threads = max((B.lib().cbd_context_lists_threads(len(per_channel)) for per_channel, _ in sequences), default=1)
+    return out, {"lists": n, "ms_per_list": 1e3 * dt / max(n, 1), "arcs_per_list": arcs / max(n, 1), "threads": threads}
 
 
 class Session:

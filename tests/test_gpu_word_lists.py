@@ -29,3 +29,20 @@ def test_lists_equal_the_checker(period, loops, words):
                 assert np.array_equal(arcs[off[i]:off[i + 1]], arcs_for_sequences(g, lists[i])), f"list {i}"
     finally:
         B.cbd_graph_free(gh)
+
+
+def test_report_of_lists_made():
+    """What runner.contexts_from_words says of its work: lists, host time, sizes and the threads they were shared over."""
+    from paper_2306_15685_amd import runner
+    g = synth.make_graph(3_000, 50, 300, 0.1, seed_stream=(77, 4), word_period=4)
+    seqs = synth.word_sequences_on_walks(g, 40, 2, np.random.default_rng(5))
+    gh = B.cbd_graph_load(g.num_states, g.num_pdfs, g.start_state, g.row_offsets, g.dst, g.ilabel, g.olabel, g.weight)
+    try:
+        made, said = runner.contexts_from_words(gh, [([[q] for q in seqs], np.zeros(40, np.float32)), ([seqs], np.zeros(1, np.float32))])
+        assert [len(lists) for lists, _ in made] == [40, 1] and said["lists"] == 41 and said["ms_per_list"] > 0
+        assert said["arcs_per_list"] * 41 == sum(x.size for lists, _ in made for x in lists)
+        assert said["threads"] == B.lib().cbd_context_lists_threads(40) and 1 <= said["threads"] <= 10
+        assert runner.contexts_from_words(gh, [([seqs], np.zeros(1, np.float32))])[1]["threads"] == 1
+        assert runner.contexts_from_words(gh, [])[1]["threads"] == 1
+    finally:
+        B.cbd_graph_free(gh)
