@@ -20,11 +20,11 @@ def test_list_lengths(torch_cuda, lookup_mode, pdfs):  # noqa: F811
     ctxs = []
     for i, k in enumerate(LENGTHS):
         lo, hi = ((0, g.num_arcs), (0, g.num_arcs // 2), (g.num_arcs // 2, g.num_arcs))[i % 3]
-        x = lo + rng.choice(hi - lo, size=k, replace=False)
-        if k > 1:
-            x[0], x[1] = 0, g.num_arcs - 1   # the ends of the numbering
-            x = np.unique(x)
-        ctxs.append(x.astype(np.int32))
+        ends = [0, g.num_arcs - 1] if k > 1 else []   # of the numbering
+        inner = np.arange(max(lo, 1), min(hi, g.num_arcs - 1))
+        x = np.sort(np.concatenate([ends, rng.choice(inner, size=k - len(ends), replace=False)]).astype(np.int32))
+        assert np.unique(x).size == k
+        ctxs.append(x)
     offs = rng.uniform(-6.0, 2.0, C).astype(np.float32)
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=12.0, max_active=0, chunks=[7, 13], lookup_mode=lookup_mode)
     assert s["status"] == 0 and s["tokens"] > 0
