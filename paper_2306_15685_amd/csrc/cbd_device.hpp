@@ -404,8 +404,10 @@ __device__ __forceinline__ bool ctx_contains(const Ctx &cx, int32_t a) {
 // second: some lane has a second arc (uniform).  A wave waits for LDS once per step for both arcs, and the number of
 // steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with no lanes
 // dropping out.  (One arc after the other with a search that ends per lane: a wave waited twice per step and for the
-// arc records before its second test.  2,048 channels with 1,000-arc lists 10.33 -> 10.14 ms, 32 channels x 333
-// frames behind the plain search 2.414 -> 2.393 ms, 8 channels x 1,000 frames 8.59 -> 8.50 ms.)
+// arc records before its second test.  32 channels x 333 frames behind the plain search 2.414 -> 2.393 ms, 8 channels
+// x 1,000 frames 8.59 -> 8.50, where runs differ by 0.3 %; 2,048 channels with 1,000-arc lists behind the filter within
+// the spread.  Waves without arcs take the steps too: leaving before them on a ballot costs 32 channels 0.8 % and 1 to
+// 100 channels 0.5 %.)
 __device__ __forceinline__ void ctx_contains_pair(const Ctx &cx, const int (&a)[2], bool second, bool (&in)[2]) {
   if (cx.n == 0) { in[0] = in[1] = false; return; }
   if (cx.use_bitmap) {
@@ -1285,7 +1287,9 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
     // (a row too long for the count field was written to the row buffer when its token was made)
     if (deg != kLeanDegEscape) rows[i] = make_int4(first, first + (int)deg, 0, 0);
   }
-  __syncthreads();   // (waits for the stores: other waves read the rows past their L1)
+  // (other waves read the rows past their L1.  The barrier doesn't wait for the stores, and need not: a compute unit's
+  // accesses leave in order, so a read behind the barrier finds what a store before it wrote)
+  __syncthreads();
 }
 
 // One call's work on one channel: `pos` is the channel's place in the call's list.
@@ -1411,6 +1415,9 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
 #ifdef CBD_PROFILE
           if (tid == 0) { sh->prof_redo += 1; sh->prof_general -= wall_clock64(); }
 #endif
+          // vmcnt(0): a frame given up behind its second barrier has not waited for this wave's pieces of the next row.
+          // All have arrived before the barrier, behind which this frame's row is written over them.
+          __builtin_amdgcn_s_waitcnt(0x0F70);
           // wipe the table, bring this frame's log-likelihood row back, hand the rows to the general code
           __syncthreads();
           for (int i = tid; i < p.lds_slots; i += kBlock) { ML.hval[i] = kEmptyVal; ML.hkey[i] = kEmptyKey; }
@@ -1469,6 +1476,8 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
       { float *gc = g_cost(); for (int i = tid; i < n; i += kBlock) gc[i] = ML.t_cost[i]; }
     }
   } else if (outcome != kFrameNoTokens) {
+    // (a lean frame without room for its records leaves pieces of the next row on their way to LDS)
+    __builtin_amdgcn_s_waitcnt(0x0F70);
     // leave the device-memory table empty for the next utterance
     { const Mem<false> MG = make_MG(); for (int i = tid; i < p.g_slots; i += kBlock) { stv<false>(&MG.hkey[i], kEmptyKey); stv<false>(&MG.hval[i], kEmptyVal); } }
   }
@@ -1527,7 +1536,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
   // here (arg-min of (cost, arc) over its final table, as the stand-alone snapshot kernel would find it), so a
   // request for partial results right after this call only has to walk.
   if (p.auto_snap) {
-    __syncthreads();   // this call's last costs and records are in device memory
+    __syncthreads();   // (reads behind it find this call's last costs and records: rows_to_device)
     if (tid < 64) {
       const int lane = tid;
       uint64_t bestk = kEmptyVal;
