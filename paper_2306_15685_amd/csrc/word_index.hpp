@@ -14,7 +14,7 @@
 // are shared out over host threads, and so is the layout.
 //
 // 2M / 10M states, lists of nine sequences, 16 threads: the word index takes 22 / 114 ms (first request), the layout
-// 30 / 260 ms and 130 / 640 MB; a list alone 0.6 / 1.2 ms by the plain search and 0.04 / 0.06 laid out, 128 lists in one
+// 30 / 190 to 260 ms and 130 / 640 MB; a list alone 0.6 / 1.2 ms by the plain search and 0.04 / 0.06 laid out, 128 lists in one
 // request 5.1 / 8.4 ms and 0.4 / 0.5.  (A layout on one thread within whatever request came first: that one waited
 // 0.4 / 2.9 s.)
 #pragma once
@@ -54,31 +54,37 @@ class WordIndex {
   void lists(const int32_t *words, const int32_t *seq_offsets, const int32_t *list_offsets, int32_t n_lists,
              std::vector<std::vector<int32_t>> &out) {
     out.resize((size_t)n_lists);
-    std::atomic<int32_t> next{0};
+    for (auto &o : out) o.clear();
+    std::vector<int32_t> at(list_offsets, list_offsets + n_lists);   // each list's next sequence; -1: the list is made
+    std::atomic<int32_t> made{0};
     std::atomic<bool> failed{false};
-    do {
-      if (due()) lay_out();
+    while (made.load() < n_lists) {
+      if (due()) lay_out();   // (lists that were begun go on from where they are)
+      std::atomic<int32_t> next{0};
       share(threads(n_lists), [&](int) {
         try {
           Search s;
-          while (!failed.load() && !due()) {
-            const int32_t i = next.fetch_add(1);
-            if (i >= n_lists) break;
+          for (int32_t i; !failed.load() && !due() && (i = next.fetch_add(1)) < n_lists;) {
+            int32_t &k = at[(size_t)i];
+            if (k < 0) continue;
             std::vector<int32_t> &o = out[(size_t)i];
-            o.clear();
-            for (int32_t k = list_offsets[i]; k < list_offsets[i + 1]; ++k)
+            for (; k < list_offsets[i + 1] && !due(); ++k) {
               sequence(words + seq_offsets[k], seq_offsets[k + 1] - seq_offsets[k], s, o);
+              if (s.met > 0) met_ += s.met;
+              s.met = 0;
+            }
+            if (k < list_offsets[i + 1]) break;
             std::sort(o.begin(), o.end());
             o.erase(std::unique(o.begin(), o.end()), o.end());
-            if (s.met > 0) met_ += s.met;
-            s.met = 0;
+            k = -1;
+            ++made;
           }
         } catch (...) {
           failed.store(true);   // (out of memory: reported by the caller's thread)
         }
       });
       if (failed.load()) throw std::bad_alloc();
-    } while (next.load() < n_lists);
+    }
   }
 
   // Host threads that a request of n lists is shared over (a thread costs about as much as half a list to start).

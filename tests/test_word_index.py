@@ -39,10 +39,11 @@ class Index:
         words, offs = B.pack_lists([np.asarray(q, np.int32) for seqs in lists for q in seqs])
         lo = np.cumsum([0] + [len(x) for x in lists]).astype(np.int32)
         ao = np.zeros(len(lists) + 1, np.int64)
-        args = (self.h, words.ctypes.data, offs.ctypes.data, lo.ctypes.data, len(lists))
-        arcs = np.zeros(max(1, self.L.word_index_lists(*args, None, -1, ao.ctypes.data)), np.int32)
-        self.L.word_index_lists(*args, arcs.ctypes.data, arcs.size, ao.ctypes.data)
-        return [arcs[ao[i]:ao[i + 1]] for i in range(len(lists))]
+        arcs = np.empty(1 << 22, np.int32)
+        n = self.L.word_index_lists(self.h, words.ctypes.data, offs.ctypes.data, lo.ctypes.data, len(lists),
+                                    arcs.ctypes.data, arcs.size, ao.ctypes.data)
+        assert n <= arcs.size
+        return [arcs[ao[i]:ao[i + 1]].copy() for i in range(len(lists))]
 
     def laid_out(self):
         return bool(self.L.word_index_laid_out(self.h))
@@ -116,6 +117,9 @@ def test_layout_comes_when_it_pays_and_changes_nothing(host, graph):
     for x, y in zip(index.lists([[q] for q in seqs]), want):
         assert np.array_equal(x, y)
     assert np.array_equal(index.lists([seqs])[0], np.unique(np.concatenate(want)))
+    index.close()
+    index = Index(host, g)   # one list that searches enough of it, taken up again behind the layout
+    assert np.array_equal(index.lists([seqs * 8])[0], np.unique(np.concatenate(want))) and index.laid_out()
     index.close()
 
 
