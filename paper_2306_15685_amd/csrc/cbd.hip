@@ -215,6 +215,12 @@ struct cbd_decoder {
   int4 *d_team_big_rows = nullptr;
   int32_t *d_team_big_group = nullptr, *d_team_big_perm = nullptr;
   int32_t team_n_big_rows = 0;
+  // frames by parts (parts = 0: not used)
+  int parts = 0, part_slots = 0, part_q1 = 0, part_q2 = 0;
+  int4 *d_long_rows = nullptr;
+  int32_t *d_long_group = nullptr, *d_long_idx = nullptr;
+  cbd::ArcRec *d_long_arcs = nullptr;
+  int32_t n_long_rows = 0;
   std::vector<int32_t> h_tmp;
   std::vector<int32_t> h_static_meta;   // result headers of cbd_best_paths_static on their way to the caller
   size_t bytes = 0;
@@ -225,11 +231,15 @@ namespace {
 using cbd::AdvanceParams;
 
 template <int kBlock> hipError_t launch_advance_t(const AdvanceParams &p, int grid, uint32_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((cbd::advance_kernel<kBlock>), dim3(grid), dim3(kBlock), lds, st, p);
+  if (p.parts > 0) hipLaunchKernelGGL((cbd::advance_parts_kernel<kBlock>), dim3(grid), dim3(kBlock), lds, st, p);
+  else hipLaunchKernelGGL((cbd::advance_kernel<kBlock>), dim3(grid), dim3(kBlock), lds, st, p);
   return hipGetLastError();
 }
 
 template <int kBlock> hipError_t set_attr_t(uint32_t lds) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_parts_kernel<kBlock>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_kernel<kBlock>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
@@ -247,11 +257,11 @@ hipError_t set_attr(int block, uint32_t lds) {
 }
 
 // Workgroups of the decode kernel that one compute unit holds at once (registers, waves and LDS together).
-hipError_t resident_per_cu(int block, uint32_t lds, int *n) {
-  if (block == 256) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, cbd::advance_kernel<256>, 256, lds);
-  if (block == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, cbd::advance_kernel<512>, 512, lds);
-  if (block == 960) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, cbd::advance_kernel<960>, 960, lds);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, cbd::advance_kernel<1024>, 1024, lds);
+hipError_t resident_per_cu(int block, bool parts, uint32_t lds, int *n) {
+  if (block == 256) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<256> : cbd::advance_kernel<256>, 256, lds);
+  if (block == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<512> : cbd::advance_kernel<512>, 512, lds);
+  if (block == 960) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<960> : cbd::advance_kernel<960>, 960, lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<1024> : cbd::advance_kernel<1024>, 1024, lds);
 }
 
 // A team launch.  The members of a team wait for one another inside the kernel, so all of a launch's workgroups
@@ -288,7 +298,7 @@ bool walks_in_flight(const cbd_decoder *d) {
 }
 
 hipError_t launch_advance(const cbd_decoder *d, const AdvanceParams &p, int grid) {
-  if (d->walk_room && d->block == 1024 && grid >= d->walk_room_min_grid && walks_in_flight(d)) {
+  if (d->walk_room && d->block == 1024 && d->parts == 0 && grid >= d->walk_room_min_grid && walks_in_flight(d)) {
     // leave the walks room on the compute units (see advance_beside_kernel)
     hipLaunchKernelGGL((cbd::advance_beside_kernel<1024>), dim3(grid), dim3(1024), d->lds_bytes, d->stream, p);
     return hipGetLastError();
@@ -314,6 +324,9 @@ AdvanceParams base_params(const cbd_decoder *d) {
   p.tok_row = d->d_tok_row;
   p.bp = d->d_bp; p.g_log = d->d_log; p.ctx = d->d_ctx; p.ctx_n = d->d_ctx_n; p.ctx_off = d->d_ctx_off;
   p.g_hkey = d->d_hkey; p.g_hval = d->d_hval; p.g_hidx = d->d_hidx;
+  p.parts = d->parts; p.part_slots = d->part_slots; p.part_q1 = d->part_q1; p.part_q2 = d->part_q2;
+  p.n_long_rows = d->n_long_rows; p.long_rows = d->d_long_rows; p.long_group = d->d_long_group;
+  p.long_arcs = d->d_long_arcs; p.long_idx = d->d_long_idx;
   return p;
 }
 
@@ -841,12 +854,25 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
     if (d->lds_slots > (int32_t)cbd::LogT<true>::kSrcMask) {
       return fail(CBD_E_INVALID, "decoder: LDS table too large for the change log's slot field");
     }
+    // Frames that outgrow the LDS tables by parts, for graphs with long rows (cbd_parts.hpp says why only these): as few
+    // shares as hold a frame of g_tok_cap tokens at seven eighths of their slots (12 bytes each, in the LDS of the lean
+    // tables, which also stages live tokens, 16 bytes per thread).
+    if (cfg->frame_code == 0 && cap > 0 && cfg->workgroups_per_channel <= 1 && g->unstored_closures == 0 && !g->long_rows.empty()) {
+      const cbd::LdsLayout l = cbd::make_layout(d->stage_rows ? g->P : 0, d->ctx_lds_cap, cap, d->lds_slots, d->lds_log_cap, lean_entries);
+      const int slots = (int)((l.total - l.hval) / 12) / 64 * 64;
+      int k = 1;
+      while (k < cbd::kPartsMax && (int64_t)k * slots * 7 / 8 < d->g_tok_cap) k *= 2;
+      if ((int64_t)k * slots * 7 / 8 >= d->g_tok_cap && slots * 12 >= d->block * 16) {
+        d->parts = k; d->part_slots = slots;
+        d->part_q1 = d->g_log_cap / 8 * 5 / k; d->part_q2 = d->g_log_cap / 8 * 3 / k;
+      }
+    }
   }
   DCHK(set_attr(d->block, d->lds_bytes));
   if (cfg->workgroups_per_cu > 1) {
     // the LDS was divided for that many workgroups side by side: registers and waves have to allow them too
     int per_cu = 0;
-    DCHK(resident_per_cu(d->block, d->lds_bytes, &per_cu));
+    DCHK(resident_per_cu(d->block, d->parts > 0, d->lds_bytes, &per_cu));
     if (per_cu < cfg->workgroups_per_cu)
       return fail(CBD_E_INVALID, "decoder: a compute unit holds " + std::to_string(per_cu) +
                                  " workgroups of this size, fewer than workgroups_per_cu");
@@ -933,6 +959,23 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
       }
     }
   }
+  if (d->parts > 0 && !g->long_rows.empty() && g->long_rows.size() <= 4096) {
+    // the graph's long rows, their arcs sorted by share (unknown rows go arc by arc through the queues)
+    std::vector<int4> rows = g->long_rows;
+    int64_t total = 0;
+    for (auto &r : rows) { r.w = (int)total; total += r.z; }
+    if (total < 0x7FFFFFF0) {
+      d->n_long_rows = (int32_t)rows.size();
+      DCHK(dmalloc(&d->d_long_rows, rows.size(), &d->bytes));
+      DCHK(dmalloc(&d->d_long_group, rows.size() * ((size_t)d->parts + 2), &d->bytes));
+      DCHK(dmalloc(&d->d_long_arcs, (size_t)total, &d->bytes));
+      DCHK(dmalloc(&d->d_long_idx, (size_t)total, &d->bytes));
+      DCHK(hipMemcpy(d->d_long_rows, rows.data(), sizeof(int4) * rows.size(), hipMemcpyHostToDevice));
+      hipLaunchKernelGGL(cbd::parts_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, g->d_arcs,
+                         d->d_long_rows, d->d_long_group, d->d_long_arcs, d->d_long_idx, d->parts);
+      DCHK(hipGetLastError());
+    }
+  }
   DCHK(dmalloc(&d->d_ctx_n, C + d->pool, &d->bytes));
   DCHK(dmalloc(&d->d_ctx_off, C + d->pool, &d->bytes));
   DCHK(hipMemsetAsync(d->d_ctx_n, 0, sizeof(int32_t) * (C + d->pool), d->stream));
@@ -981,7 +1024,8 @@ int32_t cbd_decoder_free(cbd_decoder *d) {
                   d->d_log, d->d_ctx, d->d_ctx_n, d->d_ctx_off, d->d_hkey, d->d_hval, d->d_hidx, d->d_auto_snap,
                   d->d_gc_mark, d->d_gc_prefix, d->d_gc_cross, d->d_fixed_arcs, d->d_fixed_words, d->d_due_max, d->d_ids_kept,
                   d->d_team, d->d_team_q1, d->d_team_q2, d->d_team_cwin, d->d_team_pub_key, d->d_team_pub_lid,
-                  d->d_team_big_rows, d->d_team_big_group, d->d_team_big_perm};
+                  d->d_team_big_rows, d->d_team_big_group, d->d_team_big_perm,
+                  d->d_long_rows, d->d_long_group, d->d_long_arcs, d->d_long_idx};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (d->h_new) (void)hipHostFree(d->h_new);

@@ -162,6 +162,16 @@ struct AdvanceParams {
   int2 *new_records;       // [C] or null (pinned host memory): x = the channel's records above gc_base after this
   int32_t call_seq;        //     call, y = call_seq: lets the host see when no compaction is due without waiting
   unsigned long long *due_max;  // or null: (call_seq << 32 | largest such count among the call's channels)
+  // frames by parts (run_frame_parts; parts = 0: not used)
+  int32_t parts;           // shares the states are split into
+  int32_t part_slots;      // table slots per share (LDS: what lies behind the layout's hval)
+  int32_t part_q1, part_q2;  // entries per share in the queues (emitting, closure candidates; in the change log's memory)
+  int32_t n_long_rows;
+  const int4 *long_rows;   // [n_long_rows] rows with more than kBigRowArcs emitting arcs: x = state, y = first arc (ascending),
+                           //   z = arcs, w = start in long_arcs
+  const int32_t *long_group;  // [n_long_rows][parts + 2] where each share's arcs begin there (see parts_prepare_rows_kernel)
+  const ArcRec *long_arcs;
+  const int32_t *long_idx;
 };
 
 constexpr int kSnapInts = 8;   // a best-token snapshot: status, best record, cost bits, records in use, channel,
@@ -1263,6 +1273,7 @@ __device__ __forceinline__ int run_frame(const AdvanceParams &p, const Mem<kLds>
 
 }  // namespace cbd
 #include "cbd_lean.hpp"
+#include "cbd_parts.hpp"
 namespace cbd {
 
 // Where the current tokens' arc rows are kept changes with the code that decodes the next frame: the lean code
@@ -1293,7 +1304,7 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
 }
 
 // One call's work on one channel: `pos` is the channel's place in the call's list.
-template <int kBlock>
+template <int kBlock, bool kParts>
 __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const int pos, unsigned char *smem) {
   const int tid = threadIdx.x;
   const int c = p.chan_ids[pos];
@@ -1331,6 +1342,8 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     return G;
   };
   auto g_cost = [&]() { return p.tok_cost + (size_t)c * p.g_tok_cap; };
+  // (frames by parts write the new tokens' costs beside the current ones: every other frame's are here)
+  auto g_cost_alt = [&]() { return (float *)(p.g_hidx + (size_t)c * p.g_slots); };
   int32_t *g_tok_state = p.tok_state + (size_t)c * p.g_tok_cap;
   int2 *bp = p.bp + (size_t)c * p.bp_cap;
   const float *Lbase = p.loglikes + (long long)pos * p.channel_stride;
@@ -1397,6 +1410,13 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
   __syncthreads();
   const LeanMem LM = make_lean_mem(ML.log, p.lds_tok_cap, p.lds_slots, p.lean_log_per_wave);
   bool rows_in_lds = false;   // the current tokens' rows: in LDS (lean frames) or in the row buffer `cur`
+  bool cost_alt = false;      // (kParts) the current tokens' costs are in g_cost_alt
+  bool lds_used = false;      // (kParts) the LDS of the lean tables holds a share's table
+  auto costs_home = [&]() {   // costs to where everybody else looks for them
+    float *gc = g_cost();
+    const float *ga = g_cost_alt();
+    for (int i = tid; i < sh->n_tok; i += kBlock) gc[i] = ga[i];
+  };
   for (int f = p.do_reset ? -1 : 0; f < p.n_frames; ++f) {
     // the next frame's row (staged rows: copied to LDS during this frame; others: only the lean code uses it)
     const float *Lnext = (f >= 0 && f + 1 < p.n_frames) ? Lbase + (long long)(f + 1) * p.num_pdfs : nullptr;
@@ -1448,6 +1468,23 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
         fast = false; slow = true;
       }
     }
+    if constexpr (kParts) {
+      if (slow && f >= 0) {
+        lds_used = true;
+        outcome = run_frame_parts<kBlock>(p, smem + lay.hval, c, sh, cx, Lrow, rows, p.stage_rows ? Lnext : nullptr, hist, owner_maps,
+                                          closure_maps, cur, bp, g_tok_state, last, cost_alt ? g_cost_alt() : g_cost(),
+                                          cost_alt ? g_cost() : g_cost_alt());
+        if (outcome == kFrameOk) { cur ^= 1; cost_alt = !cost_alt; }
+        if (outcome != kFrameRedo) {
+          slow = false;
+        } else {
+          if (cost_alt) { costs_home(); cost_alt = false; }
+          __syncthreads();
+          if (tid < 64) frame_init(sh, hist, false, tid);
+          __syncthreads();
+        }
+      }
+    }
     if (slow) {
       const Mem<false> MG = make_MG();
       outcome = run_frame<false, kBlock>(p, MG, sh, cx, Lrow, rows, p.stage_rows ? Lnext : nullptr, hist, owner_maps, f, cur, bp, g_tok_state, last);
@@ -1456,7 +1493,12 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     if (outcome != kFrameOk) break;
     if (!fast && p.lds_tok_cap > 0 && sh->n_tok <= p.lds_tok_cap) {
       // the token list fits LDS again
-      { float *gc = g_cost(); for (int i = tid; i < sh->n_tok; i += kBlock) ML.t_cost[i] = gc[i]; }
+      if (kParts && lds_used) {
+        for (int i = tid; i < p.lds_slots; i += kBlock) { ML.hval[i] = kEmptyVal; ML.hkey[i] = kEmptyKey; }
+        lds_used = false;
+      }
+      { const float *gc = kParts && cost_alt ? g_cost_alt() : g_cost(); for (int i = tid; i < sh->n_tok; i += kBlock) ML.t_cost[i] = gc[i]; }
+      cost_alt = false;
       fast = true;
       __syncthreads();
     }
@@ -1474,6 +1516,8 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     const int n = sh->n_tok;
     if (fast) {
       { float *gc = g_cost(); for (int i = tid; i < n; i += kBlock) gc[i] = ML.t_cost[i]; }
+    } else if (kParts && cost_alt) {
+      costs_home();
     }
   } else if (outcome != kFrameNoTokens) {
     // (a lean frame without room for its records leaves pieces of the next row on their way to LDS)
@@ -1574,7 +1618,13 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
 template <int kBlock>
 __global__ __launch_bounds__(kBlock, 4) void advance_kernel(AdvanceParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  advance_channel<kBlock>(p, (int)blockIdx.x, smem);
+  advance_channel<kBlock, false>(p, (int)blockIdx.x, smem);
+}
+// The same with frames by parts (run_frame_parts), for graphs with long rows.
+template <int kBlock>
+__global__ __launch_bounds__(kBlock, 4) void advance_parts_kernel(AdvanceParams p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  advance_channel<kBlock, true>(p, (int)blockIdx.x, smem);
 }
 
 // The same with 120 instead of 128 vector registers per wave, for launches that start while result walks of
@@ -1588,7 +1638,7 @@ __global__ __launch_bounds__(kBlock, 4) void advance_kernel(AdvanceParams p) {
 template <int kBlock>
 __global__ __launch_bounds__(kBlock, 4) __attribute__((amdgpu_num_vgpr(60))) void advance_beside_kernel(AdvanceParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  advance_channel<kBlock>(p, (int)blockIdx.x, smem);
+  advance_channel<kBlock, false>(p, (int)blockIdx.x, smem);
 }
 
 // ---- self-test of the cross-lane primitives ------------------------------------

@@ -98,7 +98,6 @@ struct TeamParams {
 };
 
 struct TeamLayout { uint32_t sh, hist, bitmap, stage, ctx, L, hval, hkey, hidx, total; };
-struct TeamLive { float cost; int32_t first; int32_t deg; int32_t idx; };   // a token that survived pruning, on its way to a lane
 struct TeamShared {
   int32_t abort_flag, fault, failed;
   int32_t n_mine;            // tokens this member has made in the current frame
@@ -118,7 +117,7 @@ __host__ __device__ inline TeamLayout team_layout(int num_pdfs_staged, int ctx_l
   l.sh = o; o += align_up((uint32_t)sizeof(TeamShared), 16);
   l.hist = o; o += 256 * 4;
   l.bitmap = o; o += kBloomWords * 4;
-  l.stage = o; o += (uint32_t)n_waves * 64 * (uint32_t)sizeof(TeamLive);   // per wave: up to 64 live tokens waiting for a full group
+  l.stage = o; o += (uint32_t)n_waves * 64 * (uint32_t)sizeof(LiveToken);   // per wave: up to 64 live tokens waiting for a full group
   l.ctx = o; o += align_up((uint32_t)ctx_lds_cap * 4, 16);
   l.L = o; o += align_up((uint32_t)num_pdfs_staged * 4, 16);
   l.hval = o; o += (uint32_t)slots * 8;
@@ -126,13 +125,6 @@ __host__ __device__ inline TeamLayout team_layout(int num_pdfs_staged, int ctx_l
   l.hidx = o; o += align_up((uint32_t)slots * 2, 16);
   l.total = o;
   return l;
-}
-
-__device__ __forceinline__ uint32_t team_hash(uint32_t state) { return state * 2654435761u; }
-// which member owns a state, and the state's home slot in that member's table (different bits of the hash)
-__device__ __forceinline__ int team_owner(uint32_t state, int k) { return (int)__umulhi(team_hash(state), (uint32_t)k); }
-__device__ __forceinline__ uint32_t team_home(uint32_t state, uint32_t slots) {
-  return __umulhi(team_hash(state) * 0x9E3779B1u, slots);
 }
 
 // Barrier across the k members of a team.  The word counts arrivals in its low 30 bits (the counter runs on from
@@ -214,7 +206,7 @@ __device__ __forceinline__ int team_count(const unsigned long long *cnt, int o) 
 
 // Finds or makes the slot of `state` in this member's table.  Returns false if the table is full.
 __device__ __forceinline__ bool team_slot(uint32_t *hkey, uint32_t slots, uint32_t state, uint32_t &h) {
-  h = team_home(state, slots);
+  h = share_home(state, slots);
   uint32_t k = atomicCAS(&hkey[h], kEmptyKey, state);
   uint32_t probe = 1;
   while (k != kEmptyKey && k != state && probe < slots) {
@@ -226,7 +218,7 @@ __device__ __forceinline__ bool team_slot(uint32_t *hkey, uint32_t slots, uint32
 }
 // The slot of a state that is known to be in the table.
 __device__ __forceinline__ uint32_t team_find(const uint32_t *hkey, uint32_t slots, uint32_t state) {
-  uint32_t h = team_home(state, slots);
+  uint32_t h = share_home(state, slots);
   uint32_t probe = 0;
   while (hkey[h] != state && probe < slots) { h = h + 1 == slots ? 0 : h + 1; ++probe; }
   return h;
@@ -285,7 +277,7 @@ __device__ __forceinline__ void team_emit(const TeamParams &tp, const Ctx &cx, c
       lmin = o < lmin ? o : lmin;
       e[u].dst = (uint32_t)rec[u].dst; e[u].cost = cand; e[u].arc = (uint32_t)a[u]; e[u].from = src_tok; e[u].row = rec[u].row;
       e[u].meta = rec[u].meta & 0xFFFF0000u;
-      owner[u] = team_owner(e[u].dst, tp.k);
+      owner[u] = share_owner(e[u].dst, tp.k);
     }
   }
   team_push<U>(q1c, sh->cnt1, sh, tp.k, tp.q_cap, me, act, owner, e, lane);
@@ -320,7 +312,7 @@ __global__ __launch_bounds__(256) void team_prepare_rows_kernel(const ArcRec *ar
   const int4 row = big_rows[blockIdx.x];
   if (threadIdx.x <= kTeamMax) count[threadIdx.x] = 0;
   __syncthreads();
-  for (int j = threadIdx.x; j < row.z; j += blockDim.x) atomicAdd(&count[team_owner((uint32_t)arcs[row.y + j].dst, k)], 1);
+  for (int j = threadIdx.x; j < row.z; j += blockDim.x) atomicAdd(&count[share_owner((uint32_t)arcs[row.y + j].dst, k)], 1);
   __syncthreads();
   if (threadIdx.x == 0) {
     int run = 0;
@@ -329,7 +321,7 @@ __global__ __launch_bounds__(256) void team_prepare_rows_kernel(const ArcRec *ar
   }
   __syncthreads();
   for (int j = threadIdx.x; j < row.z; j += blockDim.x) {
-    const int o = team_owner((uint32_t)arcs[row.y + j].dst, k);
+    const int o = share_owner((uint32_t)arcs[row.y + j].dst, k);
     big_perm[row.w + atomicAdd(&fill[o], 1)] = row.y + j;
   }
 }
@@ -380,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
   TeamShared *sh = (TeamShared *)(smem + lay.sh);
   uint32_t *hist = (uint32_t *)(smem + lay.hist);
   uint32_t *bitmap = (uint32_t *)(smem + lay.bitmap);
-  TeamLive *stage = (TeamLive *)(smem + lay.stage) + wave * 64;
+  LiveToken *stage = (LiveToken *)(smem + lay.stage) + wave * 64;
   int32_t *ctx_lds = (int32_t *)(smem + lay.ctx);
   float *Lstage = (float *)(smem + lay.L);
   uint64_t *hval = (uint64_t *)(smem + lay.hval);
@@ -540,7 +532,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       // group at a time: their rows are read then, one lane per token (rows are short, the long ones are shared
       // out), two arcs of a token together.
       auto expand_staged = [&](int n) {
-        TeamLive tk; tk.cost = 0.0f; tk.first = 0; tk.deg = 0; tk.idx = 0;
+        LiveToken tk; tk.cost = 0.0f; tk.first = 0; tk.deg = 0; tk.idx = 0;
         if (lane < n) {
           tk = stage[lane];
           // (the team keeps 8 bytes of a token's row: first emitting arc, first epsilon arc; the list a reset leaves
@@ -585,7 +577,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
           if (n_new == 0) continue;   // uniform
           if (n_staged + n_new > 64) { expand_staged(n_staged); n_staged = 0; }
           if (alive) {
-            TeamLive tk; tk.cost = c4[u]; tk.first = 0; tk.deg = 0; tk.idx = i;
+            LiveToken tk; tk.cost = c4[u]; tk.first = 0; tk.deg = 0; tk.idx = i;
             stage[n_staged + (int)__popcll(lm & ((1ull << lane) - 1ull))] = tk;
           }
           n_staged += n_new;
@@ -725,7 +717,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
             if (ok) {
               ce.dst = (uint32_t)rec.dst; ce.cost = cc; ce.arc = (uint32_t)can; ce.from = (int32_t)ps; ce.row = rec.row;
               ce.meta = rec.meta & 0xFFFF0000u;
-              owner = team_owner(ce.dst, k);
+              owner = share_owner(ce.dst, k);
               const uint32_t o = f2ord(cc);
               cmin = o < cmin ? o : cmin;
             }
@@ -906,9 +898,9 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       const int ncw = sh->n_cwin;
       for (int i = tid; i < ncw; i += kBlock) {
         const TeamClosureWin cw = cwin[i];
-        const int o = team_owner(cw.parent_state, k);
+        const int o = share_owner(cw.parent_state, k);
         const uint32_t *pk = pub_key + (size_t)o * slots;
-        uint32_t h = team_home(cw.parent_state, slots);
+        uint32_t h = share_home(cw.parent_state, slots);
         uint32_t probe = 0;
         while (pk[h] != cw.parent_state && probe < slots) {   // (plain reads: the barrier's fence made them current)
           h = h + 1 == slots ? 0 : h + 1; ++probe;

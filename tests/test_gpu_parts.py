@@ -1,0 +1,88 @@
+"""GPU parity of frames decoded by parts (graphs with long rows, frames that outgrow the LDS tables): shares of the states
+from one to eight, long rows into states with and without closure lists, an unprepared mix of long and ordinary rows, pruning,
+final costs, context swaps, frames that move between the LDS tables and the shares, and frames whose queues are too small."""
+import numpy as np
+import pytest
+
+from paper_2306_15685_amd import synth
+
+from test_gpu_parity import run_batch, torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def hub_graph(S, P, hubs, hub_arcs, mean_degree=3.0, eps=0.15, finals=False, seed=1):
+    """An HCLG-style random graph in which a few states, the start state among them, have long rows (each between 513 and
+    hub_arcs emitting arcs more), and one arc in twenty leads to one of these."""
+    g = synth.make_graph(S, P, 500, eps, seed_stream=(seed, 7), mean_degree=mean_degree, with_finals=finals)
+    rng = np.random.default_rng(seed)
+    hub = np.concatenate([[g.start_state], 1 + rng.choice(S - 1, hubs - 1, replace=False)])
+    dst = g.dst.copy()
+    to_hub = (rng.random(g.num_arcs) < 0.05) & (g.ilabel > 0)
+    dst[to_hub] = rng.choice(hub, int(to_hub.sum()))
+    rows = [[dst[a:b], g.ilabel[a:b], g.olabel[a:b], g.weight[a:b]] for a, b in zip(g.row_offsets[:-1], g.row_offsets[1:])]
+    for i, h in enumerate(hub):
+        n = 513 if i == 1 else int(rng.integers(513, hub_arcs + 1))
+        more = [rng.integers(0, S, n), rng.integers(1, P + 1, n), rng.integers(0, 500, n), rng.uniform(0.0, 3.0, n)]
+        rows[h] = [np.concatenate(x) for x in zip(rows[h], more)]
+    row = np.concatenate([[0], np.cumsum([len(r[0]) for r in rows])]).astype(np.int32)
+    d, il, ol, w = (np.concatenate([r[k] for r in rows]) for k in range(4))
+    return synth.Graph(S, int(row[-1]), P, 500, g.start_state, row, d.astype(np.int32), il.astype(np.int32),
+                       ol.astype(np.int32), w.astype(np.float32), g.final_cost)
+
+
+def inputs(torch, g, C, T, sigma, seed, arcs=200):
+    L = synth.make_loglikes(C, T, g.num_pdfs, sigma, seed_stream=(seed,), device="cuda")
+    rng = np.random.default_rng(seed)
+    ctxs = [np.sort(rng.choice(g.num_arcs, size=arcs, replace=False)).astype(np.int32) for _ in range(C)]
+    return L, ctxs, rng.uniform(-4.0, 2.0, C).astype(np.float32)
+
+
+@pytest.mark.parametrize("hash_log2,block", [(12, 1024), (13, 1024), (14, 1024), (15, 1024), (14, 960), (14, 512), (14, 256)])
+def test_shares_and_long_rows(torch_cuda, hash_log2, block):  # noqa: F811
+    """64 tokens of LDS tables leave some 2,900 slots: one share for 2,048 tokens, two, four and eight for twice as many
+    each.  Most frames hold more than 64 tokens and less than 2,048; rows read from device memory at 1,500 pdfs."""
+    print("parts", hash_log2, block, flush=True)
+    g = hub_graph(2_000, 1_500 if hash_log2 == 13 else 64, 6, 1_500, seed=hash_log2)
+    L, ctxs, offs = inputs(torch_cuda, g, 3, 24, 2.5, hash_log2)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=7.0, max_active=0, chunks=[1, 6, 17], hash_log2=hash_log2, lookup_mode=hash_log2 & 1,
+                  lds_token_cap=64, block_threads=block)
+    assert s["slow_frames"] > s["frames"] // 2 and s["eps_arcs"] > 0 and s["max_tokens"] > 300
+
+
+def test_pruning_finals_and_swap(torch_cuda):  # noqa: F811
+    g = hub_graph(4_000, 96, 5, 900, finals=True, seed=3)
+    L, ctxs, offs = inputs(torch_cuda, g, 4, 30, 2.0, 3)
+    swap = (10, [c[::2] for c in ctxs], -offs)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=8.0, max_active=150, chunks=[10, 20], hash_log2=14, use_final=True,
+                  swap=swap, lds_token_cap=128)
+    assert s["slow_frames"] > 0 and s["active_tokens"] < s["tokens"]
+
+
+def test_frames_move_between_the_tables(torch_cuda):  # noqa: F811
+    """Around as many tokens as the LDS tables hold: frames go to the shares and come back."""
+    g = hub_graph(6_000, 400, 3, 700, seed=5)
+    L, ctxs, offs = inputs(torch_cuda, g, 4, 40, 4.0, 5)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=9.0, max_active=0, chunks=[3, 17, 20], hash_log2=13, lds_token_cap=192)
+    assert 0 < s["slow_frames"] < s["frames"]
+
+
+def test_queues_too_small(torch_cuda):  # noqa: F811
+    """More candidates than a share's queue holds (640 emitting, 384 closure candidates) over a graph of 300 states, within
+    the 512 tokens and 1,024 improvements of the general code, which decodes such frames."""
+    g = hub_graph(300, 40, 2, 600, seed=9)
+    L, ctxs, offs = inputs(torch_cuda, g, 2, 12, 1.0, 9, arcs=30)
+    s = run_batch(torch_cuda, g, L, ctxs, np.abs(offs), beam=6.0, max_active=0, chunks=[5, 7], hash_log2=10, lds_token_cap=64)
+    assert s["slow_frames"] > 0 and s["status"] == 0
+
+
+@pytest.mark.parametrize("words", [300, 6_000])
+def test_lexicon_loop(torch_cuda, words):  # noqa: F811
+    """Small enough for the LDS tables to come and go, and large enough for four shares."""
+    g = synth.make_lexicon_graph(48, words, seed_stream=(5, words))
+    L = synth.make_loglikes(3, 25, 48, 2.0, seed_stream=(5,), device="cuda")
+    w = synth.scaled(synth.WORKLOADS["e2e"], channels=3, config_id=71)
+    ctxs, offs = synth.make_contexts(w, g)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=10.0, max_active=800 if words > 300 else 100, chunks=[3, 10, 12], hash_log2=15,
+                  lookup_mode=1, lds_token_cap=0 if words > 300 else 256)
+    assert s["slow_frames"] > 0 and s["status"] == 0
