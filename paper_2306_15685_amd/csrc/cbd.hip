@@ -217,10 +217,8 @@ struct cbd_decoder {
   int32_t team_n_big_rows = 0;
   // frames by parts (parts = 0: not used)
   int parts = 0, part_slots = 0, part_q1 = 0, part_q2 = 0;
-  int4 *d_long_rows = nullptr;
-  int32_t *d_long_group = nullptr, *d_long_idx = nullptr;
-  cbd::ArcRec *d_long_arcs = nullptr;
-  int32_t n_long_rows = 0;
+  char *d_long = nullptr;          // the layout of the graph's long rows ...
+  cbd::LongRows long_rows{};       // ... and its pieces
   std::vector<int32_t> h_tmp;
   std::vector<int32_t> h_static_meta;   // result headers of cbd_best_paths_static on their way to the caller
   size_t bytes = 0;
@@ -262,6 +260,47 @@ hipError_t resident_per_cu(int block, bool parts, uint32_t lds, int *n) {
   if (block == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<512> : cbd::advance_kernel<512>, 512, lds);
   if (block == 960) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<960> : cbd::advance_kernel<960>, 960, lds);
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<1024> : cbd::advance_kernel<1024>, 1024, lds);
+}
+
+// Lays out the graph's long rows for k shares with tables of `slots` slots each (prepare_long_rows_kernel): as many of
+// them as leave half of the slots to other states, 4,096 at most.  Rows without a layout go arc by arc through the queues.
+hipError_t prepare_long_rows(cbd_decoder *d, int k, int slots) {
+  std::vector<int4> rows;
+  int64_t total = 0;
+  for (int4 r : d->g->long_rows) {
+    if (rows.size() == 4096 || total + r.z > (int64_t)k * slots / 2) break;
+    r.w = (int)total;
+    total += r.z;
+    rows.push_back(r);
+  }
+  if (rows.empty()) return hipSuccess;
+  // (one allocation: [arcs][keys][rows][group][meta][full], each a multiple of 16 bytes)
+  const size_t n = rows.size(), arcs_b = sizeof(cbd::LongArc) * (size_t)total, image_b = sizeof(uint32_t) * (size_t)k * slots,
+               rows_b = sizeof(int4) * n, group_b = (sizeof(int32_t) * n * ((size_t)k + 2) + 15) / 16 * 16,
+               meta_b = (sizeof(uint32_t) * (size_t)total + 15) / 16 * 16;
+  hipError_t e = dmalloc(&d->d_long, arcs_b + image_b + rows_b + group_b + meta_b + 16, &d->bytes);
+  if (e != hipSuccess) return e;
+  char *at = d->d_long;
+  cbd::LongRows &l = d->long_rows;
+  l.arcs = (cbd::LongArc *)at; at += arcs_b;
+  l.image = (uint32_t *)at; at += image_b;
+  l.rows = (int4 *)at; at += rows_b;
+  l.group = (int32_t *)at; at += group_b;
+  l.meta = (uint32_t *)at; at += meta_b;
+  int32_t *d_full = (int32_t *)at, full = 0;
+  e = hipMemsetAsync((void *)l.image, 0xFF, image_b, d->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(d_full, 0, sizeof(int32_t), d->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync((void *)l.rows, rows.data(), rows_b, hipMemcpyHostToDevice, d->stream);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(cbd::prepare_long_rows_kernel, dim3((unsigned)n), dim3(cbd::kPrepRowThreads), 0, d->stream, d->g->d_arcs,
+                       l.rows, (int32_t *)l.group, (cbd::LongArc *)l.arcs, (uint32_t *)l.meta, (uint32_t *)l.image, (uint32_t)slots,
+                       d_full, k);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(&full, d_full, sizeof(int32_t), hipMemcpyDeviceToHost, d->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(d->stream);
+  l.n = e == hipSuccess && !full ? (int32_t)n : 0;
+  return e;
 }
 
 // A team launch.  The members of a team wait for one another inside the kernel, so all of a launch's workgroups
@@ -325,8 +364,7 @@ AdvanceParams base_params(const cbd_decoder *d) {
   p.bp = d->d_bp; p.g_log = d->d_log; p.ctx = d->d_ctx; p.ctx_n = d->d_ctx_n; p.ctx_off = d->d_ctx_off;
   p.g_hkey = d->d_hkey; p.g_hval = d->d_hval; p.g_hidx = d->d_hidx;
   p.parts = d->parts; p.part_slots = d->part_slots; p.part_q1 = d->part_q1; p.part_q2 = d->part_q2;
-  p.n_long_rows = d->n_long_rows; p.long_rows = d->d_long_rows; p.long_group = d->d_long_group;
-  p.long_arcs = d->d_long_arcs; p.long_idx = d->d_long_idx;
+  p.lr = d->long_rows;
   return p;
 }
 
@@ -959,23 +997,7 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
       }
     }
   }
-  if (d->parts > 0 && !g->long_rows.empty() && g->long_rows.size() <= 4096) {
-    // the graph's long rows, their arcs sorted by share (unknown rows go arc by arc through the queues)
-    std::vector<int4> rows = g->long_rows;
-    int64_t total = 0;
-    for (auto &r : rows) { r.w = (int)total; total += r.z; }
-    if (total < 0x7FFFFFF0) {
-      d->n_long_rows = (int32_t)rows.size();
-      DCHK(dmalloc(&d->d_long_rows, rows.size(), &d->bytes));
-      DCHK(dmalloc(&d->d_long_group, rows.size() * ((size_t)d->parts + 2), &d->bytes));
-      DCHK(dmalloc(&d->d_long_arcs, (size_t)total, &d->bytes));
-      DCHK(dmalloc(&d->d_long_idx, (size_t)total, &d->bytes));
-      DCHK(hipMemcpy(d->d_long_rows, rows.data(), sizeof(int4) * rows.size(), hipMemcpyHostToDevice));
-      hipLaunchKernelGGL(cbd::parts_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, g->d_arcs,
-                         d->d_long_rows, d->d_long_group, d->d_long_arcs, d->d_long_idx, d->parts);
-      DCHK(hipGetLastError());
-    }
-  }
+  if (d->parts > 0) DCHK(prepare_long_rows(d, d->parts, d->part_slots));
   DCHK(dmalloc(&d->d_ctx_n, C + d->pool, &d->bytes));
   DCHK(dmalloc(&d->d_ctx_off, C + d->pool, &d->bytes));
   DCHK(hipMemsetAsync(d->d_ctx_n, 0, sizeof(int32_t) * (C + d->pool), d->stream));
@@ -1025,7 +1047,7 @@ int32_t cbd_decoder_free(cbd_decoder *d) {
                   d->d_gc_mark, d->d_gc_prefix, d->d_gc_cross, d->d_fixed_arcs, d->d_fixed_words, d->d_due_max, d->d_ids_kept,
                   d->d_team, d->d_team_q1, d->d_team_q2, d->d_team_cwin, d->d_team_pub_key, d->d_team_pub_lid,
                   d->d_team_big_rows, d->d_team_big_group, d->d_team_big_perm,
-                  d->d_long_rows, d->d_long_group, d->d_long_arcs, d->d_long_idx};
+                  d->d_long};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (d->h_new) (void)hipHostFree(d->h_new);

@@ -117,6 +117,17 @@ struct __attribute__((aligned(128))) ChanState {
 static_assert(sizeof(ChanState) == 256, "one channel's state fills two 128-byte lines");
 #endif
 
+// Rows with more than kBigRowArcs emitting arcs as a decoder lays them out (prepare_long_rows_kernel).
+struct LongArc;
+struct LongRows {
+  int32_t n;               // rows laid out (0: none)
+  const int4 *rows;        // [n] x = state, y = first arc (ascending), z = arcs, w = start in arcs
+  const int32_t *group;    // [n][shares + 2] where each share's arcs begin there
+  const LongArc *arcs;
+  const uint32_t *meta;    // the same places: ArcRec::meta without the label
+  const uint32_t *image;   // [shares][slots] keys that every frame's tables start with
+};
+
 struct AdvanceParams {
   const int4 *off2;        // [S]: x = first arc of the state, y = its first epsilon-input arc, z = end of those
                            //      (start of its closure list), w = end of the closure list
@@ -166,12 +177,7 @@ struct AdvanceParams {
   int32_t parts;           // shares the states are split into
   int32_t part_slots;      // table slots per share (LDS: what lies behind the layout's hval)
   int32_t part_q1, part_q2;  // entries per share in the queues (emitting, closure candidates; in the change log's memory)
-  int32_t n_long_rows;
-  const int4 *long_rows;   // [n_long_rows] rows with more than kBigRowArcs emitting arcs: x = state, y = first arc (ascending),
-                           //   z = arcs, w = start in long_arcs
-  const int32_t *long_group;  // [n_long_rows][parts + 2] where each share's arcs begin there (see parts_prepare_rows_kernel)
-  const ArcRec *long_arcs;
-  const int32_t *long_idx;
+  LongRows lr;
 };
 
 constexpr int kSnapInts = 8;   // a best-token snapshot: status, best record, cost bits, records in use, channel,

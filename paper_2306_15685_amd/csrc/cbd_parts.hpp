@@ -13,10 +13,11 @@
 //      state has a closure list then note their state's token
 //   4  records of closure winners get their predecessor; histogram cut and scalars of the next frame
 //
-// What bounds it: vector instructions and L2 latency in turn (20,000 arcs of a hub are evaluated three times per frame
+// What bounds it: vector instructions and L2 latency in turn (20,000 arcs of a hub are costed three times per frame
 // rather than stored and read back).  The table in device memory that it replaces took a chain of six dependent
 // device-memory accesses per candidate, most of them atomics: 160 channels x 40 frames of a 20,000-word lexicon loop
-// 30.1 -> 5.5 ms (755 -> 130 us per frame), 148 channels x 31 frames of 5,600 words 6.3 -> 1.9 ms.
+// 30.3 -> 4.05 ms (755 -> 88 us per frame: 15 for reading and expanding tokens, 5 for the hub's minimum, 3 closure lists,
+// 11 to set the tables up, 19 recombination, 27 winners), 148 channels x 31 frames of 5,600 words 6.3 -> 1.9 ms.
 // Graphs without long rows keep the general code for the few frames that outgrow LDS: with this code beside the lean
 // frames in their kernel, the register allocator spills 25 instead of 6 vector registers and the lean frames take 3 to 6 %
 // longer, which is more than the frames that outgrow LDS are worth there (2,048 channels at beam 16: 10.24 -> 10.85 ms).
@@ -51,33 +52,14 @@ __device__ __forceinline__ uint32_t share_home(uint32_t state, uint32_t slots) {
   return __umulhi(share_hash(state) * 0x9E3779B1u, slots);
 }
 
-// One workgroup per long row: its arcs sorted by the share that owns their destination (a copy of the record and the
-// arc's index, so that a share's arcs are one stream), those whose destination has a closure list behind all others
-// (group k: they go through the queues).  The order inside a group does not matter.
-__global__ __launch_bounds__(256) void parts_prepare_rows_kernel(const ArcRec *arcs, const int4 *rows, int32_t *group,
-                                                                 ArcRec *sorted, int32_t *sorted_idx, int k) {
-  __shared__ int32_t count[kPartsMax + 1], fill[kPartsMax + 1];
-  const int4 row = rows[blockIdx.x];
-  if (threadIdx.x <= kPartsMax) count[threadIdx.x] = 0;
-  __syncthreads();
-  for (int j = threadIdx.x; j < row.z; j += blockDim.x) {
-    const ArcRec r = arcs[row.y + j];
-    atomicAdd(&count[meta_cl(r.meta) ? k : share_owner((uint32_t)r.dst, k)], 1);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int o = 0; o <= k; ++o) { group[blockIdx.x * (k + 2) + o] = run; fill[o] = run; run += count[o]; }
-    group[blockIdx.x * (k + 2) + k + 1] = run;
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < row.z; j += blockDim.x) {
-    const ArcRec r = arcs[row.y + j];
-    const int at = row.w + atomicAdd(&fill[meta_cl(r.meta) ? k : share_owner((uint32_t)r.dst, k)], 1);
-    sorted[at] = r;
-    sorted_idx[at] = row.y + j;
-  }
-}
+// An arc of a long row as it is laid out when the decoder is made: everything a frame needs to cost it, and the slot of
+// its destination in its share's table.
+struct __attribute__((aligned(16))) LongArc {
+  float weight;
+  uint32_t arc;       // library index
+  uint32_t slot_pdf;  // bits 0..15 slot, 16..31 pdf
+  int32_t row;        // first arc of the destination (long_meta: its degrees)
+};
 
 // Places in the queues of the entries' owners for up to U entries per lane: lane o adds the wave's count for owner o,
 // so one LDS atomic hands out the places of all owners.
@@ -104,6 +86,67 @@ __device__ __forceinline__ void parts_places(int32_t *cnt, int k, const bool (&a
   for (int u = 0; u < U; ++u) pos[u] = __shfl(base, owner[u], 64) + rank[u];
 }
 
+// One workgroup per long row: its arcs sorted by the share that owns their destination, so that a share's arcs are one
+// stream; those whose destination has a closure list lie behind all others (group k: they go through the queues).  The
+// order inside a group does not matter.  The destinations get their slots here, once: image[share][slot] is the key table
+// as every frame starts from it (all ones before; *full: a share has no slot left).  An arc of a long row is then
+// recombined without a search: the shares of a frame with 20,000 such arcs in 19 instead of 33 us (5.45 -> 4.05 ms a pass).
+constexpr int kPrepRowThreads = 1024;
+__global__ __launch_bounds__(kPrepRowThreads) void prepare_long_rows_kernel(const ArcRec *arcs, const int4 *rows, int32_t *group,
+                                                                            LongArc *out, uint32_t *out_meta, uint32_t *image,
+                                                                            uint32_t slots, int32_t *full, int k) {
+  __shared__ int32_t count[kPartsMax + 1], fill[kPartsMax + 1];
+  const int4 row = rows[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid <= kPartsMax) count[tid] = 0;
+  __syncthreads();
+  // (a wave's arcs are counted, and get their places, with one atomic per group)
+  for (int j0 = tid - lane; j0 < row.z; j0 += kPrepRowThreads) {   // uniform
+    const int j = j0 + lane;
+    const bool act[1] = {j < row.z};
+    ArcRec r; r.dst = 0; r.weight = 0.0f; r.row = 0; r.meta = 0;
+    if (act[0]) r = arcs[row.y + j];
+    const int to[1] = {meta_cl(r.meta) ? k : share_owner((uint32_t)r.dst, k)};
+    int at[1];
+    parts_places<1>(count, k + 1, act, to, lane, at);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int run = 0;
+    for (int o = 0; o <= k; ++o) { group[blockIdx.x * (k + 2) + o] = run; fill[o] = run; run += count[o]; }
+    group[blockIdx.x * (k + 2) + k + 1] = run;
+  }
+  __syncthreads();
+  for (int j0 = tid - lane; j0 < row.z; j0 += kPrepRowThreads) {   // uniform
+    const int j = j0 + lane;
+    const bool act[1] = {j < row.z};
+    ArcRec r; r.dst = 0; r.weight = 0.0f; r.row = 0; r.meta = 0;
+    if (act[0]) r = arcs[row.y + j];
+    const uint32_t state = (uint32_t)r.dst;
+    const int o = share_owner(state, k);
+    const int to[1] = {meta_cl(r.meta) ? k : o};
+    int at[1];
+    parts_places<1>(fill, k + 1, act, to, lane, at);
+    if (!act[0]) continue;
+    uint32_t h = 0;
+    if (!meta_cl(r.meta)) {
+      uint32_t *keys = image + (size_t)o * slots;
+      h = share_home(state, slots);
+      uint32_t key = atomicCAS(&keys[h], kEmptyKey, state);
+      for (uint32_t probe = 1; key != kEmptyKey && key != state && probe < slots; ++probe) {
+        h = h + 1 == slots ? 0 : h + 1;
+        key = atomicCAS(&keys[h], kEmptyKey, state);
+      }
+      if (key != kEmptyKey && key != state) *full = 1;
+    }
+    LongArc l;
+    l.weight = r.weight; l.arc = (uint32_t)(row.y + j); l.row = r.row;
+    l.slot_pdf = h | (((r.meta & 0xFFFFu) - 1u) << 16);
+    out[row.w + at[0]] = l;
+    out_meta[row.w + at[0]] = r.meta & 0xFFFF0000u;
+  }
+}
+
 // The table of the share at hand.
 struct PartTable {
   uint64_t *hval;
@@ -111,8 +154,8 @@ struct PartTable {
   uint32_t slots;
 };
 
-// E[state] = min key.  A table without a free slot sets sh->redo.
-__device__ __forceinline__ void part_min(const PartTable &T, Shared *sh, uint32_t state, uint64_t key) {
+// E[state] = min key; returns the state's slot.  A table without a free one sets sh->redo.
+__device__ __forceinline__ uint32_t part_min(const PartTable &T, Shared *sh, uint32_t state, uint64_t key) {
   uint32_t h = share_home(state, T.slots);
   uint32_t k = atomicCAS(&T.hkey[h], kEmptyKey, state);
   uint32_t probe = 1;
@@ -124,6 +167,7 @@ __device__ __forceinline__ void part_min(const PartTable &T, Shared *sh, uint32_
   }
   if (k == kEmptyKey || k == state) atomicMin((unsigned long long *)&T.hval[h], (unsigned long long)key);
   else sh->redo = 1;
+  return h;
 }
 // The slot of a state that is in the table.
 __device__ __forceinline__ uint32_t part_find(const PartTable &T, uint32_t state) {
@@ -238,9 +282,16 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   uint8_t *cmap = closure_maps + wave * 64;
   int32_t *cnt1 = sh->wcount, *cnt2 = sh->wcount + kPartsMax;   // entries per queue
   int32_t *n_made = &sh->wbase[0];                             // tokens so far
+  int32_t *n_lists = &sh->wbase[1];                            // candidates noted for step 2
+  // step 2's work: (first record, records, cost, entry) of every queued candidate whose state has a closure list
+  int4 *lists = (int4 *)(region + NW * 64 * sizeof(LiveToken));
+  const int lists_cap = (int)((p.part_slots * 12 - NW * 64 * (int)sizeof(LiveToken)) / 16);
   const bool hist_on = p.max_active > 0 && p.beam > 0.0f && p.beam < __builtin_inff();
   const float inv = 256.0f / p.beam;
   if (tid < 16) { sh->wcount[tid] = 0; sh->wbase[tid] = 0; }
+#ifdef CBD_PROFILE
+  if (tid == 0) sh->prof_last = wall_clock64();
+#endif
   __syncthreads();
 
   // ---- 1: prune and expand
@@ -278,6 +329,19 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     parts_places<2>(cnt1, k, pass, owner, lane, at);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
+      const bool list = pass[q] && meta_cl(rec[q].meta) != 0;
+      const unsigned long long lm = __ballot(list);
+      if (lm != 0) {   // uniform
+        int first = 0;
+        if (lane == 0) first = atomicAdd(n_lists, (int)__popcll(lm));
+        const int i = __builtin_amdgcn_readfirstlane(first) + (int)__popcll(lm & ((1ull << lane) - 1ull));
+        if (list) {
+          if (i < lists_cap)
+            lists[i] = make_int4(rec[q].row + (int)meta_ed(rec[q].meta) + (int)meta_xd(rec[q].meta), (int)meta_cl(rec[q].meta),
+                                 (int)__float_as_uint(cand[q]), owner[q] * cap1 + at[q]);
+          else sh->fault = 1;
+        }
+      }
       if (pass[q]) {
         if (at[q] < cap1) {
           PartEntry e;
@@ -291,7 +355,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     }
   };
   {
-    // Most tokens of a frame like this fall to the histogram cut: only the costs are read for all of them (four tiles
+    // Most tokens of a frame like this fall to the histogram cut: only the costs are read for all of them (eight tiles
     // of a wave at a time); the live ones are gathered in the wave's staging list and expanded 64 at a time.
     LiveToken *stage = (LiveToken *)region + wave * 64;
     auto expand_staged = [&](int n) {
@@ -333,18 +397,18 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       }
     };
     int n_staged = 0;
-    for (int base = wave * 64; base < n_tok; base += 4 * kBlock) {   // uniform
-      float c4[4];
+    for (int base = wave * 64; base < n_tok; base += 8 * kBlock) {   // uniform
+      float cost[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < 8; ++u) {
         const int i = base + u * kBlock + lane;
-        c4[u] = i < n_tok ? cost_in[i] : __builtin_inff();
+        cost[u] = i < n_tok ? cost_in[i] : __builtin_inff();
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < 8; ++u) {
         const int i = base + u * kBlock + lane;
-        const float r = c4[u] - best;
-        bool alive = i < n_tok && !(r > p.beam) && c4[u] < __builtin_inff();
+        const float r = cost[u] - best;
+        bool alive = i < n_tok && !(r > p.beam) && cost[u] < __builtin_inff();
         if (alive && cut < 255) {
           int bin = (int)floorf(r * inv);
           bin = bin > 255 ? 255 : bin;
@@ -356,7 +420,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
         if (n_new == 0) continue;   // uniform
         if (n_staged + n_new > 64) { expand_staged(n_staged); n_staged = 0; }
         if (alive) {
-          LiveToken tk; tk.cost = c4[u]; tk.first = 0; tk.deg = 0; tk.idx = i;
+          LiveToken tk; tk.cost = cost[u]; tk.first = 0; tk.deg = 0; tk.idx = i;
           stage[n_staged + (int)__popcll(lm & ((1ull << lane) - 1ull))] = tk;
         }
         n_staged += n_new;
@@ -365,16 +429,22 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     if (n_staged > 0) expand_staged(n_staged);
   }
   __syncthreads();
+  CBD_STAMP(0);   // (diagnostic: tokens read, live ones expanded)
   const int n_big = min(sh->n_big, kBigRows);
   // an announced long row's place among the prepared ones, or -1
   auto row_id = [&](int r) {
     const int first = sh->big_first[r];
-    int lo = 0, hi = p.n_long_rows;
+    int lo = 0, hi = p.lr.n;
     while (lo < hi) {   // uniform
       const int mid = (lo + hi) >> 1;
-      if (p.long_rows[mid].y < first) lo = mid + 1; else hi = mid;
+      if (p.lr.rows[mid].y < first) lo = mid + 1; else hi = mid;
     }
-    return (lo < p.n_long_rows && p.long_rows[lo].y == first) ? lo : -1;
+    return (lo < p.lr.n && p.lr.rows[lo].y == first) ? lo : -1;
+  };
+  auto long_cost = [&](const LongArc &l, float cost) {
+    float w = l.weight;
+    if (ctx_contains(cx, (int)l.arc)) w = w + cx.offset;   // Sec. 4.1
+    return (cost + w) - Lrow.at(l.slot_pdf >> 16);
   };
   if (n_big > 0) {   // uniform
     for (int r = 0; r < n_big; ++r) {
@@ -385,26 +455,17 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       uint32_t lmin = 0xFFFFFFFFu;
       int queue_from = 0, queue_to = deg, first_sorted = 0;   // what goes through the queues: all of an unknown row
       if (id >= 0) {
-        const int4 row = p.long_rows[id];
+        const int4 row = p.lr.rows[id];
         first_sorted = row.w;
-        queue_from = p.long_group[id * (k + 2) + k]; queue_to = p.long_group[id * (k + 2) + k + 1];
+        queue_from = p.lr.group[id * (k + 2) + k]; queue_to = p.lr.group[id * (k + 2) + k + 1];
         for (int t0 = tid; t0 < queue_from; t0 += 4 * kBlock) {
-          ArcRec rec[4];
-          int arc[4];
+          LongArc l[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) l[u] = p.lr.arcs[row.w + min(t0 + u * kBlock, queue_from - 1)];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const int t = t0 + u * kBlock;
-            arc[u] = -1;
-            if (t < queue_from) { rec[u] = p.long_arcs[row.w + t]; arc[u] = p.long_idx[row.w + t]; }
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (arc[u] >= 0) {
-              float w = rec[u].weight;
-              if (ctx_contains(cx, arc[u])) w = w + cx.offset;   // Sec. 4.1
-              const uint32_t o = f2ord((cost + w) - Lrow.at((rec[u].meta & 0xFFFFu) - 1u));
-              lmin = o < lmin ? o : lmin;
-            }
+            const uint32_t o = f2ord(long_cost(l[u], cost));   // (the last arc again and again does no harm)
+            lmin = o < lmin ? o : lmin;
           }
         }
         const uint32_t wmin = wave_min_u32(lmin);
@@ -423,8 +484,8 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
           arc[q] = 0;
           rec[q].dst = 0; rec[q].weight = 0.0f; rec[q].row = 0; rec[q].meta = 0;
           if (act[q]) {
-            arc[q] = id >= 0 ? p.long_idx[first_sorted + j] : first + j;
-            rec[q] = id >= 0 ? p.long_arcs[first_sorted + j] : p.arcs[first + j];
+            arc[q] = id >= 0 ? (int)p.lr.arcs[first_sorted + j].arc : first + j;
+            rec[q] = p.arcs[arc[q]];
           }
         }
         queue_arcs(act, arc, rec, c_own, srcs);
@@ -433,30 +494,24 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     __syncthreads();
   }
 
+  CBD_STAMP(1);   // (diagnostic: long rows' minimum)
   // ---- 2: the minimum is final; closure lists of what passes
   const uint32_t m_ord = sh->m_ord;
   if (m_ord == 0xFFFFFFFFu) return kFrameNoTokens;   // (uniform: no candidate at all)
   const float m = ord2f(m_ord);
-  for (int o = 0; o < k; ++o) {
-    const int n1 = min(cnt1[o], cap1);
-    for (int base = wave * 64; base < n1; base += kBlock) {   // uniform
-      const int i = base + lane;
-      int pos = 0, len = 0;
-      float cost = 0.0f;
-      if (i < n1) {
-        const PartEntry e = Q1[o * cap1 + i];
-        cost = e.cost;
-        if ((e.from & kPartHasList) && !(cost - m > p.beam)) {
-          const ArcRec rec = p.arcs[e.arc];
-          pos = rec.row + (int)meta_ed(rec.meta) + (int)meta_xd(rec.meta);
-          len = (int)meta_cl(rec.meta);
-        }
-      }
-      parts_closures(p, sh, cx, Q2, k * cap1, m, cmap, pos, len, cost, o * cap1 + i, lane, n_eps, n_cand, max_depth);
+  {
+    const int n = min(*n_lists, lists_cap), per = min((n + NW - 1) / NW, 64);   // shared evenly by the waves
+    for (int base = wave * per; base < n; base += NW * per) {   // uniform
+      int4 w = make_int4(0, 0, 0, 0);
+      if (lane < per && base + lane < n) w = lists[base + lane];
+      const float cost = __uint_as_float((uint32_t)w.z);
+      if (cost - m > p.beam) w.y = 0;
+      parts_closures(p, sh, cx, Q2, k * cap1, m, cmap, w.x, w.y, cost, w.w, lane, n_eps, n_cand, max_depth);
     }
   }
   __syncthreads();
   if (sh->fault) return kFrameRedo;   // (uniform: set in steps 1 and 2 only) a queue is full
+  CBD_STAMP(2);   // (diagnostic: closure lists)
   const float fbest = ord2f(umin32(m_ord, sh->best_ord));
   bool have_closures = false;
   for (int o = 0; o < k; ++o) have_closures = have_closures || cnt2[o] > 0;
@@ -468,141 +523,170 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   T.slots = (uint32_t)p.part_slots;
   const int base_cur = sh->n_rec, base_prev = sh->frame_base;
   int w_surv = 0;
-  // every candidate of the long rows for share o, one per thread: fn(destination, cost, arc, record, source token)
+  // The long rows' arcs into share o, four per thread and round: fn(arcs, their places, which of them are within the cutoff,
+  // costs, source token).  (Kept in registers for both passes, they spill 65 registers: 4.09 -> 4.25 ms.)
   auto for_long_arcs = [&](int o, auto &&fn) {
     for (int r = 0; r < n_big; ++r) {
       const int id = row_id(r);
       if (id < 0) continue;   // uniform
-      const int4 row = p.long_rows[id];
-      const int g0 = row.w + p.long_group[id * (k + 2) + o], g1 = row.w + p.long_group[id * (k + 2) + o + 1];
+      const int4 row = p.lr.rows[id];
+      const int g0 = row.w + p.lr.group[id * (k + 2) + o], g1 = row.w + p.lr.group[id * (k + 2) + o + 1];
       const float cost = sh->big_cost[r];
-      const uint32_t src = sh->big_src[r];
-      for (int t0 = g0 + tid; t0 - tid < g1; t0 += 4 * kBlock) {   // uniform
-        ArcRec rec[4];
-        int arc[4];
+      const int src = (int)sh->big_src[r];
+      for (int base = g0 + wave * 64; base < g1; base += 4 * kBlock) {   // uniform
+        LongArc l[4];
+        float cand[4];
+        bool pass[4];
+        int at[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int t = t0 + u * kBlock;
-          arc[u] = -1;
-          rec[u].dst = 0; rec[u].weight = 0.0f; rec[u].row = 0; rec[u].meta = 0;
-          if (t < g1) { rec[u] = p.long_arcs[t]; arc[u] = p.long_idx[t]; }
+          const int t = base + u * kBlock + lane;
+          pass[u] = t < g1;
+          at[u] = min(t, g1 - 1);
+          l[u] = p.lr.arcs[at[u]];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          if (__ballot(arc[u] >= 0) == 0) break;   // uniform
-          float cand = 0.0f;
-          bool pass = false;
-          if (arc[u] >= 0) {
-            float w = rec[u].weight;
-            if (ctx_contains(cx, arc[u])) w = w + cx.offset;   // Sec. 4.1
-            cand = (cost + w) - Lrow.at((rec[u].meta & 0xFFFFu) - 1u);
-            pass = !(cand - m > p.beam);
-          }
-          fn(pass, cand, (uint32_t)arc[u], rec[u], src);
+          cand[u] = long_cost(l[u], cost);
+          pass[u] = pass[u] && !(cand[u] - m > p.beam);
         }
+        fn(l, at, pass, cand, src);
       }
     }
   };
-  // the winner of a state writes the token: cost, row, state (last frame), histogram (whole waves call it)
-  auto write_token = [&](bool win, uint32_t h, uint32_t state, float cost, uint32_t arc, const ArcRec &rec, int prev) {
-    const unsigned long long wm = __ballot(win);
-    int idx = -1;
-    if (wm == 0) return idx;   // uniform
+  // the winner of a state writes the token: cost, row, state (last frame), histogram
+  auto write_token = [&](int idx, uint32_t h, uint32_t state, float cost, uint32_t arc, const RowInfo &row, int prev) {
+    T.hval[h] = 0xFFFFFFFF00000000ull | (uint32_t)idx;   // (no candidate's key) the state's token
+    if (idx >= p.g_tok_cap) return false;
+    cost_out[idx] = cost;
+    rows_out[idx] = make_int4(row.first, row.eps, row.end, 0);
+    if (base_cur + idx < p.bp_cap) bp[base_cur + idx] = make_int2((int)arc, prev);
+    if (last_frame) g_tok_state[idx] = (int)state;
+    const float r = cost - fbest;
+    const bool surv = !(r > p.beam);
+    if (surv && hist_on) {
+      int bin = (int)floorf(r * inv);
+      bin = bin > 255 ? 255 : bin;
+      atomicAdd(&hist[bin], 1u);
+    }
+    return surv;
+  };
+  // places for the tokens of the lanes with win set (by whole waves)
+  auto token_places = [&](unsigned long long wm) {
     int first = 0;
     if (lane == 0) first = atomicAdd(n_made, (int)__popcll(wm));
-    first = __builtin_amdgcn_readfirstlane(first);
-    bool surv = false;
-    if (win) {
-      idx = first + (int)__popcll(wm & ((1ull << lane) - 1ull));
-      T.hval[h] = 0xFFFFFFFF00000000ull | (uint32_t)idx;   // (no candidate's key) the state's token
-      if (idx < p.g_tok_cap) {
-        const RowInfo row = row_of(p, rec);
-        cost_out[idx] = cost;
-        rows_out[idx] = make_int4(row.first, row.eps, row.end, 0);
-        if (base_cur + idx < p.bp_cap) bp[base_cur + idx] = make_int2((int)arc, prev);
-        if (last_frame) g_tok_state[idx] = (int)state;
-        const float r = cost - fbest;
-        surv = !(r > p.beam);
-        if (surv && hist_on) {
-          int bin = (int)floorf(r * inv);
-          bin = bin > 255 ? 255 : bin;
-          atomicAdd(&hist[bin], 1u);
-        }
-      }
-    }
-    w_surv += (int)__popcll(__ballot(surv));
-    return idx;
+    return __builtin_amdgcn_readfirstlane(first) + (int)__popcll(wm & ((1ull << lane) - 1ull));
   };
   for (int o = 0; o < k; ++o) {
     const int n1 = min(cnt1[o], cap1), n2 = min(cnt2[o], cap2);
     PartEntry *q1 = Q1 + o * cap1, *q2 = Q2 + o * cap2;
-    for (uint32_t i = tid; i < T.slots; i += kBlock) { T.hval[i] = kEmptyVal; T.hkey[i] = kEmptyKey; }
+    // (the first round's entry is asked for ahead of the table and stays in registers for both passes)
+    PartEntry e0; e0.dst = 0; e0.cost = 0.0f; e0.arc = 0; e0.from = 0;
+    if (tid < n1) e0 = q1[tid];
+    {
+      // the table starts with the keys of the long rows' destinations; everything else in it is all ones
+      uint4 *t4 = (uint4 *)region;
+      const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
+      for (uint32_t i = tid; i < T.slots / 2; i += kBlock) t4[i] = ones;
+      uint4 *k4 = (uint4 *)T.hkey;
+      const uint4 *image = (const uint4 *)(p.lr.image + (size_t)o * T.slots);
+      if (p.lr.n > 0) for (uint32_t i = tid; i < T.slots / 4; i += kBlock) k4[i] = image[i];
+      else for (uint32_t i = tid; i < T.slots / 4; i += kBlock) k4[i] = ones;
+    }
     __syncthreads();
+    CBD_STAMP(3);   // (diagnostic: tables emptied)
+    uint32_t h0 = 0;
+    bool pass0 = false;
     for (int base = wave * 64; base < n1; base += kBlock) {   // uniform
       const int i = base + lane;
-      bool pass = false;
-      if (i < n1) {
-        const PartEntry e = q1[i];
-        pass = !(e.cost - m > p.beam);
-        if (pass) part_min(T, sh, e.dst, ((uint64_t)f2ord(e.cost) << 32) | e.arc);
-      }
+      const PartEntry e = base == wave * 64 ? e0 : q1[min(i, n1 - 1)];
+      const bool pass = i < n1 && !(e.cost - m > p.beam);
+      uint32_t h = 0;
+      if (pass) h = part_min(T, sh, e.dst, ((uint64_t)f2ord(e.cost) << 32) | e.arc);
+      if (base == wave * 64) { h0 = h; pass0 = pass; }
       n_cand += (uint32_t)__popcll(__ballot(pass));
     }
     for (int i = tid; i < n2; i += kBlock) {
       const PartEntry e = q2[i];
       part_min(T, sh, e.dst, ((uint64_t)f2ord(e.cost) << 32) | e.arc);
     }
-    for_long_arcs(o, [&](bool pass, float cand, uint32_t arc, const ArcRec &rec, uint32_t) {
-      if (pass) part_min(T, sh, (uint32_t)rec.dst, ((uint64_t)f2ord(cand) << 32) | arc);
-      n_cand += (uint32_t)__popcll(__ballot(pass));
+    for_long_arcs(o, [&](const LongArc (&l)[4], const int (&)[4], const bool (&pass)[4], const float (&cand)[4], int) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (pass[u]) atomicMin((unsigned long long *)&T.hval[l[u].slot_pdf & 0xFFFFu], ((uint64_t)f2ord(cand[u]) << 32) | l[u].arc);
+        n_cand += (uint32_t)__popcll(__ballot(pass[u]));
+      }
     });
     __syncthreads();
     if (sh->redo) return kFrameRedo;   // (uniform: set between this barrier and the one before) the share's table is full
+    CBD_STAMP(4);   // (diagnostic: shares recombined)
     // An emitting arc is expanded once per frame, so its entry is the only one with its key; a closure arc can have been
     // reached twice with the same key: there an exchange lets one of the two through.
     for (int base = wave * 64; base < n1; base += kBlock) {   // uniform
       const int i = base + lane;
-      bool win = false;
-      uint32_t h = 0;
-      PartEntry e; e.dst = 0; e.cost = 0.0f; e.arc = 0; e.from = 0;
-      ArcRec rec; rec.dst = 0; rec.weight = 0.0f; rec.row = 0; rec.meta = 0;
-      if (i < n1) {
-        e = q1[i];
-        if (!(e.cost - m > p.beam)) {
-          h = part_find(T, e.dst);
-          win = T.hval[h] == (((uint64_t)f2ord(e.cost) << 32) | e.arc);
-          if (win) rec = p.arcs[e.arc];
-        }
-      }
-      write_token(win, h, e.dst, e.cost, e.arc, rec, base_prev + (int)(e.from & kPartMask));
+      const bool first = base == wave * 64;
+      const PartEntry e = first ? e0 : q1[min(i, n1 - 1)];
+      const bool pass = first ? pass0 : i < n1 && !(e.cost - m > p.beam);
+      uint32_t h = h0;
+      if (!first && pass) h = part_find(T, e.dst);
+      const bool win = pass && T.hval[h] == (((uint64_t)f2ord(e.cost) << 32) | e.arc);
+      const unsigned long long wm = __ballot(win);
+      if (wm == 0) continue;   // uniform
+      bool surv = false;
+      const int idx = token_places(wm);
+      if (win) surv = write_token(idx, h, e.dst, e.cost, e.arc, row_of(p, p.arcs[e.arc]), base_prev + (int)(e.from & kPartMask));
+      w_surv += (int)__popcll(__ballot(surv));
     }
     for (int base = wave * 64; base < n2; base += kBlock) {   // uniform
       const int i = base + lane;
-      bool win = false;
+      bool win = false, surv = false;
       uint32_t h = 0;
       PartEntry e; e.dst = 0; e.cost = 0.0f; e.arc = 0; e.from = 0;
-      ArcRec rec; rec.dst = 0; rec.weight = 0.0f; rec.row = 0; rec.meta = 0;
       if (i < n2) {
         e = q2[i];
         h = part_find(T, e.dst);
         const uint64_t key = ((uint64_t)f2ord(e.cost) << 32) | e.arc;
         win = T.hval[h] == key &&
               atomicCAS((unsigned long long *)&T.hval[h], (unsigned long long)key, (unsigned long long)kEmptyVal) == key;
-        if (win) rec = p.arcs[e.arc];
       }
-      const int idx = write_token(win, h, e.dst, e.cost, e.arc, rec, -1);   // (its predecessor follows in step 4)
+      const unsigned long long wm = __ballot(win);
+      const int idx = wm ? token_places(wm) : 0;
+      // (its predecessor follows in step 4)
+      if (win) surv = write_token(idx, h, e.dst, e.cost, e.arc, row_of(p, p.arcs[e.arc]), -1);
       if (i < n2) q2[i].arc = win ? (uint32_t)idx : kArcNone;
+      w_surv += (int)__popcll(__ballot(surv));
     }
-    for_long_arcs(o, [&](bool pass, float cand, uint32_t arc, const ArcRec &rec, uint32_t src) {   // (made once more: the same bits)
-      uint32_t h = 0;
-      bool win = false;
-      if (pass) {
-        h = part_find(T, (uint32_t)rec.dst);
-        win = T.hval[h] == (((uint64_t)f2ord(cand) << 32) | arc);
+    for_long_arcs(o, [&](const LongArc (&l)[4], const int (&at)[4], const bool (&pass)[4], const float (&cand)[4], int src) {   // (costed once more: the same bits)
+      bool win[4];
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        win[u] = pass[u] && T.hval[l[u].slot_pdf & 0xFFFFu] == (((uint64_t)f2ord(cand[u]) << 32) | l[u].arc);
+        n += (int)__popcll(__ballot(win[u]));
       }
-      write_token(win, h, (uint32_t)rec.dst, cand, arc, rec, base_prev + (int)src);
+      if (n == 0) return;   // uniform
+      int first = 0;
+      if (lane == 0) first = atomicAdd(n_made, n);
+      uint32_t meta[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) meta[u] = p.lr.meta[at[u]];
+      first = __builtin_amdgcn_readfirstlane(first);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t h = l[u].slot_pdf & 0xFFFFu;
+        const unsigned long long wm = __ballot(win[u]);
+        bool surv = false;
+        if (win[u]) {
+          ArcRec rec;
+          rec.dst = (int32_t)T.hkey[h]; rec.weight = 0.0f; rec.row = l[u].row; rec.meta = meta[u];
+          surv = write_token(first + (int)__popcll(wm & ((1ull << lane) - 1ull)), h, (uint32_t)rec.dst, cand[u], l[u].arc, row_of(p, rec), base_prev + src);
+        }
+        first += (int)__popcll(wm);
+        w_surv += (int)__popcll(__ballot(surv));
+      }
     });
     __syncthreads();
+    CBD_STAMP(5);   // (diagnostic: winners)
     if (have_closures) {   // (uniform) which token the state of an entry with a closure list has become
       for (int i = tid; i < n1; i += kBlock) {
         const PartEntry e = q1[i];
@@ -617,6 +701,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     }
   }
 
+  CBD_STAMP(6);   // (diagnostic: entries' tokens)
   // ---- 4: predecessors of closure winners
   if (have_closures) {
     for (int o = 0; o < k; ++o) {
@@ -673,6 +758,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     frame_init(sh, hist, false, lane, hist_on);   // for the next frame
   }
   __syncthreads();
+  CBD_STAMP(7);   // (diagnostic: closure winners' records, next row, close)
   return kFrameOk;
 }
 
