@@ -234,24 +234,22 @@ template <int kBlock> hipError_t launch_advance_t(const AdvanceParams &p, int gr
   return hipGetLastError();
 }
 
-template <int kBlock> hipError_t set_attr_t(uint32_t lds) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_parts_kernel<kBlock>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_kernel<kBlock>),
+template <int kBlock> hipError_t set_attr_t(bool parts, uint32_t lds) {
+  return hipFuncSetAttribute(parts ? reinterpret_cast<const void *>(&cbd::advance_parts_kernel<kBlock>)
+                                   : reinterpret_cast<const void *>(&cbd::advance_kernel<kBlock>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-hipError_t set_attr(int block, uint32_t lds) {
-  if (block == 1024) {
+hipError_t set_attr(int block, bool parts, uint32_t lds) {
+  if (block == 1024 && !parts) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_beside_kernel<1024>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (block == 256) return set_attr_t<256>(lds);
-  if (block == 512) return set_attr_t<512>(lds);
-  if (block == 960) return set_attr_t<960>(lds);
-  return set_attr_t<1024>(lds);
+  if (block == 256) return set_attr_t<256>(parts, lds);
+  if (block == 512) return set_attr_t<512>(parts, lds);
+  if (block == 960) return set_attr_t<960>(parts, lds);
+  return set_attr_t<1024>(parts, lds);
 }
 
 // Workgroups of the decode kernel that one compute unit holds at once (registers, waves and LDS together).
@@ -906,7 +904,7 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
       }
     }
   }
-  DCHK(set_attr(d->block, d->lds_bytes));
+  DCHK(set_attr(d->block, d->parts > 0, d->lds_bytes));
   if (cfg->workgroups_per_cu > 1) {
     // the LDS was divided for that many workgroups side by side: registers and waves have to allow them too
     int per_cu = 0;

@@ -272,7 +272,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
                                                uint8_t *owner_maps, uint8_t *closure_maps, int cur, int2 *bp,
                                                int32_t *g_tok_state, bool last_frame, const float *cost_in, float *cost_out) {
   constexpr int NW = kBlock / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = here_tid(), lane = tid & 63, wave = tid >> 6;
   const int k = p.parts, cap1 = p.part_q1, cap2 = p.part_q2;
   PartEntry *Q1 = (PartEntry *)(p.g_log + (size_t)c * p.g_log_cap);
   PartEntry *Q2 = Q1 + (size_t)k * cap1;
