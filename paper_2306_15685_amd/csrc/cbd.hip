@@ -212,8 +212,10 @@ struct cbd_decoder {
   cbd::TeamClosureWin *d_team_cwin = nullptr;
   uint32_t *d_team_pub_key = nullptr;
   uint16_t *d_team_pub_lid = nullptr;
-  int4 *d_team_big_rows = nullptr;
-  int32_t *d_team_big_group = nullptr, *d_team_big_perm = nullptr;
+  char *d_team_big = nullptr;      // the long rows sorted by member (one allocation), and its pieces
+  cbd::ArcRec *team_big_recs = nullptr;
+  int4 *team_big_rows = nullptr;
+  int32_t *team_big_group = nullptr, *team_big_perm = nullptr;
   int32_t team_n_big_rows = 0;
   // frames by parts (parts = 0: not used)
   int parts = 0, part_slots = 0, part_q1 = 0, part_q2 = 0;
@@ -311,7 +313,7 @@ hipError_t launch_team(const cbd_decoder *d, const AdvanceParams &p, int n_chann
   tp.a = p;
   tp.team = d->d_team; tp.q1 = d->d_team_q1; tp.q2 = d->d_team_q2; tp.cwin = d->d_team_cwin;
   tp.pub_key = d->d_team_pub_key; tp.pub_lid = d->d_team_pub_lid;
-  tp.big_rows = d->d_team_big_rows; tp.big_group = d->d_team_big_group; tp.big_perm = d->d_team_big_perm;
+  tp.big_rows = d->team_big_rows; tp.big_group = d->team_big_group; tp.big_perm = d->team_big_perm; tp.big_recs = d->team_big_recs;
   tp.n_big_rows = d->team_n_big_rows;
   // (teams padded to a multiple of 8 where the device has room: see the kernel's note on dies)
   int n_cu = 0;
@@ -985,12 +987,16 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
       for (auto &r : rows) { r.w = (int)total; total += r.z; }
       if (total < 0x7FFFFFF0) {
         d->team_n_big_rows = (int32_t)rows.size();
-        DCHK(dmalloc(&d->d_team_big_rows, rows.size(), &d->bytes));
-        DCHK(dmalloc(&d->d_team_big_group, rows.size() * (k + 1), &d->bytes));
-        DCHK(dmalloc(&d->d_team_big_perm, (size_t)total, &d->bytes));
-        DCHK(hipMemcpy(d->d_team_big_rows, rows.data(), sizeof(int4) * rows.size(), hipMemcpyHostToDevice));
+        const size_t recs_b = sizeof(cbd::ArcRec) * (size_t)total, rows_b = sizeof(int4) * rows.size(),
+                     group_b = sizeof(int32_t) * rows.size() * (k + 1);
+        DCHK(dmalloc(&d->d_team_big, recs_b + rows_b + group_b + sizeof(int32_t) * (size_t)total, &d->bytes));
+        d->team_big_recs = (cbd::ArcRec *)d->d_team_big;
+        d->team_big_rows = (int4 *)(d->d_team_big + recs_b);
+        d->team_big_group = (int32_t *)(d->d_team_big + recs_b + rows_b);
+        d->team_big_perm = (int32_t *)(d->d_team_big + recs_b + rows_b + group_b);
+        DCHK(hipMemcpy(d->team_big_rows, rows.data(), sizeof(int4) * rows.size(), hipMemcpyHostToDevice));
         hipLaunchKernelGGL(cbd::team_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, g->d_arcs,
-                           d->d_team_big_rows, d->d_team_big_group, d->d_team_big_perm, d->team_k);
+                           d->team_big_rows, d->team_big_group, d->team_big_perm, d->team_big_recs, d->team_k);
         DCHK(hipGetLastError());
       }
     }
@@ -1044,7 +1050,7 @@ int32_t cbd_decoder_free(cbd_decoder *d) {
                   d->d_log, d->d_ctx, d->d_ctx_n, d->d_ctx_off, d->d_hkey, d->d_hval, d->d_hidx, d->d_auto_snap,
                   d->d_gc_mark, d->d_gc_prefix, d->d_gc_cross, d->d_fixed_arcs, d->d_fixed_words, d->d_due_max, d->d_ids_kept,
                   d->d_team, d->d_team_q1, d->d_team_q2, d->d_team_cwin, d->d_team_pub_key, d->d_team_pub_lid,
-                  d->d_team_big_rows, d->d_team_big_group, d->d_team_big_perm,
+                  d->d_team_big,
                   d->d_long};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
