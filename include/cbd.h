@@ -339,7 +339,8 @@ typedef struct cbd_stats {
   int64_t tokens;         /* sum over frames of the table size */
   int64_t eps_rounds;     /* per frame the longest run of closure levels any wave made, summed over frames */
   int64_t records;        /* back-pointer records in use */
-  int64_t slow_frames;    /* frames decoded with the device-memory tables */
+  int64_t slow_frames;    /* frames that outgrew the LDS tables: decoded by parts (cbd_get_parts) or with the tables in
+                             device memory */
   int64_t records_dropped; /* back-pointer records removed by compactions */
   int64_t lean_frames;    /* frames decoded by the lean frame code */
   int32_t compactions;    /* compactions that ran */
@@ -361,6 +362,16 @@ int32_t cbd_get_records(cbd_decoder *d, int32_t channel, int32_t *arcs, int32_t 
 /* Counters of one channel since its last reset (channel >= 0) or summed over all (-1; status = first error).
  * Synchronises. */
 int32_t cbd_get_stats(cbd_decoder *d, int32_t channel, cbd_stats *out);
+
+/* Diagnostic: frames by parts.  On graphs with states of more than 512 emitting arcs, a frame that outgrows the LDS
+ * tables is decoded with the states split into shares, one LDS table after another; a frame that does not fit the
+ * shares is given up and decoded with the tables in device memory.  Results are the same either way.  *shares: 1, 2, 4
+ * or 8, or 0 = the decoder does not use them: frame_code 1, no LDS tables, a team; a graph without such states, or with
+ * any state whose epsilon closure is not stored as a list (deeper than 15 levels, longer than 62 arcs, or that of a
+ * state with more than 62 emitting or 14 epsilon-input arcs); more tokens per frame (hash_capacity_log2) than eight
+ * shares hold.  *frames, *given_up: counts since the last reset of one channel, or summed over all (channel = -1).
+ * Any pointer may be NULL.  Synchronises. */
+int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int64_t *frames, int64_t *given_up);
 
 /* Bytes of device memory the decoder holds; LDS bytes and threads per workgroup of the decode kernel;
  * tokens per frame its LDS tables hold (0 = device-memory tables only).  Any pointer may be NULL. */

@@ -24,7 +24,7 @@ EXPORTS = [
     "cbd_graph_load", "cbd_graph_free", "cbd_context_from_words", "cbd_context_lists_from_words", "cbd_context_lists_threads", "cbd_decoder_create", "cbd_decoder_free", "cbd_reset_channels",
     "cbd_set_context", "cbd_set_contexts", "cbd_contexts_create", "cbd_context_destroy", "cbd_use_contexts", "cbd_advance", "cbd_compact_records", "cbd_best_path", "cbd_best_paths", "cbd_best_paths_static", "cbd_best_paths_begin", "cbd_best_paths_finish", "cbd_best_tails", "cbd_best_tails_begin", "cbd_best_tails_finish",
     "cbd_get_fixed", "cbd_get_tokens",
-    "cbd_get_records", "cbd_get_stats", "cbd_decoder_info", "cbd_synchronize", "cbd_selftest", "cbd_strerror", "cbd_last_error",
+    "cbd_get_records", "cbd_get_stats", "cbd_get_parts", "cbd_decoder_info", "cbd_synchronize", "cbd_selftest", "cbd_strerror", "cbd_last_error",
 ]
 
 
@@ -124,6 +124,8 @@ def lib():
     L.cbd_get_records.argtypes = [vp, i32, vp, vp, i32, vp, vp, vp]
     L.cbd_get_stats.restype = i32
     L.cbd_get_stats.argtypes = [vp, i32, C.POINTER(cbd_stats)]
+    L.cbd_get_parts.restype = i32
+    L.cbd_get_parts.argtypes = [vp, i32, vp, vp, vp]
     L.cbd_decoder_info.restype = i32
     L.cbd_decoder_info.argtypes = [vp, vp, vp, vp, vp]
     L.cbd_synchronize.restype = i32
@@ -461,6 +463,13 @@ def cbd_get_stats(d, channel=-1) -> dict:
     s = cbd_stats()
     _check(lib().cbd_get_stats(d, int(channel), C.byref(s)), "cbd_get_stats")
     return s.as_dict()
+
+
+def cbd_get_parts(d, channel=-1) -> dict:
+    """Shares a frame that outgrows LDS is split into (0: never), frames decoded so, frames given up and decoded otherwise."""
+    k, n, back = C.c_int32(0), C.c_int64(0), C.c_int64(0)
+    _check(lib().cbd_get_parts(d, int(channel), C.byref(k), C.byref(n), C.byref(back)), "cbd_get_parts")
+    return {"shares": k.value, "frames": n.value, "given_up": back.value}
 
 
 def cbd_decoder_info(d) -> dict:

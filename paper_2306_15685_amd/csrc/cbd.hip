@@ -1782,6 +1782,25 @@ int32_t cbd_get_stats(cbd_decoder *d, int32_t channel, cbd_stats *out) try {
   return fail(CBD_E_HIP, std::string("get_stats: ") + e.what());
 }
 
+int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int64_t *frames, int64_t *given_up) try {
+  if (!d) return fail(CBD_E_INVALID, "get_parts: null argument");
+  if (channel < -1 || channel >= d->C) return fail(CBD_E_INVALID, "get_parts: channel out of range");
+  HIPCHK(hipStreamSynchronize(d->stream));
+  const int32_t lo = channel < 0 ? 0 : channel, hi = channel < 0 ? d->C : channel + 1;
+  std::vector<cbd::ChanState> cs((size_t)(hi - lo));
+  HIPCHK(hipMemcpy(cs.data(), d->d_chan + lo, sizeof(cbd::ChanState) * cs.size(), hipMemcpyDeviceToHost));
+  int64_t n = 0, back = 0;
+  for (const cbd::ChanState &c : cs) { n += c.parts_frames; back += c.parts_given_up; }
+  if (shares) *shares = d->parts;
+  if (frames) *frames = n;
+  if (given_up) *given_up = back;
+  return CBD_OK;
+} catch (const std::bad_alloc &) {
+  return fail(CBD_E_NOMEM, "get_parts: host allocation failed");
+} catch (const std::exception &e) {
+  return fail(CBD_E_HIP, std::string("get_parts: ") + e.what());
+}
+
 int32_t cbd_selftest(void) {
   // the decode kernel's wave-level prefix sum and minimum against plain host loops
   int32_t *d_in = nullptr, *d_scan = nullptr;

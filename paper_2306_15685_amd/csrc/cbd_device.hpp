@@ -101,14 +101,20 @@ struct __attribute__((aligned(128))) ChanState {
   int32_t row_buf;      // which of the two row buffers (tok_row) belongs to the current token list
   long long frames, active_tokens, emit_arcs, eps_arcs, candidates, improvements, tokens, eps_rounds;
   int32_t max_tokens;
-  int32_t slow_frames;  // frames decoded with the device-memory tables
+  int32_t slow_frames;  // frames that outgrew the LDS tables: by parts or with the tables in device memory
   int32_t gc_base;      // records below this one survived the last compaction and are never examined again
   int32_t gc_runs;      // compactions since reset
   long long gc_dropped; // records they removed
   int32_t n_fixed_arcs;  // arcs / words of the paths' shared beginning written out so far (in time order, to the
   int32_t n_fixed_words; // channel's fixed_arcs / fixed_words rows)
   long long lean_frames; // frames decoded by the lean code
+  int32_t parts_frames;  // frames decoded by parts
+  int32_t parts_given_up; // frames begun by parts and decoded by the general code
+#ifdef CBD_PROFILE
   long long spare[15];
+#else
+  long long spare[14];
+#endif
 #ifdef CBD_PROFILE
   long long timeline[16];  // diagnostic build: the workgroup of the channel's last call with frames (start, end, ids)
 #endif
@@ -212,6 +218,7 @@ struct Shared {
   uint32_t lean_best[2];      // lean frames, in turn: minimum over the closure candidates accepted
   int32_t a_maxtok, a_slow;   // counters of this call
   int32_t a_lean;             // frames decoded by the lean code
+  int32_t a_parts, a_parts_back;   // frames by parts; begun by parts and given up
   unsigned long long a_lean_tokens;    // their tokens
   unsigned long long a_lean_pack[2];   // its counters, two to a word: active tokens | emitting arcs << 32,
                                        // epsilon-input arcs | candidates << 32
@@ -1413,7 +1420,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
 
   int outcome = kFrameOk;
   if (tid < 64) frame_init(sh, hist, p.do_reset != 0, tid);
-  if (tid == 0) { sh->a_lean = 0; sh->a_lean_tokens = 0; sh->a_lean_pack[0] = 0; sh->a_lean_pack[1] = 0; }
+  if (tid == 0) { sh->a_lean = 0; sh->a_parts = 0; sh->a_parts_back = 0; sh->a_lean_tokens = 0; sh->a_lean_pack[0] = 0; sh->a_lean_pack[1] = 0; }
 #ifdef CBD_PROFILE
   if (tid == 0) {
     for (int k = 0; k < 12; ++k) sh->prof[k] = 0;
@@ -1493,6 +1500,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
         if (outcome != kFrameRedo) {
           slow = false;
         } else {
+          if (tid == 0) sh->a_parts_back += 1;
           if (cost_alt) { costs_home(); cost_alt = false; }
           __syncthreads();
           if (tid < 64) frame_init(sh, hist, false, tid);
@@ -1552,9 +1560,10 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
       cs->frames = 0; cs->active_tokens = 0; cs->emit_arcs = 0; cs->eps_arcs = 0; cs->candidates = 0;
       cs->improvements = 0; cs->tokens = 0; cs->eps_rounds = 0; cs->max_tokens = 0; cs->slow_frames = 0;
       cs->gc_base = 0; cs->gc_runs = 0; cs->gc_dropped = 0; cs->n_fixed_arcs = 0; cs->n_fixed_words = 0;
-      cs->lean_frames = 0;
+      cs->lean_frames = 0; cs->parts_frames = 0; cs->parts_given_up = 0;
     }
     cs->lean_frames += sh->a_lean;
+    cs->parts_frames += sh->a_parts; cs->parts_given_up += sh->a_parts_back;
 #ifdef CBD_PROFILE
     if (p.do_reset) for (int k = 0; k < 15; ++k) cs->spare[k] = 0;
     for (int k = 0; k < 7; ++k) cs->spare[k] += sh->prof[k];

@@ -147,6 +147,7 @@ def run_batch(torch, g, L, ctxs, offs, beam, max_active, chunks, lookup_mode=0, 
             assert s["tokens"] == orcs[c].stat(1) and s["active_tokens"] == orcs[c].stat(2)
         st = dec.stats(-1)
         st["info"] = B.cbd_decoder_info(dec.dh)
+        st["parts"] = B.cbd_get_parts(dec.dh)
         return st
     finally:
         dec.close()

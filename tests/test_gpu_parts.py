@@ -1,6 +1,7 @@
 """GPU parity of frames decoded by parts (graphs with long rows, frames that outgrow the LDS tables): shares of the states
 from one to eight, long rows into states with and without closure lists, an unprepared mix of long and ordinary rows, pruning,
-final costs, context swaps, frames that move between the LDS tables and the shares, and frames whose queues are too small."""
+final costs, context swaps, frames that move between the LDS tables and the shares, frames whose queues are too small, and a
+graph that the shares cannot take."""
 import numpy as np
 import pytest
 
@@ -11,9 +12,10 @@ from test_gpu_parity import run_batch, torch_cuda  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-def hub_graph(S, P, hubs, hub_arcs, mean_degree=3.0, eps=0.15, finals=False, seed=1):
+def hub_graph(S, P, hubs, hub_arcs, mean_degree=3.0, eps=0.15, finals=False, seed=1, eps_hubs=0):
     """An HCLG-style random graph in which a few states, the start state among them, have long rows (each between 513 and
-    hub_arcs emitting arcs more), and one arc in twenty leads to one of these."""
+    hub_arcs emitting arcs more), and one arc in twenty leads to one of these.  A state with so many arcs has no stored
+    closure list if any of them is an epsilon-input arc: eps_hubs of the long rows have one, the others none."""
     g = synth.make_graph(S, P, 500, eps, seed_stream=(seed, 7), mean_degree=mean_degree, with_finals=finals)
     rng = np.random.default_rng(seed)
     hub = np.concatenate([[g.start_state], 1 + rng.choice(S - 1, hubs - 1, replace=False)])
@@ -22,6 +24,10 @@ def hub_graph(S, P, hubs, hub_arcs, mean_degree=3.0, eps=0.15, finals=False, see
     dst[to_hub] = rng.choice(hub, int(to_hub.sum()))
     rows = [[dst[a:b], g.ilabel[a:b], g.olabel[a:b], g.weight[a:b]] for a, b in zip(g.row_offsets[:-1], g.row_offsets[1:])]
     for i, h in enumerate(hub):
+        emitting = rows[h][1] > 0
+        rows[h] = [x[emitting] for x in rows[h]]
+        if i < eps_hubs:   # (epsilon-input arcs lead upwards: no cycle)
+            rows[h] = [np.append(x, y).astype(x.dtype) for x, y in zip(rows[h], (rng.integers(h + 1, S), 0, 0, 0.5))]
         n = 513 if i == 1 else int(rng.integers(513, hub_arcs + 1))
         more = [rng.integers(0, S, n), rng.integers(1, P + 1, n), rng.integers(0, 500, n), rng.uniform(0.0, 3.0, n)]
         rows[h] = [np.concatenate(x) for x in zip(rows[h], more)]
@@ -38,16 +44,35 @@ def inputs(torch, g, C, T, sigma, seed, arcs=200):
     return L, ctxs, rng.uniform(-4.0, 2.0, C).astype(np.float32)
 
 
-@pytest.mark.parametrize("hash_log2,block", [(12, 1024), (13, 1024), (14, 1024), (15, 1024), (14, 960), (14, 512), (14, 256)])
-def test_shares_and_long_rows(torch_cuda, hash_log2, block):  # noqa: F811
-    """64 tokens of LDS tables leave some 2,900 slots: one share for 2,048 tokens, two, four and eight for twice as many
-    each.  Most frames hold more than 64 tokens and less than 2,048; rows read from device memory at 1,500 pdfs."""
-    print("parts", hash_log2, block, flush=True)
-    g = hub_graph(2_000, 1_500 if hash_log2 == 13 else 64, 6, 1_500, seed=hash_log2)
+def by_parts(s, shares):
+    """Most frames that outgrew the LDS tables were decoded by parts, with that many shares.  (Small LDS tables, or 256
+    threads, leave little room for the list of closures: 4 to 29 of some 72 frames are given up for it.)"""
+    p = s["parts"]
+    print("parts", p, "slow", s["slow_frames"], "of", s["frames"], "max tokens", s["max_tokens"], flush=True)
+    return p["shares"] == shares and p["frames"] + p["given_up"] == s["slow_frames"] and p["frames"] > p["given_up"]
+
+
+@pytest.mark.parametrize("hash_log2,block,pdfs,shares", [
+    (12, 1024, 64, 1), (13, 1024, 1_500, 2), (14, 1024, 64, 4), (15, 1024, 64, 8), (14, 960, 64, 4), (13, 512, 64, 4), (12, 256, 64, 4)])
+def test_shares_and_long_rows(torch_cuda, hash_log2, block, pdfs, shares):  # noqa: F811
+    """64 tokens of LDS tables leave some 2,900 slots with 1,024 threads, 830 with 256, 12 bytes each: as many shares as hold
+    2^hash_log2 / 2 tokens in seven eighths of them.  Most frames hold more than 64 tokens and less than 2,048; rows of
+    1,500 pdfs are read from device memory."""
+    print("shares", hash_log2, block, flush=True)
+    g = hub_graph(2_000, pdfs, 6, 1_500, seed=hash_log2)
     L, ctxs, offs = inputs(torch_cuda, g, 3, 24, 2.5, hash_log2)
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=7.0, max_active=0, chunks=[1, 6, 17], hash_log2=hash_log2, lookup_mode=hash_log2 & 1,
                   lds_token_cap=64, block_threads=block)
     assert s["slow_frames"] > s["frames"] // 2 and s["eps_arcs"] > 0 and s["max_tokens"] > 300
+    assert by_parts(s, shares)
+
+
+def test_closure_that_is_not_stored(torch_cuda):  # noqa: F811
+    """One long row with an epsilon-input arc: such a state's closure has no list, which the shares need."""
+    g = hub_graph(2_000, 64, 6, 1_500, seed=12, eps_hubs=1)
+    L, ctxs, offs = inputs(torch_cuda, g, 3, 24, 2.5, 12)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=7.0, max_active=0, chunks=[1, 6, 17], hash_log2=12, lds_token_cap=64)
+    assert s["slow_frames"] > 0 and s["parts"] == {"shares": 0, "frames": 0, "given_up": 0}
 
 
 def test_pruning_finals_and_swap(torch_cuda):  # noqa: F811
@@ -56,7 +81,7 @@ def test_pruning_finals_and_swap(torch_cuda):  # noqa: F811
     swap = (10, [c[::2] for c in ctxs], -offs)
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=8.0, max_active=150, chunks=[10, 20], hash_log2=14, use_final=True,
                   swap=swap, lds_token_cap=128)
-    assert s["slow_frames"] > 0 and s["active_tokens"] < s["tokens"]
+    assert s["active_tokens"] < s["tokens"] and by_parts(s, 4)
 
 
 def test_frames_move_between_the_tables(torch_cuda):  # noqa: F811
@@ -64,7 +89,7 @@ def test_frames_move_between_the_tables(torch_cuda):  # noqa: F811
     g = hub_graph(6_000, 400, 3, 700, seed=5)
     L, ctxs, offs = inputs(torch_cuda, g, 4, 40, 4.0, 5)
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=9.0, max_active=0, chunks=[3, 17, 20], hash_log2=13, lds_token_cap=192)
-    assert 0 < s["slow_frames"] < s["frames"]
+    assert s["slow_frames"] < s["frames"] and by_parts(s, 2)
 
 
 def test_queues_too_small(torch_cuda):  # noqa: F811
@@ -73,16 +98,17 @@ def test_queues_too_small(torch_cuda):  # noqa: F811
     g = hub_graph(300, 40, 2, 600, seed=9)
     L, ctxs, offs = inputs(torch_cuda, g, 2, 12, 1.0, 9, arcs=30)
     s = run_batch(torch_cuda, g, L, ctxs, np.abs(offs), beam=6.0, max_active=0, chunks=[5, 7], hash_log2=10, lds_token_cap=64)
-    assert s["slow_frames"] > 0 and s["status"] == 0
+    assert s["status"] == 0 and s["parts"]["shares"] == 1 and s["parts"]["given_up"] > 0
+    assert s["parts"]["frames"] < s["slow_frames"]
 
 
-@pytest.mark.parametrize("words", [300, 6_000])
-def test_lexicon_loop(torch_cuda, words):  # noqa: F811
-    """Small enough for the LDS tables to come and go, and large enough for four shares."""
+@pytest.mark.parametrize("words,shares", [(600, 8), (6_000, 2)])
+def test_lexicon_loop(torch_cuda, words, shares):  # noqa: F811
+    """LDS tables of 256 tokens, and as large as LDS allows: eight shares of 3,500 slots and two of 11,700 for 16,384 tokens."""
     g = synth.make_lexicon_graph(48, words, seed_stream=(5, words))
     L = synth.make_loglikes(3, 25, 48, 2.0, seed_stream=(5,), device="cuda")
     w = synth.scaled(synth.WORKLOADS["e2e"], channels=3, config_id=71)
     ctxs, offs = synth.make_contexts(w, g)
-    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=10.0, max_active=800 if words > 300 else 100, chunks=[3, 10, 12], hash_log2=15,
-                  lookup_mode=1, lds_token_cap=0 if words > 300 else 256)
-    assert s["slow_frames"] > 0 and s["status"] == 0
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=10.0, max_active=800 if words > 600 else 100, chunks=[3, 10, 12], hash_log2=15,
+                  lookup_mode=1, lds_token_cap=0 if words > 600 else 256)
+    assert s["status"] == 0 and by_parts(s, shares)
