@@ -369,9 +369,11 @@ int32_t cbd_get_stats(cbd_decoder *d, int32_t channel, cbd_stats *out);
  * or 8, or 0 = the decoder does not use them: frame_code 1, no LDS tables, a team; a graph without such states, or with
  * any state whose epsilon closure is not stored as a list (deeper than 15 levels, longer than 62 arcs, or that of a
  * state with more than 62 emitting or 14 epsilon-input arcs); more tokens per frame (hash_capacity_log2) than eight
- * shares hold.  *frames, *given_up: counts since the last reset of one channel, or summed over all (channel = -1).
- * Any pointer may be NULL.  Synchronises. */
-int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int64_t *frames, int64_t *given_up);
+ * shares hold.  *mostly: 1 = records_per_frame is given and more than the LDS tables hold, so the decoder expects most
+ * frames to outgrow them and its kernel favours these; 0 = its kernel favours frames that fit.  *frames, *given_up:
+ * counts since the last reset of one channel, or summed over all (channel = -1).  Any pointer may be NULL.
+ * Synchronises. */
+int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int32_t *mostly, int64_t *frames, int64_t *given_up);
 
 /* Bytes of device memory the decoder holds; LDS bytes and threads per workgroup of the decode kernel;
  * tokens per frame its LDS tables hold (0 = device-memory tables only).  Any pointer may be NULL. */

@@ -125,7 +125,7 @@ def lib():
     L.cbd_get_stats.restype = i32
     L.cbd_get_stats.argtypes = [vp, i32, C.POINTER(cbd_stats)]
     L.cbd_get_parts.restype = i32
-    L.cbd_get_parts.argtypes = [vp, i32, vp, vp, vp]
+    L.cbd_get_parts.argtypes = [vp, i32, vp, vp, vp, vp]
     L.cbd_decoder_info.restype = i32
     L.cbd_decoder_info.argtypes = [vp, vp, vp, vp, vp]
     L.cbd_synchronize.restype = i32
@@ -466,10 +466,11 @@ def cbd_get_stats(d, channel=-1) -> dict:
 
 
 def cbd_get_parts(d, channel=-1) -> dict:
-    """Shares a frame that outgrows LDS is split into (0: never), frames decoded so, frames given up and decoded otherwise."""
-    k, n, back = C.c_int32(0), C.c_int64(0), C.c_int64(0)
-    _check(lib().cbd_get_parts(d, int(channel), C.byref(k), C.byref(n), C.byref(back)), "cbd_get_parts")
-    return {"shares": k.value, "frames": n.value, "given_up": back.value}
+    """Shares a frame that outgrows LDS is split into (0: never), whether most frames are expected to, frames decoded so, and
+    frames given up and decoded otherwise."""
+    k, most, n, back = C.c_int32(0), C.c_int32(0), C.c_int64(0), C.c_int64(0)
+    _check(lib().cbd_get_parts(d, int(channel), C.byref(k), C.byref(most), C.byref(n), C.byref(back)), "cbd_get_parts")
+    return {"shares": k.value, "mostly": bool(most.value), "frames": n.value, "given_up": back.value}
 
 
 def cbd_decoder_info(d) -> dict:

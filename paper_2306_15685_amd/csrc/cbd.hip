@@ -219,6 +219,7 @@ struct cbd_decoder {
   int32_t team_n_big_rows = 0;
   // frames by parts (parts = 0: not used)
   int parts = 0, part_slots = 0, part_q1 = 0, part_q2 = 0;
+  int parts_kernel = cbd::kPartsNone;   // which of the decode kernels
   char *d_long = nullptr;          // the layout of the graph's long rows ...
   cbd::LongRows long_rows{};       // ... and its pieces
   std::vector<int32_t> h_tmp;
@@ -230,21 +231,26 @@ namespace {
 
 using cbd::AdvanceParams;
 
-template <int kBlock> hipError_t launch_advance_t(const AdvanceParams &p, int grid, uint32_t lds, hipStream_t st) {
-  if (p.parts > 0) hipLaunchKernelGGL((cbd::advance_parts_kernel<kBlock>), dim3(grid), dim3(kBlock), lds, st, p);
-  else hipLaunchKernelGGL((cbd::advance_kernel<kBlock>), dim3(grid), dim3(kBlock), lds, st, p);
+template <int kBlock> auto decode_kernel(int parts) -> void (*)(AdvanceParams) {
+  if (parts == cbd::kPartsFew) return cbd::advance_parts_kernel<kBlock, cbd::kPartsFew>;
+  if (parts == cbd::kPartsMost) return cbd::advance_parts_kernel<kBlock, cbd::kPartsMost>;
+  return cbd::advance_kernel<kBlock>;
+}
+
+template <int kBlock> hipError_t launch_advance_t(int parts, const AdvanceParams &p, int grid, uint32_t lds, hipStream_t st) {
+  hipLaunchKernelGGL(decode_kernel<kBlock>(parts), dim3(grid), dim3(kBlock), lds, st, p);
   return hipGetLastError();
 }
 
-template <int kBlock> hipError_t set_attr_t(bool parts, uint32_t lds) {
-  return hipFuncSetAttribute(parts ? reinterpret_cast<const void *>(&cbd::advance_parts_kernel<kBlock>)
-                                   : reinterpret_cast<const void *>(&cbd::advance_kernel<kBlock>),
+template <int kBlock> hipError_t set_attr_t(int parts, uint32_t lds) {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(decode_kernel<kBlock>(parts)),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-hipError_t set_attr(int block, bool parts, uint32_t lds) {
-  if (block == 1024 && !parts) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_beside_kernel<1024>),
+hipError_t set_attr(int block, int parts, uint32_t lds) {
+  if (block == 1024 && parts != cbd::kPartsMost) {
+    hipError_t e = hipFuncSetAttribute(parts == cbd::kPartsFew ? reinterpret_cast<const void *>(&cbd::advance_parts_beside_kernel<1024>)
+                                                               : reinterpret_cast<const void *>(&cbd::advance_beside_kernel<1024>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
@@ -255,11 +261,11 @@ hipError_t set_attr(int block, bool parts, uint32_t lds) {
 }
 
 // Workgroups of the decode kernel that one compute unit holds at once (registers, waves and LDS together).
-hipError_t resident_per_cu(int block, bool parts, uint32_t lds, int *n) {
-  if (block == 256) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<256> : cbd::advance_kernel<256>, 256, lds);
-  if (block == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<512> : cbd::advance_kernel<512>, 512, lds);
-  if (block == 960) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<960> : cbd::advance_kernel<960>, 960, lds);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, parts ? cbd::advance_parts_kernel<1024> : cbd::advance_kernel<1024>, 1024, lds);
+hipError_t resident_per_cu(int block, int parts, uint32_t lds, int *n) {
+  if (block == 256) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, decode_kernel<256>(parts), 256, lds);
+  if (block == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, decode_kernel<512>(parts), 512, lds);
+  if (block == 960) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, decode_kernel<960>(parts), 960, lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, decode_kernel<1024>(parts), 1024, lds);
 }
 
 // Lays out the graph's long rows for k shares with tables of `slots` slots each (prepare_long_rows_kernel): as many of
@@ -337,15 +343,16 @@ bool walks_in_flight(const cbd_decoder *d) {
 }
 
 hipError_t launch_advance(const cbd_decoder *d, const AdvanceParams &p, int grid) {
-  if (d->walk_room && d->block == 1024 && d->parts == 0 && grid >= d->walk_room_min_grid && walks_in_flight(d)) {
+  if (d->walk_room && d->block == 1024 && d->parts_kernel != cbd::kPartsMost && grid >= d->walk_room_min_grid && walks_in_flight(d)) {
     // leave the walks room on the compute units (see advance_beside_kernel)
-    hipLaunchKernelGGL((cbd::advance_beside_kernel<1024>), dim3(grid), dim3(1024), d->lds_bytes, d->stream, p);
+    hipLaunchKernelGGL((d->parts_kernel == cbd::kPartsFew ? cbd::advance_parts_beside_kernel<1024> : cbd::advance_beside_kernel<1024>),
+                       dim3(grid), dim3(1024), d->lds_bytes, d->stream, p);
     return hipGetLastError();
   }
-  if (d->block == 256) return launch_advance_t<256>(p, grid, d->lds_bytes, d->stream);
-  if (d->block == 512) return launch_advance_t<512>(p, grid, d->lds_bytes, d->stream);
-  if (d->block == 960) return launch_advance_t<960>(p, grid, d->lds_bytes, d->stream);
-  return launch_advance_t<1024>(p, grid, d->lds_bytes, d->stream);
+  if (d->block == 256) return launch_advance_t<256>(d->parts_kernel, p, grid, d->lds_bytes, d->stream);
+  if (d->block == 512) return launch_advance_t<512>(d->parts_kernel, p, grid, d->lds_bytes, d->stream);
+  if (d->block == 960) return launch_advance_t<960>(d->parts_kernel, p, grid, d->lds_bytes, d->stream);
+  return launch_advance_t<1024>(d->parts_kernel, p, grid, d->lds_bytes, d->stream);
 }
 
 AdvanceParams base_params(const cbd_decoder *d) {
@@ -903,14 +910,18 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
       if ((int64_t)k * slots * 7 / 8 >= d->g_tok_cap && slots * 12 >= d->block * 16) {
         d->parts = k; d->part_slots = slots;
         d->part_q1 = d->g_log_cap / 8 * 5 / k; d->part_q2 = d->g_log_cap / 8 * 3 / k;
+        // The records that a caller reserves are the tokens of its average frame.  More than the LDS tables hold: most
+        // frames outgrow them, and the kernel is the one for these (9 % faster there, 4 to 7 % slower on lean frames:
+        // see kPartsFew).  Fewer, or no figure given: the kernel in which lean frames take what they take on other graphs.
+        d->parts_kernel = cfg->records_per_frame > cap ? cbd::kPartsMost : cbd::kPartsFew;
       }
     }
   }
-  DCHK(set_attr(d->block, d->parts > 0, d->lds_bytes));
+  DCHK(set_attr(d->block, d->parts_kernel, d->lds_bytes));
   if (cfg->workgroups_per_cu > 1) {
     // the LDS was divided for that many workgroups side by side: registers and waves have to allow them too
     int per_cu = 0;
-    DCHK(resident_per_cu(d->block, d->parts > 0, d->lds_bytes, &per_cu));
+    DCHK(resident_per_cu(d->block, d->parts_kernel, d->lds_bytes, &per_cu));
     if (per_cu < cfg->workgroups_per_cu)
       return fail(CBD_E_INVALID, "decoder: a compute unit holds " + std::to_string(per_cu) +
                                  " workgroups of this size, fewer than workgroups_per_cu");
@@ -1782,7 +1793,7 @@ int32_t cbd_get_stats(cbd_decoder *d, int32_t channel, cbd_stats *out) try {
   return fail(CBD_E_HIP, std::string("get_stats: ") + e.what());
 }
 
-int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int64_t *frames, int64_t *given_up) try {
+int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int32_t *mostly, int64_t *frames, int64_t *given_up) try {
   if (!d) return fail(CBD_E_INVALID, "get_parts: null argument");
   if (channel < -1 || channel >= d->C) return fail(CBD_E_INVALID, "get_parts: channel out of range");
   HIPCHK(hipStreamSynchronize(d->stream));
@@ -1792,6 +1803,7 @@ int32_t cbd_get_parts(cbd_decoder *d, int32_t channel, int32_t *shares, int64_t 
   int64_t n = 0, back = 0;
   for (const cbd::ChanState &c : cs) { n += c.parts_frames; back += c.parts_given_up; }
   if (shares) *shares = d->parts;
+  if (mostly) *mostly = d->parts_kernel == cbd::kPartsMost ? 1 : 0;
   if (frames) *frames = n;
   if (given_up) *given_up = back;
   return CBD_OK;

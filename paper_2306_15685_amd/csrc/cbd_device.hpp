@@ -218,7 +218,6 @@ struct Shared {
   uint32_t lean_best[2];      // lean frames, in turn: minimum over the closure candidates accepted
   int32_t a_maxtok, a_slow;   // counters of this call
   int32_t a_lean;             // frames decoded by the lean code
-  int32_t a_parts, a_parts_back;   // frames by parts; begun by parts and given up
   unsigned long long a_lean_tokens;    // their tokens
   unsigned long long a_lean_pack[2];   // its counters, two to a word: active tokens | emitting arcs << 32,
                                        // epsilon-input arcs | candidates << 32
@@ -230,6 +229,7 @@ struct Shared {
   long long prof_general;   // time in those frames' second run
 #endif
   unsigned long long a_frames, a_active, a_emit, a_eps, a_cand, a_impr, a_tokens, a_rounds;
+  int32_t a_parts, a_parts_back;   // frames by parts; begun by parts and given up
 };
 
 __device__ __forceinline__ int sh_log_n(const Shared *sh) { return (int)(uint32_t)sh->log_claim; }
@@ -1319,8 +1319,58 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
   __syncthreads();
 }
 
+// What a kernel does with frames that outgrow LDS: kPartsNone leaves them to the general code; the others decode them by
+// parts, kPartsFew in a kernel whose registers go to the lean and the general frames, kPartsMost in one that treats all
+// frames alike.  The two differ in nothing but speed (cbd_decoder_create chooses; us, kPartsNone / Few / Most):
+//   256 channels x 500 frames, all lean, results walked beside       5,805 / 5,925 / 6,925
+//   2,048 channels x 100 frames, all but 80 of 204,800 lean          8,810 / 9,000 / 9,650
+//   32 channels x 333 frames, all lean                               2,312 / 2,320 / 2,414
+//   150 channels x 60 frames of 2,000 words, general code in LDS     1,790 / 1,795 / 1,848
+//   148 channels x 40 frames of 5,600 words, all by parts            7,385 / 2,165 / 1,980
+//   160 channels x 40 frames of 20,000 words, all by parts          30,360 / 4,570 / 4,205
+// (The worst found: 160 channels on a graph whose long rows are met in most frames, 900 tokens each, general code in LDS,
+// results walked beside: 23,400 / 25,500 / 24,300.)
+enum { kPartsNone = 0, kPartsFew = 1, kPartsMost = 2 };
+
+// kPartsFew: a frame by parts that has nothing in common with the code around it.  The kernel's parameters are read anew
+// (through a pointer the compiler knows nothing about) and everything is derived from them here; otherwise some of it is
+// worked out once ahead of the frame loop and takes registers in every frame.
+typedef const __attribute__((address_space(4))) AdvanceParams *const_params_ptr;
+__device__ __forceinline__ int hidden(int x) {   // x uniform
+  x = __builtin_amdgcn_readfirstlane(x);
+  asm volatile("" : "+s"(x));
+  return x;
+}
+template <int kBlock>
+__device__ __forceinline__ int frame_by_parts_apart(unsigned char *smem, int pos_, int c_, int f_, int cur_, bool cost_alt_, int cslot_,
+                                                    int n_ctx, float offset) {
+  // (AdvanceParams is the kernel's only parameter)
+  unsigned long long params = (unsigned long long)(const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(params));
+  const AdvanceParams &p = *(const AdvanceParams *)(const_params_ptr)params;
+  const int pos = hidden(pos_), c = hidden(c_), f = hidden(f_), cur = hidden(cur_), cslot = hidden(cslot_);
+  const bool cost_alt = hidden(cost_alt_ ? 1 : 0) != 0;
+  const LdsLayout lay = make_layout(p.stage_rows ? p.num_pdfs : 0, p.ctx_lds_cap, p.lds_tok_cap, p.lds_slots,
+                                    p.lds_log_cap, p.lean_log_per_wave * (kBlock / 64));
+  float *Lrow = (float *)(smem + lay.L);
+  Ctx cx;
+  cx.n = hidden(n_ctx); cx.offset = __uint_as_float((uint32_t)hidden((int)__float_as_uint(offset)));
+  cx.g_list = p.ctx + (size_t)cslot * p.max_ctx;
+  cx.lds_list = (lds_cint_ptr)(int32_t *)(smem + lay.ctx); cx.bitmap = (uint32_t *)(smem + lay.bitmap);
+  cx.in_lds = cx.n <= p.ctx_lds_cap;
+  cx.use_bitmap = p.lookup_mode == 1;
+  Rows rows;
+  rows.lds = (lds_cfloat_ptr)Lrow; rows.staged = p.stage_rows != 0;
+  rows.glob = p.loglikes + (long long)pos * p.channel_stride + (long long)f * p.num_pdfs;
+  const float *Lnext = p.stage_rows && f + 1 < p.n_frames ? rows.glob + p.num_pdfs : nullptr;
+  float *home = p.tok_cost + (size_t)c * p.g_tok_cap, *alt = (float *)(p.g_hidx + (size_t)c * p.g_slots);
+  return run_frame_parts<kBlock>(p, smem + lay.hval, c, (Shared *)(smem + lay.sh), cx, Lrow, rows, Lnext, (uint32_t *)(smem + lay.hist),
+                                 (uint8_t *)(smem + lay.owner), (uint8_t *)(smem + lay.cmap), cur, p.bp + (size_t)c * p.bp_cap,
+                                 p.tok_state + (size_t)c * p.g_tok_cap, f == p.n_frames - 1, cost_alt ? alt : home, cost_alt ? home : alt);
+}
+
 // One call's work on one channel: `pos` is the channel's place in the call's list.
-template <int kBlock, bool kParts>
+template <int kBlock, int kParts>
 __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const int pos, unsigned char *smem) {
   const int tid = threadIdx.x;
   const int c = p.chan_ids[pos];
@@ -1490,17 +1540,21 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
         fast = false; slow = true;
       }
     }
-    if constexpr (kParts) {
-      if (slow && f >= 0) {
+    if constexpr (kParts != kPartsNone) {
+      const bool by_parts = slow && f >= 0;
+      if (kParts == kPartsFew ? __builtin_expect_with_probability(by_parts, 0, 0.999) : by_parts) {
         lds_used = true;
-        outcome = run_frame_parts<kBlock>(p, smem + lay.hval, c, sh, cx, Lrow, rows, p.stage_rows ? Lnext : nullptr, hist, owner_maps,
-                                          closure_maps, cur, bp, g_tok_state, last, cost_alt ? g_cost_alt() : g_cost(),
-                                          cost_alt ? g_cost() : g_cost_alt());
+        if constexpr (kParts == kPartsFew)
+          outcome = frame_by_parts_apart<kBlock>(smem, pos, c, f, cur, cost_alt, cslot, cx.n, cx.offset);
+        else
+          outcome = run_frame_parts<kBlock>(p, smem + lay.hval, c, sh, cx, Lrow, rows, p.stage_rows ? Lnext : nullptr, hist, owner_maps,
+                                            closure_maps, cur, bp, g_tok_state, last, cost_alt ? g_cost_alt() : g_cost(),
+                                            cost_alt ? g_cost() : g_cost_alt());
         if (outcome == kFrameOk) { cur ^= 1; cost_alt = !cost_alt; }
         if (outcome != kFrameRedo) {
           slow = false;
         } else {
-          if (tid == 0) sh->a_parts_back += 1;
+          if (tid == 0) atomicAdd(&sh->a_parts_back, 1);
           if (cost_alt) { costs_home(); cost_alt = false; }
           __syncthreads();
           if (tid < 64) frame_init(sh, hist, false, tid);
@@ -1508,7 +1562,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
         }
       }
     }
-    if (slow) {
+    if (kParts == kPartsFew ? __builtin_expect_with_probability(slow, 0, 0.999) : slow) {
       const Mem<false> MG = make_MG();
       outcome = run_frame<false, kBlock>(p, MG, sh, cx, Lrow, rows, p.stage_rows ? Lnext : nullptr, hist, owner_maps, f, cur, bp, g_tok_state, last);
       if (outcome == kFrameOk) cur ^= 1;
@@ -1516,11 +1570,11 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     if (outcome != kFrameOk) break;
     if (!fast && p.lds_tok_cap > 0 && sh->n_tok <= p.lds_tok_cap) {
       // the token list fits LDS again
-      if (kParts && lds_used) {
+      if (kParts != kPartsNone && lds_used) {
         for (int i = tid; i < p.lds_slots; i += kBlock) { ML.hval[i] = kEmptyVal; ML.hkey[i] = kEmptyKey; }
         lds_used = false;
       }
-      { const float *gc = kParts && cost_alt ? g_cost_alt() : g_cost(); for (int i = tid; i < sh->n_tok; i += kBlock) ML.t_cost[i] = gc[i]; }
+      { const float *gc = kParts != kPartsNone && cost_alt ? g_cost_alt() : g_cost(); for (int i = tid; i < sh->n_tok; i += kBlock) ML.t_cost[i] = gc[i]; }
       cost_alt = false;
       fast = true;
       __syncthreads();
@@ -1539,7 +1593,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     const int n = sh->n_tok;
     if (fast) {
       { float *gc = g_cost(); for (int i = tid; i < n; i += kBlock) gc[i] = ML.t_cost[i]; }
-    } else if (kParts && cost_alt) {
+    } else if (kParts != kPartsNone && cost_alt) {
       costs_home();
     }
   } else if (outcome != kFrameNoTokens) {
@@ -1642,13 +1696,13 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
 template <int kBlock>
 __global__ __launch_bounds__(kBlock, 4) void advance_kernel(AdvanceParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  advance_channel<kBlock, false>(p, (int)blockIdx.x, smem);
+  advance_channel<kBlock, kPartsNone>(p, (int)blockIdx.x, smem);
 }
 // The same with frames by parts (run_frame_parts), for graphs with long rows.
-template <int kBlock>
+template <int kBlock, int kParts>
 __global__ __launch_bounds__(kBlock, 4) void advance_parts_kernel(AdvanceParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  advance_channel<kBlock, true>(p, (int)blockIdx.x, smem);
+  advance_channel<kBlock, kParts>(p, (int)blockIdx.x, smem);
 }
 
 // The same with 120 instead of 128 vector registers per wave, for launches that start while result walks of
@@ -1662,7 +1716,14 @@ __global__ __launch_bounds__(kBlock, 4) void advance_parts_kernel(AdvanceParams 
 template <int kBlock>
 __global__ __launch_bounds__(kBlock, 4) __attribute__((amdgpu_num_vgpr(60))) void advance_beside_kernel(AdvanceParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  advance_channel<kBlock, false>(p, (int)blockIdx.x, smem);
+  advance_channel<kBlock, kPartsNone>(p, (int)blockIdx.x, smem);
+}
+// (for graphs with long rows, kPartsFew; a launch whose frames mostly outgrow LDS is not held up by walks: 160 channels x 40
+// frames of 20,000 words in two chunks, 4,235 us with results walked beside the second, 4,242 without)
+template <int kBlock>
+__global__ __launch_bounds__(kBlock, 4) __attribute__((amdgpu_num_vgpr(60))) void advance_parts_beside_kernel(AdvanceParams p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  advance_channel<kBlock, kPartsFew>(p, (int)blockIdx.x, smem);
 }
 
 // ---- self-test of the cross-lane primitives ------------------------------------

@@ -752,7 +752,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       atomicAdd(&sh->a_tokens, (unsigned long long)n_claim);
       atomicMax(&sh->a_maxtok, n_claim);
       atomicAdd(&sh->a_slow, 1);
-      sh->a_parts += 1;
+      atomicAdd(&sh->a_parts, 1);
       atomicAdd(&sh->a_impr, (unsigned long long)n_claim);
       atomicAdd(&sh->a_rounds, (unsigned long long)sh->rounds);
     }

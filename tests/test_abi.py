@@ -82,5 +82,12 @@ def test_decoding_kernel_register_budget():
     k1024 = [v for k, v in usage.items() if "advance_kernelILi1024E" in k]
     assert len(k1024) == 1
     assert k1024[0]["vgprs"] <= 128 and k1024[0]["scratch"] <= 96
+    # (frames by parts are a third code in the same kernel)
+    parts = [v for k, v in usage.items() if "advance_parts_kernelILi1024E" in k]
+    assert len(parts) == 2
+    assert all(v["vgprs"] <= 128 and v["scratch"] <= 96 for v in parts)
+    beside = [v for k, v in usage.items() if "advance_beside_kernel" in k or "advance_parts_beside_kernel" in k]
+    assert len(beside) == 2
+    assert all(v["vgprs"] <= 120 and v["scratch"] <= 128 for v in beside)
     walk = [v for k, v in usage.items() if "best_walk_kernel" in k]
     assert len(walk) == 1 and walk[0]["vgprs"] <= 32

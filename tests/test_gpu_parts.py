@@ -5,6 +5,8 @@ graph that the shares cannot take."""
 import numpy as np
 import pytest
 
+import gpu_harness as GH
+from paper_2306_15685_amd import binding as B
 from paper_2306_15685_amd import synth
 
 from test_gpu_parity import run_batch, torch_cuda  # noqa: F401
@@ -72,7 +74,7 @@ def test_closure_that_is_not_stored(torch_cuda):  # noqa: F811
     g = hub_graph(2_000, 64, 6, 1_500, seed=12, eps_hubs=1)
     L, ctxs, offs = inputs(torch_cuda, g, 3, 24, 2.5, 12)
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=7.0, max_active=0, chunks=[1, 6, 17], hash_log2=12, lds_token_cap=64)
-    assert s["slow_frames"] > 0 and s["parts"] == {"shares": 0, "frames": 0, "given_up": 0}
+    assert s["slow_frames"] > 0 and s["parts"] == {"shares": 0, "mostly": False, "frames": 0, "given_up": 0}
 
 
 def test_pruning_finals_and_swap(torch_cuda):  # noqa: F811
@@ -112,3 +114,55 @@ def test_lexicon_loop(torch_cuda, words, shares):  # noqa: F811
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=10.0, max_active=800 if words > 600 else 100, chunks=[3, 10, 12], hash_log2=15,
                   lookup_mode=1, lds_token_cap=0 if words > 600 else 256)
     assert s["status"] == 0 and by_parts(s, shares)
+
+
+@pytest.mark.parametrize("block", [1024, 960, 512, 256])
+def test_kernel_for_frames_that_mostly_outgrow_lds(torch_cuda, block):  # noqa: F811
+    """records_per_frame chooses between two kernels of the same results: more than the LDS tables hold, or not (equal to
+    them, or not given)."""
+    g = hub_graph(2_000, 64, 6, 1_500, seed=21)
+    L, ctxs, offs = inputs(torch_cuda, g, 2, 16, 2.5, 21)
+    for records, mostly in ((0, False), (64, False), (65, True), (2_000, True)):
+        s = run_batch(torch_cuda, g, L, ctxs, offs, beam=7.0, max_active=0, chunks=[5, 11], hash_log2=12, lds_token_cap=64,
+                      block_threads=block, max_frames=16 if records in (0, 2_000) else 400, records_per_frame=records)
+        assert s["parts"]["mostly"] is mostly and s["parts"]["frames"] > s["frames"] // 4
+
+
+def test_long_rows_beside_result_walks(torch_cuda):  # noqa: F811
+    """A decoder whose calls fill the device in one round, on a graph with long rows: every chunk's partial result is
+    requested before the next chunk is decoded, which then runs in the 120-register kernel.  Lean frames, general ones and
+    frames by parts; partial results, final tables and paths are the checker's (every fifth channel)."""
+    n_cu = torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    C, T = n_cu * 5 // 8, 30
+    g = hub_graph(6_000, 400, 3, 700, seed=5)
+    L, ctxs, offs = inputs(torch_cuda, g, C, T, 4.0, 5)
+    dec = GH.GpuDecoder(g, C, 9.0, max_frames=T, hash_log2=13, lds_token_cap=192)
+    try:
+        some = range(0, C, 5)
+        orcs = dict(zip(some, GH.oracle_channels(g, len(some), 9.0)))
+        Lh = L[::5].cpu().numpy()
+        dec.set_contexts(ctxs, offs)
+        dec.reset()
+        for c in some:
+            orcs[c].set_context(ctxs[c], offs[c])
+            orcs[c].reset()
+        pending, want = None, None
+        for t in range(0, T, 6):
+            dec.advance(L, t, t + 6)
+            if pending is not None:
+                st, wl, al, cost, na, nw = B.cbd_best_paths_finish(dec.dh, pending)
+                for c in some:
+                    GH.assert_best_equal((int(st[c]), wl[c], al[c], float(cost[c])), want[c], f"partial t={t} ch={c}")
+            pending = B.cbd_best_paths_begin(dec.dh, dec.all, False, 4 * T + 16)
+            for i, c in enumerate(some):
+                orcs[c].advance(Lh[i, t:t + 6])
+            want = {c: orcs[c].best_path(False) for c in some}
+        B.cbd_best_paths_finish(dec.dh, pending)
+        for c in some:
+            GH.assert_tables_equal(dec.tokens(c), orcs[c].tokens(), f"final table ch={c}")
+            GH.assert_best_equal(dec.best(c), orcs[c].best_path(False), f"final ch={c}")
+        p, s = B.cbd_get_parts(dec.dh), dec.stats()
+        print("beside", p, s["lean_frames"], s["frames"], flush=True)
+        assert p["shares"] > 0 and not p["mostly"] and p["frames"] > 0 and 0 < s["lean_frames"] < s["frames"]
+    finally:
+        dec.close()
