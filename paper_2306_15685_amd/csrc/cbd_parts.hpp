@@ -21,7 +21,7 @@
 // Graphs without long rows keep the general code for the few frames that outgrow LDS: with this code beside the lean
 // frames in their kernel, the register allocator spills 25 instead of 6 vector registers and the lean frames take 3 to 6 %
 // longer, which is more than the frames that outgrow LDS are worth there (2,048 channels at beam 16: 10.24 -> 10.85 ms).
-// A frame that does not fit (a full queue or share) leaves nothing behind and is redone by the general code.
+// A frame that does not fit (a full queue or share) leaves nothing behind and is redone by the general code (parts_failed).
 #pragma once
 
 namespace cbd {
@@ -263,6 +263,15 @@ __device__ __forceinline__ void parts_closures(const AdvanceParams &p, Shared *s
   }
 }
 
+// A frame was begun by parts and given up (one thread).  Such a frame is decoded twice, and its like tend to follow: from
+// the third in a row on, 1, 2, 4 ... 64 frames go straight to the general code before one is tried again.
+__device__ __forceinline__ void parts_failed(Shared *sh) {
+  sh->a_parts_back += 1;
+  const int n = min(sh->parts_fails + 1, 9);
+  sh->parts_fails = n;
+  if (n >= 3) sh->parts_wait = 1 << (n - 3);
+}
+
 // One frame.  region: the LDS of the lean tables, p.part_slots * 12 bytes.  cost_in / cost_out: the current tokens'
 // costs and where the new ones go (apart, so that a frame can be given up at any point).  Returns kFrameOk,
 // kFrameNoTokens, kFrameOverflow, kFrameRecordsFull, or kFrameRedo (the general code decodes the frame).
@@ -288,11 +297,16 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   const int lists_cap = (int)((p.part_slots * 12 - NW * 64 * (int)sizeof(LiveToken)) / 16);
   const bool hist_on = p.max_active > 0 && p.beam > 0.0f && p.beam < __builtin_inff();
   const float inv = 256.0f / p.beam;
+  const int wait = __builtin_amdgcn_readfirstlane(sh->parts_wait);
   if (tid < 16) { sh->wcount[tid] = 0; sh->wbase[tid] = 0; }
 #ifdef CBD_PROFILE
   if (tid == 0) sh->prof_last = wall_clock64();
 #endif
   __syncthreads();
+  if (__builtin_expect(wait > 0, 0)) {   // (uniform)
+    if (tid == 0) sh->parts_wait = wait - 1;
+    return kFrameRedo;
+  }
 
   // ---- 1: prune and expand
   uint32_t n_active = 0, n_emit = 0, n_eps = 0, n_cand = 0;
@@ -510,7 +524,10 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     }
   }
   __syncthreads();
-  if (sh->fault) return kFrameRedo;   // (uniform: set in steps 1 and 2 only) a queue is full
+  if (__builtin_expect(sh->fault, 0)) {   // (uniform: set in steps 1 and 2 only) a queue is full
+    if (tid == 0) parts_failed(sh);
+    return kFrameRedo;
+  }
   CBD_STAMP(2);   // (diagnostic: closure lists)
   const float fbest = ord2f(umin32(m_ord, sh->best_ord));
   bool have_closures = false;
@@ -618,7 +635,10 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       }
     });
     __syncthreads();
-    if (sh->redo) return kFrameRedo;   // (uniform: set between this barrier and the one before) the share's table is full
+    if (__builtin_expect(sh->redo, 0)) {   // (uniform: set between this barrier and the one before) the share's table is full
+      if (tid == 0) parts_failed(sh);
+      return kFrameRedo;
+    }
     CBD_STAMP(4);   // (diagnostic: shares recombined)
     // An emitting arc is expanded once per frame, so its entry is the only one with its key; a closure arc can have been
     // reached twice with the same key: there an exchange lets one of the two through.
@@ -753,6 +773,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       atomicMax(&sh->a_maxtok, n_claim);
       atomicAdd(&sh->a_slow, 1);
       atomicAdd(&sh->a_parts, 1);
+      sh->parts_fails = 0;
       atomicAdd(&sh->a_impr, (unsigned long long)n_claim);
       atomicAdd(&sh->a_rounds, (unsigned long long)sh->rounds);
     }

@@ -51,7 +51,7 @@ def by_parts(s, shares):
     threads, leave little room for the list of closures: 4 to 29 of some 72 frames are given up for it.)"""
     p = s["parts"]
     print("parts", p, "slow", s["slow_frames"], "of", s["frames"], "max tokens", s["max_tokens"], flush=True)
-    return p["shares"] == shares and p["frames"] + p["given_up"] == s["slow_frames"] and p["frames"] > p["given_up"]
+    return p["shares"] == shares and s["slow_frames"] // 2 < p["frames"] <= s["slow_frames"] - p["given_up"]
 
 
 @pytest.mark.parametrize("hash_log2,block,pdfs,shares", [
@@ -102,6 +102,19 @@ def test_queues_too_small(torch_cuda):  # noqa: F811
     s = run_batch(torch_cuda, g, L, ctxs, np.abs(offs), beam=6.0, max_active=0, chunks=[5, 7], hash_log2=10, lds_token_cap=64)
     assert s["status"] == 0 and s["parts"]["shares"] == 1 and s["parts"]["given_up"] > 0
     assert s["parts"]["frames"] < s["slow_frames"]
+
+
+@pytest.mark.parametrize("chunks", [[40], [1] * 40])
+def test_frames_that_keep_failing(torch_cuda, chunks):  # noqa: F811
+    """When frames are given up one after another, most of the following ones are not begun by parts any more, also from
+    call to call."""
+    g = hub_graph(300, 40, 2, 600, seed=9)
+    L, ctxs, offs = inputs(torch_cuda, g, 2, 40, 1.0, 9, arcs=30)
+    s = run_batch(torch_cuda, g, L, ctxs, np.abs(offs), beam=6.5, max_active=0, chunks=chunks, hash_log2=10, lds_token_cap=64)
+    print("failing", s["parts"], s["slow_frames"], flush=True)
+    assert s["status"] == 0 and s["slow_frames"] > 60
+    # (40 frames of a channel that all fail: 3 tries, then one after 1, 2, 4, 8 and 16 frames)
+    assert 0 < s["parts"]["given_up"] <= s["slow_frames"] // 3
 
 
 @pytest.mark.parametrize("words,shares", [(600, 8), (6_000, 2)])
