@@ -309,6 +309,39 @@ hipError_t prepare_long_rows(cbd_decoder *d, int k, int slots) {
   return e;
 }
 
+// The graph's long rows for a team, their arcs sorted by owning member (a few thousand rows at most: beyond that the rows
+// are shared out arc by arc through the queues, as are rows this table does not know).  The arcs' records are copied in
+// that order (2 % of a frame) where the copy takes at most an eighth of the memory that the decoder holds anyway and is
+// to be had once everything else is; elsewhere they are read through their indices.
+hipError_t prepare_team_rows(cbd_decoder *d) {
+  const size_t k = (size_t)d->team_k;
+  if (d->g->long_rows.empty() || d->g->long_rows.size() > 4096) return hipSuccess;
+  std::vector<int4> rows = d->g->long_rows;
+  int64_t total = 0;
+  for (auto &r : rows) { r.w = (int)total; total += r.z; }
+  if (total >= 0x7FFFFFF0) return hipSuccess;
+  const size_t rows_b = sizeof(int4) * rows.size(), group_b = sizeof(int32_t) * rows.size() * (k + 1);
+  size_t recs_b = sizeof(cbd::ArcRec) * (size_t)total;
+  if (recs_b > d->bytes / 8) recs_b = 0;
+  hipError_t e = dmalloc(&d->d_team_big, recs_b + rows_b + group_b + sizeof(int32_t) * (size_t)total, &d->bytes);
+  if (e != hipSuccess && recs_b > 0) {
+    (void)hipGetLastError();
+    recs_b = 0;
+    e = dmalloc(&d->d_team_big, rows_b + group_b + sizeof(int32_t) * (size_t)total, &d->bytes);
+  }
+  if (e != hipSuccess) return e;
+  d->team_n_big_rows = (int32_t)rows.size();
+  d->team_big_recs = recs_b ? (cbd::ArcRec *)d->d_team_big : nullptr;
+  d->team_big_rows = (int4 *)(d->d_team_big + recs_b);
+  d->team_big_group = (int32_t *)(d->d_team_big + recs_b + rows_b);
+  d->team_big_perm = (int32_t *)(d->d_team_big + recs_b + rows_b + group_b);
+  e = hipMemcpy(d->team_big_rows, rows.data(), rows_b, hipMemcpyHostToDevice);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(cbd::team_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, d->g->d_arcs,
+                     d->team_big_rows, d->team_big_group, d->team_big_perm, d->team_big_recs, d->team_k);
+  return hipGetLastError();
+}
+
 // A team launch.  The members of a team wait for one another inside the kernel, so all of a launch's workgroups
 // have to become resident without waiting for one another: the grid never exceeds the device's compute units
 // (checked when the decoder is made), a workgroup fills a compute unit's LDS, launches of one decoder follow one
@@ -329,7 +362,7 @@ hipError_t launch_team(const cbd_decoder *d, const AdvanceParams &p, int n_chann
   tp.n_teams = n_channels;
   tp.k = d->team_k; tp.q_cap = d->team_q_cap; tp.part_cap = d->team_part_cap; tp.slots = d->team_slots;
   tp.stage_rows = d->team_stage_rows; tp.ctx_lds_cap = d->ctx_lds_cap;
-  hipLaunchKernelGGL(cbd::advance_team_kernel<1024>, dim3((unsigned)(padded * d->team_k)), dim3(1024), d->team_lds, d->stream, tp);
+  hipLaunchKernelGGL((d->team_big_recs ? cbd::advance_team_kernel<1024, true> : cbd::advance_team_kernel<1024, false>), dim3((unsigned)(padded * d->team_k)), dim3(1024), d->team_lds, d->stream, tp);
   return hipGetLastError();
 }
 
@@ -955,13 +988,14 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
     // (a sender's queue to one owner: in the frame after a reset one member expands a long start row by itself)
     d->team_q_cap = d->team_part_cap + d->team_part_cap / 4;
     d->team_lds = cbd::team_layout(d->team_stage_rows ? g->P : 0, d->ctx_lds_cap, slots, d->team_block / 64).total;
-    DCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&cbd::advance_team_kernel<1024>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)d->team_lds));
+    for (auto kernel : {cbd::advance_team_kernel<1024, true>, cbd::advance_team_kernel<1024, false>})
+      DCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)d->team_lds));
     {
       // the members wait for one another inside the kernel: the device has to hold all of them at once
-      int per_cu = 0;
-      DCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cbd::advance_team_kernel<1024>, 1024, d->team_lds));
-      if ((int64_t)per_cu * n_cu < (int64_t)d->C * k)
+      int per_cu = 0, per_cu_recs = 0;
+      DCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cbd::advance_team_kernel<1024, false>, 1024, d->team_lds));
+      DCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_recs, cbd::advance_team_kernel<1024, true>, 1024, d->team_lds));
+      if ((int64_t)std::min(per_cu, per_cu_recs) * n_cu < (int64_t)d->C * k)
         return fail(CBD_E_INVALID, "decoder: the device cannot hold all members of all teams at once");
     }
     // a frame's records: one block of k shares
@@ -990,27 +1024,6 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
     DCHK(dmalloc(&d->d_team_cwin, C * k * (size_t)d->team_part_cap, &d->bytes));
     DCHK(dmalloc(&d->d_team_pub_key, C * k * (size_t)d->team_slots, &d->bytes));
     DCHK(dmalloc(&d->d_team_pub_lid, C * k * (size_t)d->team_slots, &d->bytes));
-    // the graph's long rows, their arcs sorted by owning member (a few thousand rows at most: beyond that the
-    // rows are shared out arc by arc through the queues, as are rows this table does not know)
-    if (!g->long_rows.empty() && g->long_rows.size() <= 4096) {
-      std::vector<int4> rows = g->long_rows;
-      int64_t total = 0;
-      for (auto &r : rows) { r.w = (int)total; total += r.z; }
-      if (total < 0x7FFFFFF0) {
-        d->team_n_big_rows = (int32_t)rows.size();
-        const size_t recs_b = sizeof(cbd::ArcRec) * (size_t)total, rows_b = sizeof(int4) * rows.size(),
-                     group_b = sizeof(int32_t) * rows.size() * (k + 1);
-        DCHK(dmalloc(&d->d_team_big, recs_b + rows_b + group_b + sizeof(int32_t) * (size_t)total, &d->bytes));
-        d->team_big_recs = (cbd::ArcRec *)d->d_team_big;
-        d->team_big_rows = (int4 *)(d->d_team_big + recs_b);
-        d->team_big_group = (int32_t *)(d->d_team_big + recs_b + rows_b);
-        d->team_big_perm = (int32_t *)(d->d_team_big + recs_b + rows_b + group_b);
-        DCHK(hipMemcpy(d->team_big_rows, rows.data(), sizeof(int4) * rows.size(), hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(cbd::team_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, g->d_arcs,
-                           d->team_big_rows, d->team_big_group, d->team_big_perm, d->team_big_recs, d->team_k);
-        DCHK(hipGetLastError());
-      }
-    }
   }
   if (d->parts > 0) DCHK(prepare_long_rows(d, d->parts, d->part_slots));
   DCHK(dmalloc(&d->d_ctx_n, C + d->pool, &d->bytes));
@@ -1042,6 +1055,7 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
   DCHK(dmalloc(&d->d_ids_kept, C, &d->bytes));
   // context staging: [channels n][list offsets n+1][offsets n][lists ...]
   DCHK(d->ctxs.init(sizeof(int32_t) * (C * 4 + 1 + C * (size_t)d->max_ctx)));
+  if (d->team_k > 1) DCHK(prepare_team_rows(d));
   DCHK(hipStreamSynchronize(d->stream));
 #undef DCHK
   guard.d = nullptr;

@@ -88,7 +88,7 @@ struct TeamParams {
   const int4 *big_rows;    // [n_big_rows] x = state (ascending), y = first emitting arc, z = emitting arcs, w = start in big_perm
   const int32_t *big_group;  // [n_big_rows][k + 1] where each member's arcs begin in the row's stretch of big_perm
   const int32_t *big_perm;   // library arc indices
-  const ArcRec *big_recs;    // the same places: the arcs' records
+  const ArcRec *big_recs;    // the same places: the arcs' records (null: they are read through big_perm)
   int32_t n_big_rows;
   int32_t k;               // members per team
   int32_t q_cap;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) void team_prepare_rows_kernel(const ArcRec *ar
     const ArcRec rec = arcs[row.y + j];
     const int at = row.w + atomicAdd(&fill[share_owner((uint32_t)rec.dst, k)], 1);
     big_perm[at] = row.y + j;
-    big_recs[at] = rec;
+    if (big_recs) big_recs[at] = rec;
   }
 }
 // The place of `state` among the long rows, or -1.
@@ -354,7 +354,8 @@ __global__ void team_reset_kernel(TeamChan *team, const int32_t *chan_ids, int n
 #define TEAM_STAMP(k_) do {} while (0)
 #endif
 
-template <int kBlock>
+// kRecs: the long rows' records are there in the sorted order.  (Chosen within the kernel, they cost all of it 1.3 %.)
+template <int kBlock, bool kRecs>
 __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const AdvanceParams &p = tp.a;
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
     // 100 frames of 20,000 words 8.43 -> 8.26 ms, 8 channels of 3,000 words the same)
     auto long_load = [&](int perm0, int t, int t_end, int &a, ArcRec &rec) {
       a = -1; rec.dst = 0; rec.weight = 0.0f; rec.row = 0; rec.meta = 0;
-      if (t < t_end) { a = tp.big_perm[perm0 + t]; rec = tp.big_recs[perm0 + t]; }
+      if (t < t_end) { a = tp.big_perm[perm0 + t]; rec = kRecs ? tp.big_recs[perm0 + t] : p.arcs[a]; }
     };
     auto long_entry = [&](int a, const ArcRec &rec, float cost, int src) {
       TeamEntry e; e.dst = kEmptyKey; e.cost = 0.0f; e.arc = 0; e.from = 0; e.row = 0; e.meta = 0; e.pad[0] = 0; e.pad[1] = 0;

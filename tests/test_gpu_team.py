@@ -117,3 +117,21 @@ def test_team_overflow_parks_the_channel_and_reset_revives_it(torch_cuda):
                 GH.assert_best_equal(dec.best(c), orcs[c].best_path(False), f"after reset ch={c}")
     finally:
         dec.close()
+
+
+def test_team_of_a_small_decoder_on_very_long_rows(torch_cuda):
+    """Rows of some 300,000 arcs and a decoder that holds a few MB: what it keeps of the long rows is four bytes per arc and
+    at most an eighth of the rest (the arcs' records are then read through their indices, not copied)."""
+    from test_gpu_parts import hub_graph, inputs
+    print("team of 2: very long rows", flush=True)
+    g = hub_graph(3_000, 48, 4, 300_000, seed=31)
+    short = hub_graph(3_000, 48, 1, 513, seed=31)
+    deg = np.diff(g.row_offsets)
+    g.start_state = int(np.flatnonzero((deg > 2) & (deg < 10))[0])   # (one member alone expands the start state's row)
+    long_arcs = int(deg[deg > 512].sum())
+    L, ctxs, offs = inputs(torch_cuda, g, 2, 8, 2.0, 31)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=1.5, max_active=0, chunks=[3, 5], hash_log2=14, workgroups_per_channel=2)
+    base = run_batch(torch_cuda, short, L, [[], []], offs, beam=1.0, max_active=0, chunks=[8], hash_log2=14, workgroups_per_channel=2)
+    rows, rest = s["info"]["device_bytes"] - base["info"]["device_bytes"], base["info"]["device_bytes"]
+    print("long-row arcs", long_arcs, "bytes", rows, "rest", rest, flush=True)
+    assert long_arcs > 200_000 and rows <= 4 * long_arcs + rest // 8 + 65_536
