@@ -268,13 +268,15 @@ hipError_t resident_per_cu(int block, int parts, uint32_t lds, int *n) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, decode_kernel<1024>(parts), 1024, lds);
 }
 
-// Lays out the graph's long rows for k shares with tables of `slots` slots each (prepare_long_rows_kernel): as many of
-// them as leave half of the slots to other states, 4,096 at most.  Rows without a layout go arc by arc through the queues.
+// Lays out the graph's long rows for k shares with tables of `slots` slots each (prepare_long_rows_kernel): those that
+// together, in the graph's order, leave half of the slots to other states, 4,096 at most.  Rows without a layout go arc by
+// arc through the queues; so do all rows if a share is full or there is no memory.
 hipError_t prepare_long_rows(cbd_decoder *d, int k, int slots) {
   std::vector<int4> rows;
   int64_t total = 0;
   for (int4 r : d->g->long_rows) {
-    if (rows.size() == 4096 || total + r.z > (int64_t)k * slots / 2) break;
+    if (rows.size() == 4096) break;
+    if (total + r.z > (int64_t)k * slots / 2) continue;
     r.w = (int)total;
     total += r.z;
     rows.push_back(r);
@@ -285,7 +287,10 @@ hipError_t prepare_long_rows(cbd_decoder *d, int k, int slots) {
                rows_b = sizeof(int4) * n, group_b = (sizeof(int32_t) * n * ((size_t)k + 2) + 15) / 16 * 16,
                meta_b = (sizeof(uint32_t) * (size_t)total + 15) / 16 * 16;
   hipError_t e = dmalloc(&d->d_long, arcs_b + image_b + rows_b + group_b + meta_b + 16, &d->bytes);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;
+  }
   char *at = d->d_long;
   cbd::LongRows &l = d->long_rows;
   l.arcs = (cbd::LongArc *)at; at += arcs_b;
@@ -304,7 +309,8 @@ hipError_t prepare_long_rows(cbd_decoder *d, int k, int slots) {
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&full, d_full, sizeof(int32_t), hipMemcpyDeviceToHost, d->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(d->stream);
+  const hipError_t done = hipStreamSynchronize(d->stream);   // (also after an error: rows and full are about to go)
+  if (e == hipSuccess) e = done;
   l.n = e == hipSuccess && !full ? (int32_t)n : 0;
   return e;
 }
@@ -1025,7 +1031,6 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
     DCHK(dmalloc(&d->d_team_pub_key, C * k * (size_t)d->team_slots, &d->bytes));
     DCHK(dmalloc(&d->d_team_pub_lid, C * k * (size_t)d->team_slots, &d->bytes));
   }
-  if (d->parts > 0) DCHK(prepare_long_rows(d, d->parts, d->part_slots));
   DCHK(dmalloc(&d->d_ctx_n, C + d->pool, &d->bytes));
   DCHK(dmalloc(&d->d_ctx_off, C + d->pool, &d->bytes));
   DCHK(hipMemsetAsync(d->d_ctx_n, 0, sizeof(int32_t) * (C + d->pool), d->stream));
@@ -1055,6 +1060,8 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
   DCHK(dmalloc(&d->d_ids_kept, C, &d->bytes));
   // context staging: [channels n][list offsets n+1][offsets n][lists ...]
   DCHK(d->ctxs.init(sizeof(int32_t) * (C * 4 + 1 + C * (size_t)d->max_ctx)));
+  // (last: what they ask for beyond the rest they can do without)
+  if (d->parts > 0) DCHK(prepare_long_rows(d, d->parts, d->part_slots));
   if (d->team_k > 1) DCHK(prepare_team_rows(d));
   DCHK(hipStreamSynchronize(d->stream));
 #undef DCHK

@@ -104,6 +104,30 @@ def test_queues_too_small(torch_cuda):  # noqa: F811
     assert s["parts"]["frames"] < s["slow_frames"]
 
 
+def test_one_row_too_long_to_lay_out(torch_cuda):  # noqa: F811
+    """The first long row, the start state's, alone exceeds what the shares' tables take; the others are laid out all the
+    same (the key tables, four bytes per slot, are there), and all frames agree."""
+    g = hub_graph(2_000, 64, 6, 600, seed=12)
+    deg = np.diff(g.row_offsets)
+    others, n = int(deg[deg > 512].sum() - deg[g.start_state]), 6_000
+    rng = np.random.default_rng(4)
+    at = g.row_offsets[g.start_state + 1]
+    add = lambda x, y: np.insert(x, at, np.asarray(y, x.dtype))  # noqa: E731
+    row = g.row_offsets.copy()
+    row[g.start_state + 1:] += n
+    big = synth.Graph(g.num_states, g.num_arcs + n, g.num_pdfs, g.num_words, g.start_state, row, add(g.dst, rng.integers(0, 2_000, n)),
+                      add(g.ilabel, rng.integers(1, 65, n)), add(g.olabel, rng.integers(0, 500, n)), add(g.weight, rng.uniform(0, 3, n)), None)
+    assert others < 2 * 2_880 // 2 < n
+    plain = synth.make_graph(2_000, 64, 500, 0.15, seed_stream=(12, 7))
+    L, ctxs, offs = inputs(torch_cuda, big, 3, 16, 2.5, 12)
+    kw = dict(beam=7.0, max_active=0, chunks=[1, 15], hash_log2=13, lds_token_cap=64)
+    s = run_batch(torch_cuda, big, L, ctxs, offs, **kw)
+    base = run_batch(torch_cuda, plain, L, [c[c < plain.num_arcs] for c in ctxs], offs, **kw)
+    extra = s["info"]["device_bytes"] - base["info"]["device_bytes"]
+    print("too long", s["parts"], s["slow_frames"], extra, flush=True)
+    assert s["parts"]["shares"] == 2 and s["parts"]["frames"] > 0 and extra > 4 * 2 * 2_880
+
+
 @pytest.mark.parametrize("chunks", [[40], [1] * 40])
 def test_frames_that_keep_failing(torch_cuda, chunks):  # noqa: F811
     """When frames are given up one after another, most of the following ones are not begun by parts any more, also from
