@@ -110,11 +110,11 @@ struct __attribute__((aligned(128))) ChanState {
   long long lean_frames; // frames decoded by the lean code
   int32_t parts_frames;  // frames decoded by parts
   int32_t parts_given_up; // frames begun by parts and decoded by the general code
-  int32_t parts_fails;   // how many of these in a row, and how many more frames go straight to the general code
-  int32_t parts_wait;    // (parts_failed)
+  int32_t parts_state;   // how frames by parts have fared lately (parts_failed)
 #ifdef CBD_PROFILE
   long long spare[15];
 #else
+  int32_t spare0;
   long long spare[13];
 #endif
 #ifdef CBD_PROFILE
@@ -220,6 +220,7 @@ struct Shared {
   uint32_t lean_best[2];      // lean frames, in turn: minimum over the closure candidates accepted
   int32_t a_maxtok, a_slow;   // counters of this call
   int32_t a_lean;             // frames decoded by the lean code
+  int32_t parts_state;        // as in ChanState
   unsigned long long a_lean_tokens;    // their tokens
   unsigned long long a_lean_pack[2];   // its counters, two to a word: active tokens | emitting arcs << 32,
                                        // epsilon-input arcs | candidates << 32
@@ -230,10 +231,11 @@ struct Shared {
   int32_t prof_why[8];   // why lean frames went back to the general code (see CBD_WHY)
   long long prof_general;   // time in those frames' second run
 #endif
+  // (the upper halves of a_frames and a_rounds count frames by parts and such frames given up: kPartsCount)
   unsigned long long a_frames, a_active, a_emit, a_eps, a_cand, a_impr, a_tokens, a_rounds;
-  int32_t a_parts, a_parts_back;   // frames by parts; begun by parts and given up
-  int32_t parts_fails, parts_wait;   // as in ChanState
 };
+
+constexpr unsigned long long kPartsCount = 1ull << 32;
 
 __device__ __forceinline__ int sh_log_n(const Shared *sh) { return (int)(uint32_t)sh->log_claim; }
 __device__ __forceinline__ int sh_n_claim(const Shared *sh) { return (int)(uint32_t)(sh->log_claim >> 32); }
@@ -1325,14 +1327,14 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
 // What a kernel does with frames that outgrow LDS: kPartsNone leaves them to the general code; the others decode them by
 // parts, kPartsFew in a kernel whose registers go to the lean and the general frames, kPartsMost in one that treats all
 // frames alike.  The two differ in nothing but speed (cbd_decoder_create chooses; us, kPartsNone / Few / Most):
-//   256 channels x 500 frames, all lean, results walked beside       5,805 / 5,790 / 6,930
-//   2,048 channels x 100 frames, all but 80 of 204,800 lean          8,810 / 8,770 / 9,650
-//   32 channels x 333 frames, all lean                               2,312 / 2,308 / 2,414
-//   150 channels x 60 frames of 2,000 words, general code in LDS     1,790 / 1,806 / 1,848
+//   256 channels x 500 frames, all lean, results walked beside       5,805 / 5,820 / 6,930
+//   2,048 channels x 100 frames, all but 80 of 204,800 lean          8,810 / 9,000 / 9,660
+//   32 channels x 333 frames, all lean                               2,312 / 2,309 / 2,420
+//   150 channels x 60 frames of 2,000 words, general code in LDS     1,790 / 1,805 / 1,848
 //   148 channels x 40 frames of 5,600 words, all by parts            7,385 / 2,165 / 1,980
 //   160 channels x 40 frames of 20,000 words, all by parts          30,360 / 4,570 / 4,205
 // (The worst found: 160 channels on a graph whose long rows are met in most frames, 900 tokens each, general code in LDS,
-// results walked beside: 23,400 / 24,400 / 24,300.)
+// results walked beside: 23,400 / 25,400 / 24,300.)
 enum { kPartsNone = 0, kPartsFew = 1, kPartsMost = 2 };
 
 // kPartsFew: a frame by parts that has nothing in common with the code around it.  The kernel's parameters are read anew
@@ -1432,8 +1434,8 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     sh->cut_bin = p.do_reset ? 255 : cs->cut_bin;
     sh->a_maxtok = 0; sh->a_slow = 0;
     if constexpr (kParts != kPartsNone) {
-      sh->parts_fails = p.do_reset ? 0 : cs->parts_fails;
-      sh->parts_wait = p.do_reset ? 0 : cs->parts_wait;
+      if (p.do_reset) { cs->parts_frames = 0; cs->parts_given_up = 0; cs->parts_state = 0; }
+      sh->parts_state = cs->parts_state;
     }
     sh->a_frames = sh->a_active = sh->a_emit = sh->a_eps = sh->a_cand = sh->a_impr = sh->a_tokens = sh->a_rounds = 0;
   }
@@ -1477,7 +1479,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
 
   int outcome = kFrameOk;
   if (tid < 64) frame_init(sh, hist, p.do_reset != 0, tid);
-  if (tid == 0) { sh->a_lean = 0; sh->a_parts = 0; sh->a_parts_back = 0; sh->a_lean_tokens = 0; sh->a_lean_pack[0] = 0; sh->a_lean_pack[1] = 0; }
+  if (tid == 0) { sh->a_lean = 0; sh->a_lean_tokens = 0; sh->a_lean_pack[0] = 0; sh->a_lean_pack[1] = 0; }
 #ifdef CBD_PROFILE
   if (tid == 0) {
     for (int k = 0; k < 12; ++k) sh->prof[k] = 0;
@@ -1620,11 +1622,10 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
       cs->frames = 0; cs->active_tokens = 0; cs->emit_arcs = 0; cs->eps_arcs = 0; cs->candidates = 0;
       cs->improvements = 0; cs->tokens = 0; cs->eps_rounds = 0; cs->max_tokens = 0; cs->slow_frames = 0;
       cs->gc_base = 0; cs->gc_runs = 0; cs->gc_dropped = 0; cs->n_fixed_arcs = 0; cs->n_fixed_words = 0;
-      cs->lean_frames = 0; cs->parts_frames = 0; cs->parts_given_up = 0; cs->parts_fails = 0; cs->parts_wait = 0;
+      cs->lean_frames = 0;
     }
     cs->lean_frames += sh->a_lean;
-    cs->parts_frames += sh->a_parts; cs->parts_given_up += sh->a_parts_back;
-    if constexpr (kParts != kPartsNone) { cs->parts_fails = sh->parts_fails; cs->parts_wait = sh->parts_wait; }
+    if constexpr (kParts != kPartsNone) cs->parts_state = sh->parts_state;
 #ifdef CBD_PROFILE
     if (p.do_reset) for (int k = 0; k < 15; ++k) cs->spare[k] = 0;
     for (int k = 0; k < 7; ++k) cs->spare[k] += sh->prof[k];
@@ -1646,8 +1647,12 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
       cs->timeline[3] = pos;
     }
     cs->spare[10] += sh->a_lean;
-    cs->spare[11] += (long long)sh->a_frames + sh->a_lean;
+    cs->spare[11] += (long long)(uint32_t)sh->a_frames + sh->a_lean;
 #endif
+    if constexpr (kParts != kPartsNone) {
+      cs->parts_frames += (int)(sh->a_frames >> 32); cs->parts_given_up += (int)(sh->a_rounds >> 32);
+      sh->a_frames &= 0xFFFFFFFFull; sh->a_rounds &= 0xFFFFFFFFull;
+    }
     cs->frames += sh->a_frames + sh->a_lean;
     cs->active_tokens += sh->a_active + (sh->a_lean_pack[0] & 0xFFFFFFFFull);
     cs->emit_arcs += sh->a_emit + (sh->a_lean_pack[0] >> 32);

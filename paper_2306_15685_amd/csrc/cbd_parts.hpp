@@ -265,11 +265,11 @@ __device__ __forceinline__ void parts_closures(const AdvanceParams &p, Shared *s
 
 // A frame was begun by parts and given up (one thread).  Such a frame is decoded twice, and its like tend to follow: from
 // the third in a row on, 1, 2, 4 ... 64 frames go straight to the general code before one is tried again.
+// parts_state: how many are still to go (low 8 bits); failures in a row, 9 at most, << 8.
 __device__ __forceinline__ void parts_failed(Shared *sh) {
-  sh->a_parts_back += 1;
-  const int n = min(sh->parts_fails + 1, 9);
-  sh->parts_fails = n;
-  if (n >= 3) sh->parts_wait = 1 << (n - 3);
+  const int n = min((sh->parts_state >> 8) + 1, 9);
+  sh->parts_state = (n << 8) | (n >= 3 ? 1 << (n - 3) : 0);
+  sh->a_rounds += kPartsCount;
 }
 
 // One frame.  region: the LDS of the lean tables, p.part_slots * 12 bytes.  cost_in / cost_out: the current tokens'
@@ -297,14 +297,14 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   const int lists_cap = (int)((p.part_slots * 12 - NW * 64 * (int)sizeof(LiveToken)) / 16);
   const bool hist_on = p.max_active > 0 && p.beam > 0.0f && p.beam < __builtin_inff();
   const float inv = 256.0f / p.beam;
-  const int wait = __builtin_amdgcn_readfirstlane(sh->parts_wait);
+  const int state = __builtin_amdgcn_readfirstlane(sh->parts_state);
   if (tid < 16) { sh->wcount[tid] = 0; sh->wbase[tid] = 0; }
 #ifdef CBD_PROFILE
   if (tid == 0) sh->prof_last = wall_clock64();
 #endif
   __syncthreads();
-  if (__builtin_expect(wait > 0, 0)) {   // (uniform)
-    if (tid == 0) sh->parts_wait = wait - 1;
+  if (__builtin_expect((state & 0xFF) != 0, 0)) {   // (uniform)
+    if (tid == 0) sh->parts_state = state - 1;
     return kFrameRedo;
   }
 
@@ -768,12 +768,11 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       sh->frame_base = base_cur;
       sh->n_rec = base_cur + n_claim;
       sh->best = fbest;
-      atomicAdd(&sh->a_frames, 1ull);
+      atomicAdd(&sh->a_frames, kPartsCount + 1ull);
       atomicAdd(&sh->a_tokens, (unsigned long long)n_claim);
       atomicMax(&sh->a_maxtok, n_claim);
       atomicAdd(&sh->a_slow, 1);
-      atomicAdd(&sh->a_parts, 1);
-      sh->parts_fails = 0;
+      sh->parts_state = 0;
       atomicAdd(&sh->a_impr, (unsigned long long)n_claim);
       atomicAdd(&sh->a_rounds, (unsigned long long)sh->rounds);
     }
