@@ -130,8 +130,11 @@ typedef struct cbd_config {
                                  epsilon-input arcs (and in rounds over the change log): a closure that needs more,
                                  a legitimate acyclic chain that long included, parks the channel with
                                  CBD_E_EPS_DIVERGED; raise the limit for graphs with longer epsilon chains */
-  int32_t records_per_frame;  /* average back-pointer records per frame to reserve; 0 = table capacity / 2 */
-  int32_t table_location;     /* 0 or 1 = LDS tables, frames that outgrow them are redone in device memory;
+  int32_t records_per_frame;  /* average back-pointer records per frame to reserve; 0 = table capacity / 2.  A figure above
+                                 what the LDS tables hold also chooses the kernel of graphs with very long rows
+                                 (cbd_get_parts) */
+  int32_t table_location;     /* 0 or 1 = LDS tables, frames that outgrow them are redone by parts, one LDS table after
+                                 another (graphs with very long rows: cbd_get_parts), or in device memory;
                                  2 = device-memory tables only */
   int32_t lds_token_cap;      /* tokens per frame the LDS tables hold; 0 = as many as fit (a log-likelihood row of
                                  up to 1024 pdfs is kept in LDS beside them, a longer one is read from device memory) */
@@ -149,8 +152,9 @@ typedef struct cbd_config {
   int32_t block_threads;      /* threads per workgroup of the decoding kernel: 256, 512, 960 or 1024; 0 = chosen by
                                  the library from workgroups_per_cu (1024 / 512 / 256 for 1 / 2 / 4) */
   int32_t frame_code;         /* 0 = frames that qualify (tables in LDS, every closure met stored as a list with the
-                                 graph) are decoded by the lean frame code, the rest by the general code; 1 = general
-                                 code only.  Results are the same either way. */
+                                 graph) are decoded by the lean frame code, those that outgrow the tables by parts where
+                                 the decoder does that (cbd_get_parts), the rest by the general code; 1 = general code
+                                 only.  Results are the same either way. */
   int32_t workgroups_per_channel; /* 0 or 1 = one workgroup decodes a channel; 2, 4 or 8 = a team of that many
                                  shares it (for frames with far more tokens than one compute unit's LDS holds: the
                                  states are split over the team, candidates travel between members through device
@@ -335,7 +339,7 @@ typedef struct cbd_stats {
   int64_t emit_arcs;      /* emitting arcs expanded */
   int64_t eps_arcs;       /* epsilon-input arcs expanded (every relaxation round counts) */
   int64_t candidates;     /* candidates that passed the cutoff and reached the state table */
-  int64_t improvements;   /* table updates (change-log entries) */
+  int64_t improvements;   /* table updates (change-log entries; of a frame by the lean code or by parts: its tokens) */
   int64_t tokens;         /* sum over frames of the table size */
   int64_t eps_rounds;     /* per frame the longest run of closure levels any wave made, summed over frames */
   int64_t records;        /* back-pointer records in use */

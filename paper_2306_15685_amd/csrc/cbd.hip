@@ -938,9 +938,12 @@ int32_t cbd_decoder_create(const cbd_graph *g, const cbd_config *cfg, void *hip_
     if (d->lds_slots > (int32_t)cbd::LogT<true>::kSrcMask) {
       return fail(CBD_E_INVALID, "decoder: LDS table too large for the change log's slot field");
     }
-    // Frames that outgrow the LDS tables by parts, for graphs with long rows (cbd_parts.hpp says why only these): as few
-    // shares as hold a frame of g_tok_cap tokens at seven eighths of their slots (12 bytes each, in the LDS of the lean
-    // tables, which also stages live tokens, 16 bytes per thread).
+    // Frames that outgrow the LDS tables by parts, for graphs with long rows and all closures stored (cbd_parts.hpp says why
+    // only these): as few shares as hold a frame of g_tok_cap tokens at seven eighths of their slots (12 bytes each, in the
+    // LDS of the lean tables, which also stages live tokens, 16 bytes per thread).  Slots that long rows' destinations take
+    // from the start are not counted: the tokens of a large frame are mostly such destinations, and a frame that does not
+    // fit is decoded by the general code.  Eight shares of the largest tables, 11,700 slots, hold 2^17 / 2 tokens: a larger
+    // hash_capacity_log2 decodes all its outgrown frames by the general code.
     if (cfg->frame_code == 0 && cap > 0 && cfg->workgroups_per_channel <= 1 && g->unstored_closures == 0 && !g->long_rows.empty()) {
       const cbd::LdsLayout l = cbd::make_layout(d->stage_rows ? g->P : 0, d->ctx_lds_cap, cap, d->lds_slots, d->lds_log_cap, lean_entries);
       const int slots = (int)((l.total - l.hval) / 12) / 64 * 64;

@@ -1328,13 +1328,13 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
 // parts, kPartsFew in a kernel whose registers go to the lean and the general frames, kPartsMost in one that treats all
 // frames alike.  The two differ in nothing but speed (cbd_decoder_create chooses; us, kPartsNone / Few / Most):
 //   256 channels x 500 frames, all lean, results walked beside       5,805 / 5,820 / 6,930
-//   2,048 channels x 100 frames, all but 80 of 204,800 lean          8,810 / 9,000 / 9,660
+//   2,048 channels x 100 frames, all but 80 of 204,800 lean          8,810 / 8,975 / 9,670
 //   32 channels x 333 frames, all lean                               2,312 / 2,309 / 2,420
 //   150 channels x 60 frames of 2,000 words, general code in LDS     1,790 / 1,805 / 1,848
 //   148 channels x 40 frames of 5,600 words, all by parts            7,385 / 2,165 / 1,980
 //   160 channels x 40 frames of 20,000 words, all by parts          30,360 / 4,570 / 4,205
 // (The worst found: 160 channels on a graph whose long rows are met in most frames, 900 tokens each, general code in LDS,
-// results walked beside: 23,400 / 25,400 / 24,300.)
+// results walked beside: 23,450 / 25,500 / 24,400.)
 enum { kPartsNone = 0, kPartsFew = 1, kPartsMost = 2 };
 
 // kPartsFew: a frame by parts that has nothing in common with the code around it.  The kernel's parameters are read anew

@@ -16,11 +16,14 @@
 // What bounds it: vector instructions and L2 latency in turn (20,000 arcs of a hub are costed three times per frame
 // rather than stored and read back).  The table in device memory that it replaces took a chain of six dependent
 // device-memory accesses per candidate, most of them atomics: 160 channels x 40 frames of a 20,000-word lexicon loop
-// 30.3 -> 4.05 ms (755 -> 88 us per frame: 15 for reading and expanding tokens, 5 for the hub's minimum, 3 closure lists,
-// 11 to set the tables up, 19 recombination, 27 winners), 148 channels x 31 frames of 5,600 words 6.3 -> 1.9 ms.
-// Graphs without long rows keep the general code for the few frames that outgrow LDS: with this code beside the lean
-// frames in their kernel, the register allocator spills 25 instead of 6 vector registers and the lean frames take 3 to 6 %
-// longer, which is more than the frames that outgrow LDS are worth there (2,048 channels at beam 16: 10.24 -> 10.85 ms).
+// 31.0 -> 4.0 ms (kernel time per frame 755 -> 95 us; wave 0 stamps 15 for reading and expanding tokens, 5 for the hub's
+// minimum, 3 closure lists, 11 to set the tables up, 19 recombination, 27 winners, 80 together), 148 channels x 40 frames
+// of 5,600 words 7.4 -> 2.0 ms.
+// Who decodes so: cbd_decoder_create, from the graph and the sizes alone.  Graphs without long rows keep the general code
+// for the frames that outgrow LDS, which are too few there to tell (in the kernel of kPartsFew 2,048 channels at beam 16
+// take 9,840 to 10,140 us instead of 9,950 to 10,170, four other cases the same).  So do graphs with a state whose closure
+// is not stored as a list, were it only one: queued entries find their closure records by the degrees in an arc's record,
+// which such a state does not have.  A long row with an epsilon-input arc (a back-off) is such a state.
 // A frame that does not fit (a full queue or share) leaves nothing behind and is redone by the general code (parts_failed).
 #pragma once
 
