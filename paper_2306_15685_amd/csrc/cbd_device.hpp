@@ -110,12 +110,10 @@ struct __attribute__((aligned(128))) ChanState {
   long long lean_frames; // frames decoded by the lean code
   int32_t parts_frames;  // frames decoded by parts
   int32_t parts_given_up; // frames begun by parts and decoded by the general code
-  int32_t parts_state;   // how frames by parts have fared lately (parts_failed)
 #ifdef CBD_PROFILE
   long long spare[15];
 #else
-  int32_t spare0;
-  long long spare[13];
+  long long spare[14];
 #endif
 #ifdef CBD_PROFILE
   long long timeline[16];  // diagnostic build: the workgroup of the channel's last call with frames (start, end, ids)
@@ -220,7 +218,6 @@ struct Shared {
   uint32_t lean_best[2];      // lean frames, in turn: minimum over the closure candidates accepted
   int32_t a_maxtok, a_slow;   // counters of this call
   int32_t a_lean;             // frames decoded by the lean code
-  int32_t parts_state;        // as in ChanState
   unsigned long long a_lean_tokens;    // their tokens
   unsigned long long a_lean_pack[2];   // its counters, two to a word: active tokens | emitting arcs << 32,
                                        // epsilon-input arcs | candidates << 32
@@ -1334,7 +1331,7 @@ __device__ __forceinline__ void rows_to_device(const Mem<true> &M, const LeanMem
 //   148 channels x 40 frames of 5,600 words, all by parts            7,385 / 2,165 / 1,980
 //   160 channels x 40 frames of 20,000 words, all by parts          30,360 / 4,570 / 4,205
 // (The worst found: 160 channels on a graph whose long rows are met in most frames, 900 tokens each, general code in LDS,
-// results walked beside: 23,450 / 25,500 / 24,400.)
+// results walked beside: 23,450 / 24,430 / 24,300.)
 enum { kPartsNone = 0, kPartsFew = 1, kPartsMost = 2 };
 
 // kPartsFew: a frame by parts that has nothing in common with the code around it.  The kernel's parameters are read anew
@@ -1434,8 +1431,7 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
     sh->cut_bin = p.do_reset ? 255 : cs->cut_bin;
     sh->a_maxtok = 0; sh->a_slow = 0;
     if constexpr (kParts != kPartsNone) {
-      if (p.do_reset) { cs->parts_frames = 0; cs->parts_given_up = 0; cs->parts_state = 0; }
-      sh->parts_state = cs->parts_state;
+      if (p.do_reset) { cs->parts_frames = 0; cs->parts_given_up = 0; }
     }
     sh->a_frames = sh->a_active = sh->a_emit = sh->a_eps = sh->a_cand = sh->a_impr = sh->a_tokens = sh->a_rounds = 0;
   }
@@ -1625,7 +1621,6 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
       cs->lean_frames = 0;
     }
     cs->lean_frames += sh->a_lean;
-    if constexpr (kParts != kPartsNone) cs->parts_state = sh->parts_state;
 #ifdef CBD_PROFILE
     if (p.do_reset) for (int k = 0; k < 15; ++k) cs->spare[k] = 0;
     for (int k = 0; k < 7; ++k) cs->spare[k] += sh->prof[k];

@@ -24,7 +24,9 @@
 // take 9,840 to 10,140 us instead of 9,950 to 10,170, four other cases the same).  So do graphs with a state whose closure
 // is not stored as a list, were it only one: queued entries find their closure records by the degrees in an arc's record,
 // which such a state does not have.  A long row with an epsilon-input arc (a back-off) is such a state.
-// A frame that does not fit (a full queue or share) leaves nothing behind and is redone by the general code (parts_failed).
+// A frame that does not fit (a full queue or share) leaves nothing behind and is redone by the general code, each time: to let
+// such frames go there at once would refuse some that fit, since its change log counts the arcs of long rows and the queues do
+// not (a second try in the frame loop behind it spilled 43 to 70 registers).
 #pragma once
 
 namespace cbd {
@@ -266,15 +268,6 @@ __device__ __forceinline__ void parts_closures(const AdvanceParams &p, Shared *s
   }
 }
 
-// A frame was begun by parts and given up (one thread).  Such a frame is decoded twice, and its like tend to follow: from
-// the third in a row on, 1, 2, 4 ... 64 frames go straight to the general code before one is tried again.
-// parts_state: how many are still to go (low 8 bits); failures in a row, 9 at most, << 8.
-__device__ __forceinline__ void parts_failed(Shared *sh) {
-  const int n = min((sh->parts_state >> 8) + 1, 9);
-  sh->parts_state = (n << 8) | (n >= 3 ? 1 << (n - 3) : 0);
-  sh->a_rounds += kPartsCount;
-}
-
 // One frame.  region: the LDS of the lean tables, p.part_slots * 12 bytes.  cost_in / cost_out: the current tokens'
 // costs and where the new ones go (apart, so that a frame can be given up at any point).  Returns kFrameOk,
 // kFrameNoTokens, kFrameOverflow, kFrameRecordsFull, or kFrameRedo (the general code decodes the frame).
@@ -300,16 +293,11 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   const int lists_cap = (int)((p.part_slots * 12 - NW * 64 * (int)sizeof(LiveToken)) / 16);
   const bool hist_on = p.max_active > 0 && p.beam > 0.0f && p.beam < __builtin_inff();
   const float inv = 256.0f / p.beam;
-  const int state = __builtin_amdgcn_readfirstlane(sh->parts_state);
   if (tid < 16) { sh->wcount[tid] = 0; sh->wbase[tid] = 0; }
 #ifdef CBD_PROFILE
   if (tid == 0) sh->prof_last = wall_clock64();
 #endif
   __syncthreads();
-  if (__builtin_expect((state & 0xFF) != 0, 0)) {   // (uniform)
-    if (tid == 0) sh->parts_state = state - 1;
-    return kFrameRedo;
-  }
 
   // ---- 1: prune and expand
   uint32_t n_active = 0, n_emit = 0, n_eps = 0, n_cand = 0;
@@ -528,7 +516,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
   }
   __syncthreads();
   if (__builtin_expect(sh->fault, 0)) {   // (uniform: set in steps 1 and 2 only) a queue is full
-    if (tid == 0) parts_failed(sh);
+    if (tid == 0) sh->a_rounds += kPartsCount;
     return kFrameRedo;
   }
   CBD_STAMP(2);   // (diagnostic: closure lists)
@@ -639,7 +627,7 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
     });
     __syncthreads();
     if (__builtin_expect(sh->redo, 0)) {   // (uniform: set between this barrier and the one before) the share's table is full
-      if (tid == 0) parts_failed(sh);
+      if (tid == 0) sh->a_rounds += kPartsCount;
       return kFrameRedo;
     }
     CBD_STAMP(4);   // (diagnostic: shares recombined)
@@ -775,7 +763,6 @@ __device__ __forceinline__ int run_frame_parts(const AdvanceParams &p, unsigned 
       atomicAdd(&sh->a_tokens, (unsigned long long)n_claim);
       atomicMax(&sh->a_maxtok, n_claim);
       atomicAdd(&sh->a_slow, 1);
-      sh->parts_state = 0;
       atomicAdd(&sh->a_impr, (unsigned long long)n_claim);
       atomicAdd(&sh->a_rounds, (unsigned long long)sh->rounds);
     }

@@ -128,19 +128,6 @@ def test_one_row_too_long_to_lay_out(torch_cuda):  # noqa: F811
     assert s["parts"]["shares"] == 2 and s["parts"]["frames"] > 0 and extra > 4 * 2 * 2_880
 
 
-@pytest.mark.parametrize("chunks", [[40], [1] * 40])
-def test_frames_that_keep_failing(torch_cuda, chunks):  # noqa: F811
-    """When frames are given up one after another, most of the following ones are not begun by parts any more, also from
-    call to call."""
-    g = hub_graph(300, 40, 2, 600, seed=9)
-    L, ctxs, offs = inputs(torch_cuda, g, 2, 40, 1.0, 9, arcs=30)
-    s = run_batch(torch_cuda, g, L, ctxs, np.abs(offs), beam=6.5, max_active=0, chunks=chunks, hash_log2=10, lds_token_cap=64)
-    print("failing", s["parts"], s["slow_frames"], flush=True)
-    assert s["status"] == 0 and s["slow_frames"] > 60
-    # (40 frames of a channel that all fail: 3 tries, then one after 1, 2, 4, 8 and 16 frames)
-    assert 0 < s["parts"]["given_up"] <= s["slow_frames"] // 3
-
-
 @pytest.mark.parametrize("words,shares", [(600, 8), (6_000, 2)])
 def test_lexicon_loop(torch_cuda, words, shares):  # noqa: F811
     """LDS tables of 256 tokens, and as large as LDS allows: eight shares of 3,500 slots and two of 11,700 for 16,384 tokens."""
