@@ -196,6 +196,7 @@ constexpr int kBigRowArcs = 512;  // a row with more arcs than this is shared ou
 // Workgroup-shared scalars.
 struct Shared {
   uint32_t m_ord;      // running minimum of emitting candidates (orderable bits)
+  int32_t redo;        // lean frame: something ahead of the first barrier needs the general code (the frame is redone there)
   uint32_t best_ord;   // minimum over all accepted candidates of the frame
   unsigned long long log_claim;  // low 32 bits: change-log entries; high 32 bits: states in the table (= tokens)
   int32_t n_front[2];  // log entries of the last / the running phase whose state has epsilon-input arcs
@@ -211,10 +212,8 @@ struct Shared {
   float big_cost[kBigRows];
   uint32_t big_src[kBigRows];
   int32_t n_done;             // lean frame: waves through with the look-up phase
-  int32_t redo, redo_b;       // lean frame: something this frame needs the general code (the frame is redone there);
-                              // set before the first / between the first and the second barrier of the frame
-  int32_t wcount[16];         // lean frame: states each wave created; wbase: the same as exclusive prefix sums
-  int32_t wbase[16];
+  int32_t wcount[16];         // lean frame: states each wave created (kLeanRedoCount: it gave the frame up)
+  int32_t wbase[16];          // frames by parts: counters
   uint32_t lean_best[2];      // lean frames, in turn: minimum over the closure candidates accepted
   int32_t a_maxtok, a_slow;   // counters of this call
   int32_t a_lean;             // frames decoded by the lean code
@@ -327,6 +326,17 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return s;
 }
 
+// The same within each row of 16 lanes.
+__device__ __forceinline__ int row_incl_scan(int v) {
+  int s = v;
+  s += dpp_step<kRowShr1, 0xf, 0xf>(0, v);
+  s += dpp_step<kRowShr2, 0xf, 0xf>(0, v);
+  s += dpp_step<kRowShr3, 0xf, 0xf>(0, v);
+  s += dpp_step<kRowShr4, 0xf, 0xe>(0, s);
+  s += dpp_step<kRowShr8, 0xf, 0xc>(0, s);
+  return s;
+}
+
 // Inclusive running maximum over the 64 lanes (values >= 0), same ladder.  The arithmetic is unsigned: 0 is then
 // the maximum's identity, and a lane a step does not reach keeps its value in one instruction.
 __device__ __forceinline__ int wave_incl_scan_max(int v) {
@@ -425,45 +435,6 @@ __device__ __forceinline__ bool ctx_contains(const Ctx &cx, int32_t a) {
   }
   if (cx.in_lds) return sorted_contains(cx.lds_list, cx.n, a);
   return sorted_contains(cx.g_list, cx.n, a);
-}
-
-// The same test for up to two arcs per lane, by a whole wave.  in: what this lane wants tested; out: what is listed.
-// second: some lane has a second arc (uniform).  A wave waits for LDS once per step for both arcs, and the number of
-// steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with no lanes
-// dropping out.  (One arc after the other with a search that ends per lane: a wave waited twice per step and for the
-// arc records before its second test.  32 channels x 333 frames behind the plain search 2.414 -> 2.393 ms, 8 channels
-// x 1,000 frames 8.59 -> 8.50, where runs differ by 0.3 %; 2,048 channels with 1,000-arc lists behind the filter within
-// the spread.  Waves without arcs take the steps too: leaving before them on a ballot costs 32 channels 0.8 % and 1 to
-// 100 channels 0.5 %.)
-__device__ __forceinline__ void ctx_contains_pair(const Ctx &cx, const int (&a)[2], bool second, bool (&in)[2]) {
-  if (cx.n == 0) { in[0] = in[1] = false; return; }
-  if (cx.use_bitmap) {
-    const uint32_t h0 = bloom_hash(a[0]), h1 = bloom_hash(a[1]);
-    const uint32_t m0 = bloom_mask(h0), m1 = bloom_mask(h1);
-    const uint32_t w0 = cx.bitmap[bloom_word(h0)], w1 = second ? cx.bitmap[bloom_word(h1)] : 0u;
-    in[0] = in[0] && (w0 & m0) == m0;
-    in[1] = in[1] && (w1 & m1) == m1;
-    if (__ballot(in[0] || in[1]) == 0) return;   // uniform
-  }
-  if (!cx.in_lds) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) if (in[q]) in[q] = sorted_contains(cx.g_list, cx.n, a[q]);
-    return;
-  }
-  // the last entry <= a lies in [b, b + len), if there is one
-  int b0 = 0, b1 = 0;
-  for (int len = __builtin_amdgcn_readfirstlane(cx.n); len > 1;) {
-    const int half = len >> 1;
-    const int v0 = cx.lds_list[b0 + half];
-    if (second) {
-      const int v1 = cx.lds_list[b1 + half];
-      b1 = v1 <= a[1] ? b1 + half : b1;
-    }
-    b0 = v0 <= a[0] ? b0 + half : b0;
-    len -= half;
-  }
-  in[0] = in[0] && cx.lds_list[b0] == a[0];
-  in[1] = in[1] && cx.lds_list[b1] == a[1];
 }
 
 // A token's arc row as another wave of the workgroup stored it to device memory: read past the L1.
@@ -944,7 +915,7 @@ __device__ __forceinline__ void frame_init(Shared *sh, uint32_t *hist, bool star
     sh->best_ord = 0xFFFFFFFFu;   // minimum over closure candidates; the table's minimum is min(m, this)
     sh->lean_best[0] = sh->lean_best[1] = 0xFFFFFFFFu;
     sh->log_claim = 0; sh->n_front[0] = 0; sh->n_front[1] = 0; sh->n_surv = 0; sh->n_live = 0; sh->rounds = 0;
-    sh->fault = 0; sh->diverged = 0; sh->halt = 0; sh->n_big = 0; sh->redo = 0; sh->redo_b = 0; sh->n_done = 0;
+    sh->fault = 0; sh->diverged = 0; sh->halt = 0; sh->n_big = 0; sh->redo = 0; sh->n_done = 0;
   }
 }
 
@@ -1391,9 +1362,10 @@ __device__ __forceinline__ void advance_channel(const AdvanceParams &p, const in
   // (The offsets are kept in vector registers, of which there are some to spare, though every lane holds the same: as
   // scalars they are ten of some 120 values too many for the scalar registers, and each use begins with reading one back
   // from a vector register's lane.  With that and here_tid(): 32 channels x 333 frames 2.30 -> 2.27 ms, 256 streams
-  // 6.38 -> 6.20, 2,048 channels 10.2 -> 9.9.)
+  // 6.38 -> 6.20, 2,048 channels 10.2 -> 9.9; with lean frames in a loop of their own still 1 to 4 %.  In kernels with frames by
+  // parts there are none to spare.)
   uint32_t o_hval = lay.hval, o_hkey = lay.hkey, o_hidx = lay.hidx, o_tcost = lay.tcost, o_log = lay.log;
-  asm volatile("" : "+v"(o_hval), "+v"(o_hkey), "+v"(o_hidx), "+v"(o_tcost), "+v"(o_log));
+  if constexpr (kParts == kPartsNone) asm volatile("" : "+v"(o_hval), "+v"(o_hkey), "+v"(o_hidx), "+v"(o_tcost), "+v"(o_log));
   ML.hval = (uint64_t *)(smem + o_hval);
   ML.hkey = (uint32_t *)(smem + o_hkey);
   ML.hidx = (uint16_t *)(smem + o_hidx);

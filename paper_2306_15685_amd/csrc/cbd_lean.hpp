@@ -17,9 +17,15 @@
 //     token and its back-pointer record); token indices are wave-local ordinals, made dense by a prefix sum
 //     over the waves' counts.
 // Whatever does not fit (a tile with more than 256 arcs, a hub row, a closure without stored list, a full table
-// or log) sets Shared::redo (before the first barrier) or Shared::redo_b (between the barriers); each is read by
-// all waves after the barrier that follows, and the frame is then decoded again by run_frame(), which handles
-// everything.
+// or log) sets Shared::redo (before the first barrier) or the wave's count in Shared::wcount to more than any table holds
+// (between the barriers); each is read by all waves after the barrier that follows, and the frame is then decoded again by
+// run_frame(), which handles everything.
+// What bounds it: of four waves on a SIMD, all in the same phase, the instructions, and between them the chain of dependent
+// LDS and device-memory reads.  So a wave goes through straight-line code for the 64 or 128 arcs it has (one or two slots per
+// lane), and what lanes do is kept in lane masks.  Against the same steps with a flag per lane, an owner search by running
+// maximum and shuffles for the emitting arcs, and one code for one and two slots (us): one channel x 100 frames 656 -> 562,
+// 32 x 333 2,120 -> 1,792, 100 x 151 1,352 -> 1,211, 256 x 500 6,028 -> 5,625, 512 x 400 7,793 -> 7,187, 2,048 x 100 9,932 ->
+// 9,048.
 #pragma once
 
 namespace cbd {
@@ -56,13 +62,13 @@ struct LeanMem {
   int32_t *t_first;    // [tok_cap] first emitting arc of each current token's state
   uint16_t *t_deg;     // [tok_cap] number of emitting arcs
   int32_t *hrow;       // [slots] the same for the states in the table, written by whoever creates the entry
-  uint8_t *hed;        // [slots]  (kLeanEdEscape: the row is too long for the lean code)
+  uint8_t *hed;        // [slots]  (kEdEscape: the row is too long for the lean code)
   LeanLog *clog;       // [waves][kLeanLogPerWave]
 };
-constexpr uint8_t kLeanEdEscape = 0xFF;
 
 constexpr int kLeanLogPerWave = 256;   // commits a wave can log per frame (more: the frame goes to the general code)
 constexpr int kLeanLogEntryBytes = 8;
+constexpr int kLeanRedoCount = 1 << 24;   // Shared::wcount of a wave that gave the frame up
 
 __device__ __forceinline__ LeanMem make_lean_mem(void *log_region, int tok_cap, int slots) {
   LeanMem R;
@@ -76,6 +82,20 @@ __device__ __forceinline__ LeanMem make_lean_mem(void *log_region, int tok_cap, 
   R.clog = (LeanLog *)b;
   return R;
 }
+
+// Lane masks.  Which lanes of a wave do something is kept as 64 bits in a scalar register pair from one step to the next:
+// a mask becomes a lane's condition and a count of the lanes below in one or two instructions, where a flag per lane would
+// be moved through a vector register and compared again at every branch.
+__device__ __forceinline__ uint64_t lanes_with(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// base + the number of lanes of m below this one
+__device__ __forceinline__ int rank_in(uint64_t m, int base) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+__device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
+__device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(from_lane(__float_as_int(v), lane)); }
+// a register of which no one reads what it holds
+__device__ __forceinline__ uint32_t any_value() { uint32_t x; asm volatile("" : "=v"(x)); return x; }
 
 // table slot of a state: home slot first, then linear probing (same function as table_min)
 __device__ __forceinline__ uint32_t lean_home(uint32_t state, uint32_t slots) {
@@ -100,114 +120,222 @@ struct LeanTile {
   int total;      // arcs in the list (uniform)
 };
 
-// Loads tile `st` of this wave (tokens tile0 + st * 64 + lane, below tile_end), prunes (step 1), and writes the
-// heads of its arc list into omap: the owner of a list position is the last head at or before it.
+// What the lanes of an arc list need to know about the token that owns their position, by the tokens' ranks among those
+// with arcs.  In the emit phase it lies where the wave's commit log is in the rest of the frame.
+struct __attribute__((aligned(16))) LeanOwner {
+  int rel;
+  float cost;
+  uint32_t from;   // LeanLog::from in the upper half
+  uint32_t unused;
+};
+static_assert(64 * sizeof(LeanOwner) <= kLeanLogPerWave * sizeof(LeanLog), "a tile's owners fit the wave's log");
+
+// Loads the tile of tokens base + lane, below tile_end (base < tile_end), prunes (step 1), and writes the heads of its arc list
+// into omap (the owner of a list position is the last head at or before it) and, if kOwners, the owners by rank.
+template <bool kOwners>
 __device__ __forceinline__ LeanTile lean_load_tile(const AdvanceParams &p, const Mem<true> &M, const LeanMem &R,
-                                                   Shared *sh, uint8_t *omap, int tile0, int tile_end, int st, int lane,
-                                                   float best, int cut, float inv, uint32_t &n_active) {
+                                                   Shared *sh, uint8_t *omap, LeanOwner *owners, int base, int tile_end,
+                                                   int lane, float best, int cut, float inv, int &n_active) {
   LeanTile T;
-  T.base = tile0 + st * 64;
-  const int i = T.base + lane;
-  bool alive = false;
-  T.cost = 0.0f;
-  int first = 0, deg = 0;
-  if (i < tile_end) {
-    // (all three are asked for together: 32 channels x 333 frames 0.7 % faster than the row behind the test)
-    T.cost = M.t_cost[i];
-    const int first_i = R.t_first[i], deg_i = (int)R.t_deg[i];
-    const float r = T.cost - best;
-    alive = !(r > p.beam) && T.cost < __builtin_inff();
-    if (alive && cut < 255) {
-      int bin = (int)floorf(r * inv);
-      bin = bin > 255 ? 255 : bin;
-      alive = bin <= cut;
-    }
-    if (alive) { first = first_i; deg = deg_i; }
+  T.base = base;
+  // (lanes beyond the last token look at that one: no branch, so what is asked of it stays in lane masks)
+  const int i = min(base + lane, tile_end - 1);
+  T.cost = M.t_cost[i];
+  const int first = R.t_first[i];
+  int deg = (int)R.t_deg[i];
+  const float r = T.cost - best;
+  uint64_t alive = lanes_with(base + lane < tile_end) & lanes_with(!(r > p.beam)) & lanes_with(T.cost < __builtin_inff());
+  if (cut < 255) {   // uniform
+    int bin = (int)floorf(r * inv);
+    bin = bin > 255 ? 255 : bin;
+    alive &= lanes_with(bin <= cut);
   }
-  if (deg == (int)kLeanDegEscape) { sh->redo = 1; deg = 0; CBD_WHY(3); }
+  deg = lane_in(alive) ? deg : 0;
   const int incl = wave_incl_scan(deg);
   const int pos = incl - deg;
   T.total = __builtin_amdgcn_readlane(incl, 63);
-  if (T.total > kOwnerMap) { if (lane == 0) { sh->redo = 1; CBD_WHY(3); } T.total = 0; }
-  ((uint32_t *)omap)[lane] = 0;
-  if (deg > 0 && pos < kOwnerMap) omap[pos] = (uint8_t)(lane + 1);
   T.rel = first - pos;
-  n_active += (uint32_t)__popcll(__ballot(alive));
+  n_active += __popcll(alive);
+  if (T.total > kOwnerMap) {   // uniform (a row too long for the count field, kLeanDegEscape, is one such)
+    if (lane == 0) { sh->redo = 1; CBD_WHY(3); }
+    T.total = 0;
+    return T;
+  }
+  ((uint32_t *)omap)[lane] = 0;
+  const uint64_t heads = lanes_with(deg > 0);
+  if (lane_in(heads)) {
+    omap[pos] = (uint8_t)(lane + 1);
+    if (kOwners) {
+      LeanOwner o;
+      o.rel = T.rel; o.cost = T.cost; o.from = (uint32_t)(i | kLeanFromToken) << 16; o.unused = 0;
+      owners[rank_in(heads, 0)] = o;
+    }
+  }
   return T;
 }
 
-// One emitting candidate per lane and slot: two slots, list positions jb + lane and jb + 64 + lane.
+// Emitting candidates, one per lane and slot: list positions jb + lane and (second slot) jb + 64 + lane.
 struct LeanEmit {
   float cand[2];
   int arc[2];
   ArcRec rec[2];
-  int src[2];      // token (index in the previous frame's list) the arc leaves from
-  bool act[2];
+  uint32_t from[2];   // LeanLog::from in the upper half
+  uint64_t act[2];    // the lanes that hold one (uniform)
 };
 
-// Candidates of list positions [jb, jb + 128) of tile T (jb a multiple of 128).  Returns the minimum (orderable
-// bits) over the candidates computed.
-template <bool kRowFromLds>
-__device__ __forceinline__ uint32_t lean_candidates(const AdvanceParams &p, const Ctx &cx, const Rows &Lrow,
-                                                    const uint8_t *omap, int jb, int lane, const LeanTile &T,
-                                                    LeanEmit &E) {
+// Which of the arcs a[] are listed, for lanes in act[] (lane masks; uniform).  A wave waits for LDS once per step for both
+// slots, and the number of steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with
+// no lanes dropping out.  (One arc after the other with a search that ends per lane: a wave waited twice per step and for the
+// arc records before its second test.  32 channels x 333 frames behind the plain search 2.414 -> 2.393 ms, 8 channels x 1,000
+// frames 8.59 -> 8.50, where runs differ by 0.3 %; 2,048 channels with 1,000-arc lists behind the filter within the spread.)
+template <int kSlots>
+__device__ __forceinline__ void lean_listed(const Ctx &cx, const int (&a)[2], const uint64_t (&act)[2], uint64_t (&in)[2]) {
+  uint64_t any = 0;
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) in[q] = 0;
+  if (cx.n == 0) return;
+  if (cx.use_bitmap) {
+    uint32_t w[kSlots], m[kSlots];
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      const uint32_t h = bloom_hash(a[q]);
+      m[q] = bloom_mask(h);
+      w[q] = cx.bitmap[bloom_word(h)];
+    }
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) { in[q] = act[q] & lanes_with((w[q] & m[q]) == m[q]); any |= in[q]; }
+    if (any == 0) return;
+  } else {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) in[q] = act[q];
+  }
+  if (!cx.in_lds) {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      bool is = false;
+      if (lane_in(in[q])) is = sorted_contains(cx.g_list, cx.n, a[q]);
+      in[q] = lanes_with(is);
+    }
+    return;
+  }
+  // the last entry <= a lies in [b, b + len), if there is one
+  int b[kSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) b[q] = 0;
+  for (int len = __builtin_amdgcn_readfirstlane(cx.n); len > 1;) {
+    const int half = len >> 1;
+    int v[kSlots];
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) v[q] = cx.lds_list[b[q] + half];
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) b[q] = v[q] <= a[q] ? b[q] + half : b[q];
+    len -= half;
+  }
+  int v[kSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) v[q] = cx.lds_list[b[q]];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) in[q] &= lanes_with(v[q] == a[q]);
+}
+
+// Costs of the candidates whose arcs and tokens' costs are known.  The records of both slots are asked for before either is
+// used, and so are their scores: every lane asks, those beyond the list for what the last arc needs, so that no branch makes
+// the first slot's score wait before the second's is asked for, as a condition per lane did.
+template <int kSlots, bool kRowFromLds>
+__device__ __forceinline__ uint32_t lean_costs(const AdvanceParams &p, const Ctx &cx, const Rows &Lrow, const float *own_cost,
+                                               LeanEmit &E) {
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) E.rec[q] = p.arcs[E.arc[q]];
+  // the bias test needs the arcs' numbers only: it runs while the records are on their way
+  uint64_t listed[2];
+  lean_listed<kSlots>(cx, E.arc, E.act, listed);
+  float ll[kSlots];
+  if (kRowFromLds && Lrow.staged) {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) ll[q] = Lrow.lds[(E.rec[q].meta & 0xFFFFu) - 1u];
+  } else {
+    const char *row = (const char *)(Lrow.glob - 1);
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) ll[q] = *(const float *)(row + ((E.rec[q].meta & 0xFFFFu) << 2));
+  }
   uint32_t lmin = 0xFFFFFFFFu;
-  // owner + 1 of the last position before jb
-  int carry = 0;
-  for (int b = 0; b < jb; b += 64) {   // (uniform; only beyond the first 128 arcs of a tile)
-    const int t = __builtin_amdgcn_readlane(wave_incl_scan_max((int)omap[b + lane]), 63);
-    carry = t > carry ? t : carry;
-  }
-  // both slots' arc records are asked for before either is used (one wait for both)
-  float c_own[2] = {0.0f, 0.0f};
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int j0 = jb + q * 64, j = j0 + lane;
-    E.act[q] = j < T.total;
-    E.cand[q] = 0.0f; E.arc[q] = 0; E.src[q] = 0;
-    E.rec[q].dst = 0; E.rec[q].weight = 0.0f; E.rec[q].row = 0; E.rec[q].meta = 0;
-    if (j0 < T.total) {   // uniform
-      // the lane that owns position j: the last head at or before j (heads carry lane + 1)
-      int own1 = wave_incl_scan_max((int)omap[j]);
-      own1 = own1 > carry ? own1 : carry;
-      carry = __builtin_amdgcn_readlane(own1, 63);
-      const int owner = own1 - 1;
-      E.arc[q] = __shfl(T.rel, owner, 64) + j;
-      c_own[q] = __shfl(T.cost, owner, 64);
-      E.src[q] = T.base + owner;
-      if (E.act[q]) E.rec[q] = p.arcs[E.arc[q]];
-    }
-  }
-  // the bias test needs the arc's number only: it runs while the records are on their way
-  const bool second = jb + 64 < T.total;   // uniform
-  bool listed[2] = {E.act[0], E.act[1]};
-  ctx_contains_pair(cx, E.arc, second, listed);
-  // both slots' scores are asked for before either is used
-  float ll[2] = {0.0f, 0.0f};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    if (E.act[q]) {
-      const uint32_t pdf = (E.rec[q].meta & 0xFFFFu) - 1u;
-      ll[q] = kRowFromLds ? Lrow.at(pdf) : Lrow.glob[pdf];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < kSlots; ++q) {
     float w = E.rec[q].weight;
-    w = listed[q] ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
-    E.cand[q] = (c_own[q] + w) - ll[q];
-    const uint32_t o = E.act[q] ? f2ord(E.cand[q]) : 0xFFFFFFFFu;
-    lmin = o < lmin ? o : lmin;
+    w = lane_in(listed[q]) ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
+    E.cand[q] = (own_cost[q] + w) - ll[q];
+    lmin = umin32(lmin, f2ord(E.cand[q]));   // (lanes beyond the list: the last arc's once more)
   }
   return lmin;
 }
 
-// Per-wave running state of the commit phase.
+// Emit phase: candidates of list positions [jb, jb + 64 kSlots) of tile T (T.total > jb).  heads: number of rows that begin
+// before jb.  Returns the minimum (orderable bits) over the candidates computed.
+template <int kSlots>
+__device__ __forceinline__ uint32_t lean_candidates(const AdvanceParams &p, const Ctx &cx, const Rows &Lrow,
+                                                    const uint8_t *omap, const LeanOwner *owners, int jb, int heads, int lane,
+                                                    const LeanTile &T, LeanEmit &E) {
+  uint32_t head[kSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) head[q] = omap[jb + q * 64 + lane];
+  LeanOwner o[kSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) {
+    const uint64_t hm = lanes_with(head[q] != 0);
+    o[q] = owners[rank_in(hm >> 1, heads + (int)(hm & 1) - 1)];   // the last head at or before this lane
+    heads += __popcll(hm);
+  }
+  float own_cost[kSlots];
+  E.act[0] = E.act[1] = 0;
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) {
+    const int j = jb + q * 64 + lane;
+    E.act[q] = lanes_with(j < T.total);
+    E.arc[q] = o[q].rel + min(j, T.total - 1);
+    own_cost[q] = o[q].cost;
+    E.from[q] = o[q].from;
+  }
+  return lean_costs<kSlots, true>(p, cx, Lrow, own_cost, E);
+}
+// The number of rows of the tile in omap that begin before position jb (a multiple of 64; uniform).
+__device__ __forceinline__ int lean_heads_before(const uint8_t *omap, int jb, int lane) {
+  int n = 0;
+  for (int b = 0; b < jb; b += 64) n += __popcll(lanes_with(omap[b + lane] != 0));
+  return n;
+}
+
+// The same again after the first barrier (the commit log is in use by then: a position's owner is found by a running maximum
+// over the heads, and what it has comes from its lane), both slots.
+__device__ __forceinline__ void lean_candidates_again(const AdvanceParams &p, const Ctx &cx, const Rows &Lrow, const uint8_t *omap,
+                                                      int jb, int lane, const LeanTile &T, LeanEmit &E) {
+  int carry = 0;   // owner + 1 of the last position before jb
+  for (int b = 0; b < jb; b += 64) {   // (uniform)
+    const int t = __builtin_amdgcn_readlane(wave_incl_scan_max((int)omap[b + lane]), 63);
+    carry = t > carry ? t : carry;
+  }
+  float own_cost[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int j = jb + q * 64 + lane;
+    int own1 = wave_incl_scan_max((int)omap[j]);
+    own1 = own1 > carry ? own1 : carry;
+    carry = __builtin_amdgcn_readlane(own1, 63);
+    const int owner = own1 - 1;
+    E.act[q] = lanes_with(j < T.total);
+    E.arc[q] = from_lane(T.rel, owner) + min(j, T.total - 1);
+    own_cost[q] = from_lane(T.cost, owner);
+    E.from[q] = (uint32_t)((T.base + owner) | kLeanFromToken) << 16;
+  }
+  lean_costs<2, false>(p, cx, Lrow, own_cost, E);
+}
+
+// Per-wave running state of the commit phase (all uniform).
 struct LeanWave {
-  int n_claimed;     // states this wave created so far (uniform)
-  int n_clog;        // commits it logged (uniform)
-  uint32_t n_cand, n_eps;
+  int claimed;       // wave << kLeanLidBits | states this wave created so far
+  int n_clog;        // commits it logged
+  int n_cand, n_eps;
   int max_depth;
+  bool redo;         // it met something this code cannot take
 };
 
 // Copies a log-likelihood row from device memory into LDS without passing through registers: every wave asks for
@@ -234,204 +362,179 @@ __device__ __forceinline__ void stage_row_async(float *lds_row, const float *row
   }
 }
 
-// Asks for the table slot of `state` for lanes with ok set: h, and k = what the slot held before (kEmptyKey: this
-// lane created the entry).
-__device__ __forceinline__ void lean_slot(const Mem<true> &M, bool ok, uint32_t state, uint32_t &h, uint32_t &k) {
-  k = 0; h = 0;
-  if (ok) {
-    h = lean_home(state, M.slots);
-    k = atomicCAS(&M.hkey[h], kEmptyKey, state);
-  }
+// Asks for the table slot of `state` for lanes in ok: h, and k = what the slot held before (kEmptyKey: this
+// lane created the entry).  Other lanes' h and k mean nothing.
+__device__ __forceinline__ void lean_slot(const Mem<true> &M, uint64_t ok, uint32_t state, uint32_t &h, uint32_t &k) {
+  h = lean_home(state, M.slots);
+  k = any_value();
+  if (lane_in(ok)) k = atomicCAS(&M.hkey[h], kEmptyKey, state);
 }
-// After a collision at the home slot: walks on.  Clears ok and sets sh->redo_b if the table is full.
-__device__ __forceinline__ void lean_slot_collisions(const Mem<true> &M, Shared *sh, bool &ok, uint32_t state,
-                                                     uint32_t &h, uint32_t &k) {
-  const bool collided = ok && k != kEmptyKey && k != state;
-  if (__ballot(collided) != 0) {   // rare
-    if (collided && !lean_probe(M, state, h, k)) { sh->redo_b = 1; ok = false; CBD_WHY(3); }
+// After a collision at the home slot: walks on.  A table without room sets W.redo.
+__device__ __forceinline__ void lean_slot_collisions(const Mem<true> &M, Shared *sh, uint64_t &ok, uint32_t state,
+                                                     uint32_t &h, uint32_t &k, LeanWave &W) {
+  const uint64_t collided = ok & lanes_with(k != kEmptyKey) & lanes_with(k != state);
+  if (collided != 0) {   // rare
+    bool full = false;
+    if (lane_in(collided)) full = !lean_probe(M, state, h, k);
+    const uint64_t f = lanes_with(full);
+    if (f != 0) { ok &= ~f; W.redo = true; if (lane_in(1ull)) CBD_WHY(3); }
   }
 }
 
-// E[state] = min key for lanes with ok set (slot h, previous holder k from lean_slot), the token's wave-local id
-// and the state's row if the lane created the entry, and the log entry for the look-up after the barrier.
-// Returns whether this lane created the entry.
-__device__ __forceinline__ bool lean_min_and_log(const Mem<true> &M, const LeanMem &R, Shared *sh, bool ok, uint32_t h,
-                                                 uint32_t k, uint64_t key, const ArcRec &rec, uint32_t from, int wave,
-                                                 int lane, LeanWave &W) {
-  if (ok) atomicMin((unsigned long long *)&M.hval[h], (unsigned long long)key);
-  const bool claimed = ok && k == kEmptyKey;
-  const unsigned long long om = __ballot(ok);
-  const unsigned long long cm = __ballot(claimed);
-  const unsigned long long below = (1ull << lane) - 1ull;
-  if (claimed) {
+// E[state] = min key for lanes in ok (slot h, previous holder k from lean_slot), the token's wave-local id and the state's
+// row if the lane created the entry, and the log entry for the look-up after the barrier.
+__device__ __forceinline__ void lean_min_and_log(const Mem<true> &M, const LeanMem &R, Shared *sh, uint64_t ok, uint32_t h,
+                                                 uint32_t k, uint32_t cost_ord, uint32_t arc, const ArcRec &rec, uint32_t from,
+                                                 LeanLog *clog, LeanWave &W) {
+  const int n_ok = __popcll(ok);
+  if (W.n_clog + n_ok > kLeanLogPerWave) {   // uniform
+    W.redo = true;
+    if (lane_in(1ull)) CBD_WHY(1);
+    return;
+  }
+  const uint64_t claimed = ok & lanes_with(k == kEmptyKey);
+  if (lane_in(ok)) {
+    atomicMin((unsigned long long *)&M.hval[h], ((unsigned long long)cost_ord << 32) | arc);
+    *(uint2 *)&clog[rank_in(ok, W.n_clog)] = make_uint2(arc, h | from);   // LeanLog
+  }
+  if (lane_in(claimed)) {
     // this lane created the state's entry: it names the token (wave-local id, made dense after the barrier) and
     // files the state's row, which the next frame expands
-    const int ord = W.n_claimed + __popcll(cm & below);
-    if (ord <= kLeanLidMask) M.hidx[h] = (uint16_t)((wave << kLeanLidBits) | ord);
-    else { sh->redo_b = 1; CBD_WHY(3); }
-    const uint32_t ed = meta_ed(rec.meta);
+    M.hidx[h] = (uint16_t)rank_in(claimed, W.claimed);
     R.hrow[h] = rec.row;
-    R.hed[h] = ed == kEdEscape ? kLeanEdEscape : (uint8_t)ed;
+    R.hed[h] = (uint8_t)meta_ed(rec.meta);
   }
-  if (ok) {
-    const int e = W.n_clog + __popcll(om & below);
-    if (e < kLeanLogPerWave) {
-      LeanLog le;
-      le.arc = (uint32_t)key; le.h = (uint16_t)h; le.from = (uint16_t)from;
-      (R.clog + (size_t)wave * kLeanLogPerWave)[e] = le;
-    } else {
-      sh->redo_b = 1;
-      CBD_WHY(1);
-    }
-  }
-  W.n_claimed += __popcll(cm);
-  W.n_clog += __popcll(om);
-  return claimed;
-}
-
-// The closure stage, first half.  A lane may bring up to two lists: the stored closure lists of the states it is
-// committing candidates to (len[q] records from pos[q]; root[q]: the candidate's cost).  The records of all the
-// wave's lists are spread over the lanes, one record per lane, and asked for with one read.
-struct LeanClosure {
-  int total;        // records (uniform); 0: nothing to do
-  bool act, second; // this lane holds a record; it is of its owner's second list
-  int owner;        // the lane whose list it belongs to
-  int plane;        // the lane before the list's first record (the parent's position is added to it)
-  float o_root;     // cost of the candidate the list hangs from
-  ArcRec rec;
-  int can;
-};
-
-__device__ __forceinline__ LeanClosure lean_closure_begin(const AdvanceParams &p, Shared *sh, int lane, uint8_t *cmap,
-                                                          const int *pos, const int *len, const float *root) {
-  LeanClosure C;
-  C.act = false; C.second = false; C.owner = 0; C.plane = 0; C.o_root = 0.0f; C.can = 0;
-  C.rec.dst = 0; C.rec.weight = 0.0f; C.rec.row = 0; C.rec.meta = 0;
-  const int mine = len[0] + len[1];
-  const int incl = wave_incl_scan(mine);
-  C.total = __builtin_amdgcn_readlane(incl, 63);
-  if (C.total == 0) return C;   // uniform
-  if (C.total > 64) {           // (rare: the general code takes the frame)
-    if (lane == 0) { sh->redo_b = 1; CBD_WHY(0); }
-    C.total = 0;
-    return C;
-  }
-  const int start = incl - mine;
-  // which lane's lists a record belongs to: the last head at or before its position
-  if (lane < 16) ((uint32_t *)cmap)[lane] = 0;
-  if (mine > 0) cmap[start] = (uint8_t)(lane + 1);
-  C.owner = wave_incl_scan_max((int)cmap[lane]) - 1;   // (position 0 is a head)
-  C.act = lane < C.total;
-  const int o_start = __shfl(start, C.owner, 64);
-  const int o_len0 = __shfl(len[0], C.owner, 64);
-  const int kk = lane - o_start;                 // position among the owner's records
-  C.second = kk >= o_len0;
-  const int o_pos0 = __shfl(pos[0], C.owner, 64);
-  const int o_pos1 = __shfl(pos[1] - len[0], C.owner, 64);
-  const int rpos = (C.second ? o_pos1 : o_pos0) + kk;
-  if (C.act) { C.rec = p.arcs[rpos]; C.can = p.canon[rpos]; }
-  const float o_root0 = __shfl(root[0], C.owner, 64), o_root1 = __shfl(root[1], C.owner, 64);
-  C.o_root = C.second ? o_root1 : o_root0;
-  C.plane = o_start + (C.second ? o_len0 : 0) - 1;
-  return C;
-}
-
-// Second half: costs follow the lists' trees level by level (a record names its parent's position), a dropped
-// record drops its subtree, and everything that passes is committed in one go.  root_h: the slots of the states
-// this lane's lists hang from.
-__device__ __forceinline__ void lean_closure_end(const AdvanceParams &p, const Mem<true> &M, const LeanMem &R,
-                                                 Shared *sh, const Ctx &cx, float m, int wave, int lane, LeanWave &W,
-                                                 const LeanClosure &C, const uint32_t *root_h, int par) {
-  if (C.total == 0) return;   // uniform
-  const uint32_t o_hh = (uint32_t)__shfl((int)(root_h[0] | (root_h[1] << 16)), C.owner, 64);
-  const uint32_t o_h = C.second ? o_hh >> 16 : o_hh & 0xFFFFu;
-  W.n_eps += (uint32_t)C.total;
-  const ArcRec &rec = C.rec;
-  const int depth = C.act ? (int)(rec.meta & 0xFu) : 0;   // 1..kClosureMaxDepth
-  const int plane = (C.plane + (int)((rec.meta >> 4) & 0x3Fu)) & 63;   // the lane that holds the parent record
-  const int can[2] = {C.can, 0};
-  bool listed[2] = {C.act, false};
-  ctx_contains_pair(cx, can, false, listed);
-  float w = rec.weight;
-  w = listed[0] ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
-  const float beam = p.beam;
-  float c = __builtin_inff();
-  bool ok = false;
-  if (depth == 1) {
-    const float cc = C.o_root + w;
-    ok = cc < __builtin_inff() && !(cc - m > beam);
-    if (ok) c = cc;
-  }
-  const int maxd = __builtin_amdgcn_readlane(wave_incl_scan_max(depth), 63);
-  for (int d = 2; d <= maxd; ++d) {   // uniform
-    const float pc = __shfl(c, plane, 64);
-    if (depth == d) {
-      const float cc = pc + w;
-      ok = cc < __builtin_inff() && !(cc - m > beam);
-      if (ok) c = cc;
-    }
-  }
-  W.max_depth = max(W.max_depth, maxd);
-  const unsigned long long om = __ballot(ok);
-  if (om == 0) return;
-  W.n_cand += (uint32_t)__popcll(om);
-  const uint32_t co = ok ? f2ord(c) : 0xFFFFFFFFu;
-  if (__ballot(ok && co < f2ord(m)) != 0) {
-    // the frame's minimum is min(m, closure candidates): only a candidate below m can move it
-    const uint32_t wmin = wave_min_u32(co);
-    if (lane == 0) atomicMin(&sh->lean_best[par], wmin);
-  }
-  uint32_t h, k;
-  lean_slot(M, ok, (uint32_t)rec.dst, h, k);
-  lean_slot_collisions(M, sh, ok, (uint32_t)rec.dst, h, k);
-  // the source state's slot: the list's state, or the parent record's (found a moment ago by its lane)
-  const uint32_t ph = (uint32_t)__shfl((int)h, plane, 64);
-  lean_min_and_log(M, R, sh, ok, h, k, ((uint64_t)co << 32) | (uint32_t)C.can, rec, depth == 1 ? o_h : ph, wave, lane,
-                   W);
+  W.claimed += __popcll(claimed);
+  W.n_clog += n_ok;
 }
 
 // Commits the emitting candidates in E (the cutoff m is final) and walks the closure lists behind them.  The
 // steps are ordered so that waits overlap: the table slots are asked for, then the closure records, and only
 // then are the slots looked at.
+// The closure stage: a lane may bring up to two lists, the stored closure lists of the states it is committing candidates
+// to.  The records of all the wave's lists are spread over the lanes, one record per lane, and asked for with one read; then
+// costs follow the lists' trees level by level (a record names its parent's position), a dropped record drops its subtree,
+// and everything that passes is committed in one go.
+template <int kSlots>
 __device__ __forceinline__ void lean_commit(const AdvanceParams &p, const Mem<true> &M, const LeanMem &R, Shared *sh,
-                                            const Ctx &cx, float m, int wave, int lane, LeanWave &W, uint8_t *cmap,
+                                            const Ctx &cx, float m, int lane, LeanWave &W, uint8_t *cmap, LeanLog *clog,
                                             const LeanEmit &E, int par) {
-  bool pass[2];
-  uint32_t h[2], k[2];
+  const float beam = p.beam;
+  uint64_t pass[kSlots], any = 0;
+  uint32_t h[kSlots], k[kSlots];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) pass[q] = E.act[q] && !(E.cand[q] - m > p.beam);
-  if (__ballot(pass[0] || pass[1]) == 0) return;   // uniform
+  for (int q = 0; q < kSlots; ++q) { pass[q] = E.act[q] & lanes_with(!(E.cand[q] - m > beam)); any |= pass[q]; }
+  if (any == 0) return;   // uniform
 #pragma unroll
-  for (int q = 0; q < 2; ++q) lean_slot(M, pass[q], (uint32_t)E.rec[q].dst, h[q], k[q]);
+  for (int q = 0; q < kSlots; ++q) lean_slot(M, pass[q], (uint32_t)E.rec[q].dst, h[q], k[q]);
   // the closure lists of the destinations
-  int pos[2] = {0, 0}, len[2] = {0, 0};
+  int len[kSlots], mine = 0;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const uint32_t cl = meta_cl(E.rec[q].meta);
-    if (pass[q] && cl > 0) {
-      if (cl == kClEscape) {
-        sh->redo_b = 1;   // no stored list: the general code follows this closure
-        CBD_WHY(3);
-      } else {
-        pos[q] = E.rec[q].row + (int)meta_ed(E.rec[q].meta) + (int)meta_xd(E.rec[q].meta);
-        len[q] = (int)cl;
-      }
+  for (int q = 0; q < kSlots; ++q) { len[q] = lane_in(pass[q]) ? (int)meta_cl(E.rec[q].meta) : 0; mine += len[q]; }
+  const int incl = wave_incl_scan(mine);
+  int total = __builtin_amdgcn_readlane(incl, 63);
+  if (total >= (int)kClEscape) {   // (rare: no stored list, or more than a lane per record; the general code takes the frame)
+    uint64_t esc = 0;
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) esc |= lanes_with(len[q] == (int)kClEscape);
+    if (esc != 0 || total > 64) {
+      W.redo = true;
+      if (lane_in(1ull)) CBD_WHY(esc != 0 ? 3 : 0);
+      total = 0;
     }
   }
-  const LeanClosure C = lean_closure_begin(p, sh, lane, cmap, pos, len, E.cand);
+  auto commit_emitting = [&]() {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) lean_slot_collisions(M, sh, pass[q], (uint32_t)E.rec[q].dst, h[q], k[q], W);
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      W.n_cand += __popcll(pass[q]);
+      lean_min_and_log(M, R, sh, pass[q], h[q], k[q], f2ord(E.cand[q]), (uint32_t)E.arc[q], E.rec[q], E.from[q], clog, W);
+    }
+    CBD_STAMP(7);   // (diagnostic: emitting candidates committed)
+  };
+  if (total == 0) {   // uniform
+    CBD_STAMP(6);
+    commit_emitting();
+    CBD_STAMP(8);
+    return;
+  }
+  // which list a record belongs to: the last head at or before its position.  A head names its lane and which of the lane's
+  // lists it is (2 lane + which + 1: later positions have larger names)
+  int start[kSlots];
+  start[0] = incl - mine;
+  if (lane_in(0xFFFFull)) ((uint32_t *)cmap)[lane] = 0;
+  if (len[0] > 0) cmap[start[0]] = (uint8_t)(kSlots * lane + 1);
+  if (kSlots == 2) {
+    start[1] = start[0] + len[0];
+    if (len[1] > 0) cmap[start[1]] = (uint8_t)(2 * lane + 2);
+  }
+  const int name = wave_incl_scan_max((int)cmap[lane]) - 1;   // (position 0 is a head)
+  const int owner = kSlots == 2 ? name >> 1 : name;
+  const bool second = kSlots == 2 && (name & 1) != 0;
+  // what the list's lane knows: where its records lie and begin in the stage, and the cost they hang from
+  int at[kSlots];
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q)
+    at[q] = E.rec[q].row + (int)meta_ed(E.rec[q].meta) + (int)meta_xd(E.rec[q].meta) - start[q];
+  int rpos = from_lane(at[0], owner), o_start = from_lane(kSlots == 2 ? start[0] | (start[1] << 8) : start[0], owner);
+  float o_root = from_lane(E.cand[0], owner);
+  if (kSlots == 2) {
+    const int rpos1 = from_lane(at[1], owner);
+    const float root1 = from_lane(E.cand[1], owner);
+    rpos = second ? rpos1 : rpos;
+    o_root = second ? root1 : o_root;
+    o_start = second ? o_start >> 8 : o_start & 0xFF;
+  }
+  const uint64_t act = total == 64 ? ~0ull : (1ull << total) - 1ull;
+  // (lanes beyond the lists ask for the last record once more)
+  rpos += min(lane, total - 1);
+  const ArcRec rec = p.arcs[rpos];
+  int can[2];
+  can[0] = can[1] = p.canon[rpos];
   CBD_STAMP(6);   // (diagnostic: cutoff, slot requests, closure records requested)
   // now the emitting candidates' slots
-#pragma unroll
-  for (int q = 0; q < 2; ++q) lean_slot_collisions(M, sh, pass[q], (uint32_t)E.rec[q].dst, h[q], k[q]);
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    if (__ballot(pass[q]) == 0) continue;   // uniform
-    W.n_cand += (uint32_t)__popcll(__ballot(pass[q]));
-    const uint64_t key = ((uint64_t)f2ord(E.cand[q]) << 32) | (uint32_t)E.arc[q];
-    lean_min_and_log(M, R, sh, pass[q], h[q], k[q], key, E.rec[q], (uint32_t)E.src[q] | kLeanFromToken, wave, lane, W);
+  commit_emitting();
+
+  const int o_hh = from_lane((int)(kSlots == 2 ? h[0] | (h[1] << 16) : h[0]), owner);
+  W.n_eps += total;
+  const int depth = (int)(rec.meta & 0xFu);   // 1..kClosureMaxDepth
+  const int plane = (o_start - 1 + (int)((rec.meta >> 4) & 0x3Fu)) & 63;   // the lane that holds the parent record
+  const uint64_t acts[2] = {act, 0};
+  uint64_t listed[2];
+  lean_listed<1>(cx, can, acts, listed);
+  float w = rec.weight;
+  w = lane_in(listed[0]) ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
+  const uint64_t d1 = act & lanes_with(depth == 1);
+  float c = o_root + w;
+  uint64_t ok = d1 & lanes_with(c < __builtin_inff()) & lanes_with(!(c - m > beam));
+  c = lane_in(ok) ? c : __builtin_inff();
+  int d = 1;
+  for (;;) {   // uniform (a record of one level has its parent in the level before)
+    const uint64_t dm = act & lanes_with(depth == d + 1);
+    if (dm == 0) break;
+    ++d;
+    const float cc = from_lane(c, plane) + w;
+    const uint64_t okd = dm & lanes_with(cc < __builtin_inff()) & lanes_with(!(cc - m > beam));
+    c = lane_in(okd) ? cc : c;
+    ok |= okd;
   }
-  CBD_STAMP(7);   // (diagnostic: emitting candidates committed)
-  lean_closure_end(p, M, R, sh, cx, m, wave, lane, W, C, h, par);
+  W.max_depth = max(W.max_depth, d);
+  if (ok == 0) { CBD_STAMP(8); return; }   // uniform
+  W.n_cand += __popcll(ok);
+  const uint32_t co = f2ord(c);
+  if ((ok & lanes_with(co < f2ord(m))) != 0) {
+    // the frame's minimum is min(m, closure candidates): only a candidate below m can move it
+    const uint32_t wmin = wave_min_u32(lane_in(ok) ? co : 0xFFFFFFFFu);
+    if (lane == 0) atomicMin(&sh->lean_best[par], wmin);
+  }
+  uint32_t ch, ck;
+  lean_slot(M, ok, (uint32_t)rec.dst, ch, ck);
+  lean_slot_collisions(M, sh, ok, (uint32_t)rec.dst, ch, ck, W);
+  // the source state's slot: the list's state, or the parent record's (found a moment ago by its lane)
+  const uint32_t ph = (uint32_t)from_lane((int)ch, plane);
+  const uint32_t o_h = kSlots == 2 ? (second ? (uint32_t)o_hh >> 16 : (uint32_t)o_hh & 0xFFFFu) : (uint32_t)o_hh;
+  lean_min_and_log(M, R, sh, ok, ch, ck, co, (uint32_t)can[0], rec, (lane_in(d1) ? o_h : ph) << 16, clog, W);
   CBD_STAMP(8);   // (diagnostic: closure records committed)
 }
 
@@ -456,7 +559,7 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
                                               int2 *bp, int32_t *g_tok_state, bool last_frame, int par) {
   constexpr int NW = kBlock / 64;
   static_assert(NW <= 16, "Shared::wcount holds 16 waves");
-  const int tid = here_tid(), lane = tid & 63, wave = tid >> 6;
+  const int tid = here_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #ifdef CBD_PROFILE
   if (tid == 0) sh->prof_last = wall_clock64();
 #endif
@@ -464,38 +567,46 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
   const float inv = 256.0f / p.beam;
   uint8_t *omap = owner_maps + wave * kOwnerMap;
   uint8_t *cmap = closure_maps + wave * 64;
+  LeanLog *clog = R.clog + wave * kLeanLogPerWave;
+  LeanOwner *owners = (LeanOwner *)clog;
 
   // ---- emit: prune (step 1), expand (step 2).  The wave's share of the tokens is taken in tiles of 64, a tile's
   // arcs 128 at a time; tile 0's first 128 come last and stay in registers.
-  const int n_tok = sh->n_tok;
+  const int n_tok = __builtin_amdgcn_readfirstlane(sh->n_tok);
   const float best = sh->best;
-  const int cut = sh->cut_bin;
+  const int cut = __builtin_amdgcn_readfirstlane(sh->cut_bin);
   const int tpw = (n_tok + NW - 1) / NW;
   const int tile0 = wave * tpw;
   const int tile_end = min(tile0 + tpw, n_tok);
-  const int n_tiles = (tpw + 63) >> 6;   // (uniform over the workgroup)
-  uint32_t n_active = 0, n_emit = 0;
+  int n_active = 0, n_emit = 0;
   uint32_t lmin = 0xFFFFFFFFu;
   LeanEmit E;
   LeanTile T;
-  for (int st = n_tiles - 1; st >= 0; --st) {
-    T = lean_load_tile(p, M, R, sh, omap, tile0, tile_end, st, lane, best, cut, inv, n_active);
-    n_emit += (uint32_t)T.total;
-    for (int jb = T.total > 0 ? ((T.total - 1) >> 7) << 7 : 0; jb >= 0; jb -= 128) {
-      const uint32_t l = lean_candidates<true>(p, cx, Lrow, omap, jb, lane, T, E);
-      lmin = l < lmin ? l : lmin;
+  T.total = 0;
+  for (int base = tile0 + ((tile_end - 1 - tile0) & ~63); base >= tile0; base -= 64) {   // (none: tile_end <= tile0)
+    T = lean_load_tile<true>(p, M, R, sh, omap, owners, base, tile_end, lane, best, cut, inv, n_active);
+    if (T.total == 0) continue;   // uniform
+    n_emit += T.total;
+    for (int jb = (T.total - 1) & ~127; jb >= 0; jb -= 128) {   // (one round but for heavy frames)
+      const int heads = lean_heads_before(omap, jb, lane);
+      const uint32_t l = T.total - jb > 64 ? lean_candidates<2>(p, cx, Lrow, omap, owners, jb, heads, lane, T, E)
+                                           : lean_candidates<1>(p, cx, Lrow, omap, owners, jb, heads, lane, T, E);
+      lmin = umin32(lmin, l);
     }
   }
-  const uint32_t n_active_frame = n_active;
-  const uint32_t wmin = wave_min_u32(lmin);
-  if (lane == 0 && wmin != 0xFFFFFFFFu) atomicMin(&sh->m_ord, wmin);
+  const int n_active_frame = n_active;
+  if (n_emit != 0) {   // uniform
+    const uint32_t wmin = wave_min_u32(lmin);
+    if (lane == 0) atomicMin(&sh->m_ord, wmin);
+  }
   CBD_STAMP(0);   // emit phase of wave 0
   wg_barrier<true>();
   CBD_STAMP(1);   // its wait at the first barrier
 
   // ---- step 3: the emission minimum fixes the frame's cutoff
   const uint32_t m_ord = sh->m_ord;
-  if (sh->redo) return kFrameRedo;              // (uniform: set before the barrier, or never)
+  const int redo = sh->redo;
+  if (redo) return kFrameRedo;                  // (uniform: set before the barrier, or never)
   if (m_ord == 0xFFFFFFFFu) return kFrameNoTokens;
   const float m = ord2f(m_ord);
 
@@ -503,16 +614,15 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
   // then whatever the tiles hold beyond them, computed again (the staged row may be on its way out by then: these
   // read the row in device memory)
   LeanWave W;
-  W.n_claimed = 0; W.n_clog = 0; W.n_cand = 0; W.n_eps = 0; W.max_depth = 0;
-  {
-    bool have = true;   // E holds tile 0's first 128 candidates
-    for (int st = 0; st < n_tiles; ++st) {
-      if (st > 0) T = lean_load_tile(p, M, R, sh, omap, tile0, tile_end, st, lane, best, cut, inv, n_active);
-      for (int jb = 0; jb == 0 || jb < T.total; jb += 128) {
-        if (!have) lean_candidates<false>(p, cx, Lrow, omap, jb, lane, T, E);
-        have = false;
-        lean_commit(p, M, R, sh, cx, m, wave, lane, W, cmap, E, par);
-      }
+  W.claimed = wave << kLeanLidBits; W.n_clog = 0; W.n_cand = 0; W.n_eps = 0; W.max_depth = 0; W.redo = false;
+  if (T.total > 64) lean_commit<2>(p, M, R, sh, cx, m, lane, W, cmap, clog, E, par);
+  else if (T.total > 0) lean_commit<1>(p, M, R, sh, cx, m, lane, W, cmap, clog, E, par);
+  for (int base = tile0; base < tile_end; base += 64) {
+    if (base > tile0) T = lean_load_tile<false>(p, M, R, sh, omap, owners, base, tile_end, lane, best, cut, inv, n_active);
+    for (int jb = base > tile0 ? 0 : 128; jb < T.total; jb += 128) {
+      LeanEmit X;
+      lean_candidates_again(p, cx, Lrow, omap, jb, lane, T, X);
+      lean_commit<2>(p, M, R, sh, cx, m, lane, W, cmap, clog, X, par);
     }
   }
   // The emit phase is long over: the next frame's row starts its way.  (Not earlier: loads return in order, and
@@ -527,26 +637,22 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
     else if (back * 16 < p.num_pdfs) touched = Lnext[back * 16];
   }
   if (lane == 0) {
-    sh->wcount[wave] = W.n_claimed;
+    sh->wcount[wave] = W.redo ? kLeanRedoCount : W.claimed & kLeanLidMask;
     if (W.max_depth) atomicMax(&sh->rounds, W.max_depth);
   }
-  const int base_cur = sh->n_rec, base_prev = sh->frame_base;
+  const int base_cur = __builtin_amdgcn_readfirstlane(sh->n_rec), base_prev = __builtin_amdgcn_readfirstlane(sh->frame_base);
   CBD_STAMP(2);   // commit phase of wave 0
   wg_barrier<true>();
   CBD_STAMP(3);   // its wait at the second barrier
 
   // ---- step 5 and bookkeeping: the winner of each state writes the token
-  if (sh->redo_b) return kFrameRedo;   // (uniform: set between the two barriers, or never)
-  // dense token indices: prefix sums over the waves' counts (every wave computes the same numbers)
-  int n_claim;
-  {
-    const int c = lane < NW ? sh->wcount[lane] : 0;
-    const int inc = wave_incl_scan(c);
-    n_claim = __builtin_amdgcn_readlane(inc, 63);
-    if (lane < NW) sh->wbase[lane] = inc - c;
-  }
-  if (n_claim > M.tok_cap) {   // (the general code decides what an overflow means)
-    if (tid == 0) CBD_WHY(2);
+  // dense token indices: prefix sums over the waves' counts (every wave computes the same numbers; lane w < NW has wave w's)
+  const int my_count = sh->wcount[lane & 15];
+  const int count_incl = row_incl_scan(lane < NW ? my_count : 0);
+  const int wbase = count_incl - my_count;
+  const int n_claim = __builtin_amdgcn_readlane(count_incl, 15);
+  if (n_claim > M.tok_cap) {   // (the general code decides what an overflow means; or some wave gave the frame up)
+    if (tid == 0 && n_claim < kLeanRedoCount) CBD_WHY(2);
     return kFrameRedo;
   }
   if (base_cur + n_claim > p.bp_cap) return kFrameRecordsFull;
@@ -567,7 +673,6 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
     sh->a_rounds += (unsigned long long)sh->rounds;
     sh->rounds = 0;
   }
-  int4 *hbm_rows = M.t_row + (size_t)row_buf * M.row_cap;
   int w_surv = 0;
   // vmcnt(0): this wave's pieces of the next row have arrived in LDS; the barrier at the end of the frame tells the
   // others.  (The compiler waits for them already at the write of wcount, as it does before any LDS access behind such a
@@ -582,63 +687,62 @@ __device__ __forceinline__ int run_frame_lean(const AdvanceParams &p, const Mem<
   // histogram.  An emitting arc is expanded once per frame, so its entry is unique; a closure record can have
   // been committed twice with the same (cost, arc) (two walks of one list from values that round to the same
   // sum): the compare-and-swap lets one of the two write.
-  {
-    const LeanLog *clog = R.clog + (size_t)wave * kLeanLogPerWave;
-    const int lane_here = here_tid() & 63;
-    for (int j0 = 0; j0 < W.n_clog; j0 += 64) {
-      const int j = j0 + lane_here;
-      bool surv = false;
-      if (j < W.n_clog) {
-        const LeanLog e = clog[j];
-        // everything the winner will need is asked for together: the state's value, row and token id, the source
-        // state's token id, and the waves' bases
-        const uint64_t v = M.hval[e.h];
-        const int row = R.hrow[e.h];
-        const uint32_t ed = R.hed[e.h];
-        const int lid = (int)M.hidx[e.h];
-        const bool from_token = (e.from & kLeanFromToken) != 0;
-        const int from = (int)(e.from & (kLeanFromToken - 1));
-        const int plid = (int)M.hidx[from_token ? 0 : from];
-        const int idx = sh->wbase[(lid >> kLeanLidBits) & 15] + (lid & kLeanLidMask);
-        const int pidx = sh->wbase[(plid >> kLeanLidBits) & 15] + (plid & kLeanLidMask);
-        bool win = (uint32_t)v == e.arc && v != kEmptyVal;
-        if (win && !from_token)
-          win = atomicCAS((unsigned long long *)&M.hval[e.h], (unsigned long long)v, (unsigned long long)kEmptyVal) == v;
-        if (win) {
-          const float c = ord2f((uint32_t)(v >> 32));
-          M.t_cost[idx] = c;
-          R.t_first[idx] = row;
-          R.t_deg[idx] = ed == kLeanEdEscape ? kLeanDegEscape : (uint16_t)ed;
-          bp[base_cur + idx] = make_int2((int)e.arc, from_token ? base_prev + from : base_cur + pidx);
-          uint32_t state = 0;
-          if (last_frame || ed == kLeanEdEscape) state = M.hkey[e.h];
-          if (last_frame) g_tok_state[idx] = (int)state;
-          if (ed == kLeanEdEscape) {
-            // a row too long for the count field (rare): its bounds go to the row buffer in device memory, where
-            // the general code, which will take the next frame, looks for them
-            const int4 o = p.off2[state];
-            hbm_rows[idx] = make_int4(o.x, o.y, o.z, 0);
-          }
-          M.hkey[e.h] = kEmptyKey;
-          if (from_token) M.hval[e.h] = kEmptyVal;
-          if (hist_need) {
-            const float r = c - fbest;
-            if (!(r > p.beam)) {
-              surv = true;
-              int bin = (int)floorf(r * inv);
-              bin = bin > 255 ? 255 : bin;
-              atomicAdd(&hist[bin], 1u);
-            }
+  int2 *bp_cur = bp + base_cur;
+  for (int j0 = 0; j0 < W.n_clog; j0 += 64) {
+    // (lanes beyond the log look at its last entry: all lanes have to take part in what the waves' bases come from)
+    const uint2 e = *(const uint2 *)&clog[min(j0 + lane, W.n_clog - 1)];
+    const uint32_t eh = e.y & 0xFFFFu;
+    // everything the winner will need is asked for together: the state's value, row and token id, and the source
+    // state's token id
+    const uint64_t v = M.hval[eh];
+    const int row = R.hrow[eh];
+    const uint32_t ed = R.hed[eh];
+    const int lid = (int)M.hidx[eh];
+    const bool from_token = (int)e.y < 0;
+    const int from = (int)((e.y >> 16) & (kLeanFromToken - 1));
+    const int plid = (int)M.hidx[from_token ? 0 : from];
+    const int idx = from_lane(wbase, lid >> kLeanLidBits) + (lid & kLeanLidMask);
+    const int pidx = from_lane(wbase, (plid >> kLeanLidBits) & 15) + (plid & kLeanLidMask);
+    bool surv = false;
+    if (j0 + lane < W.n_clog) {
+      bool win = (uint32_t)v == e.x && v != kEmptyVal;
+      if (win && !from_token)
+        win = atomicCAS((unsigned long long *)&M.hval[eh], (unsigned long long)v, (unsigned long long)kEmptyVal) == v;
+      if (win) {
+        const float c = ord2f((uint32_t)(v >> 32));
+        M.t_cost[idx] = c;
+        R.t_first[idx] = row;
+        R.t_deg[idx] = ed == kEdEscape ? kLeanDegEscape : (uint16_t)ed;
+        bp_cur[idx] = make_int2((int)e.x, from_token ? base_prev + from : base_cur + pidx);
+        uint32_t state = 0;
+        if (last_frame || ed == kEdEscape) state = M.hkey[eh];
+        if (last_frame) g_tok_state[idx] = (int)state;
+        if (ed == kEdEscape) {
+          // a row too long for the count field (rare): its bounds go to the row buffer in device memory, where
+          // the general code, which will take the next frame, looks for them
+          const int4 o = p.off2[state];
+          int4 *hbm_rows = M.t_row + (size_t)row_buf * M.row_cap;
+          hbm_rows[idx] = make_int4(o.x, o.y, o.z, 0);
+        }
+        M.hkey[eh] = kEmptyKey;
+        if (from_token) M.hval[eh] = kEmptyVal;
+        if (hist_need) {
+          const float r = c - fbest;
+          if (!(r > p.beam)) {
+            surv = true;
+            int bin = (int)floorf(r * inv);
+            bin = bin > 255 ? 255 : bin;
+            atomicAdd(&hist[bin], 1u);
           }
         }
       }
-      if (hist_need) w_surv += __popcll(__ballot(surv));
     }
+    if (hist_need) w_surv += __popcll(lanes_with(surv));
   }
   if (lane == 0) {
     // (two counters to an atomic; they are taken apart when the call ends)
-    atomicAdd(&sh->a_lean_pack[0], (unsigned long long)n_active_frame | ((unsigned long long)n_emit << 32));
-    atomicAdd(&sh->a_lean_pack[1], (unsigned long long)W.n_eps | ((unsigned long long)W.n_cand << 32));
+    atomicAdd(&sh->a_lean_pack[0], (unsigned long long)(uint32_t)n_active_frame | ((unsigned long long)(uint32_t)n_emit << 32));
+    atomicAdd(&sh->a_lean_pack[1], (unsigned long long)(uint32_t)W.n_eps | ((unsigned long long)(uint32_t)W.n_cand << 32));
   }
   // ---- the histogram cut: the wave that gets here last takes it (every wave's LDS traffic of this phase lies before
   // its count, and LDS keeps a wave's operations in order)
