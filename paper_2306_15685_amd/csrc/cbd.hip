@@ -326,7 +326,7 @@ hipError_t prepare_team_rows(cbd_decoder *d) {
   int64_t total = 0;
   for (auto &r : rows) { r.w = (int)total; total += r.z; }
   if (total >= 0x7FFFFFF0) return hipSuccess;
-  const size_t rows_b = sizeof(int4) * rows.size(), group_b = sizeof(int32_t) * rows.size() * (k + 1);
+  const size_t rows_b = sizeof(int4) * rows.size(), group_b = sizeof(int32_t) * rows.size() * (3 * k + 1);
   size_t recs_b = sizeof(cbd::ArcRec) * (size_t)total;
   if (recs_b > d->bytes / 8) recs_b = 0;
   hipError_t e = dmalloc(&d->d_team_big, recs_b + rows_b + group_b + sizeof(int32_t) * (size_t)total, &d->bytes);
@@ -343,8 +343,10 @@ hipError_t prepare_team_rows(cbd_decoder *d) {
   d->team_big_perm = (int32_t *)(d->d_team_big + recs_b + rows_b + group_b);
   e = hipMemcpy(d->team_big_rows, rows.data(), rows_b, hipMemcpyHostToDevice);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cbd::team_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), 0, d->stream, d->g->d_arcs,
-                     d->team_big_rows, d->team_big_group, d->team_big_perm, d->team_big_recs, d->team_k);
+  // (a bit per member and slot: 12 KB at most)
+  const size_t taken_b = sizeof(uint32_t) * k * (((size_t)d->team_slots + 31) / 32);
+  hipLaunchKernelGGL(cbd::team_prepare_rows_kernel, dim3((unsigned)rows.size()), dim3(256), taken_b, d->stream, d->g->d_arcs,
+                     d->team_big_rows, d->team_big_group, d->team_big_perm, d->team_big_recs, (uint32_t)d->team_slots, d->team_k);
   return hipGetLastError();
 }
 

@@ -367,6 +367,18 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
 }
 
+// Lane masks.  Which lanes of a wave do something is kept as 64 bits in a scalar register pair from one step to the next:
+// a mask becomes a lane's condition and a count of the lanes below in one or two instructions, where a flag per lane would
+// be moved through a vector register and compared again at every branch.
+__device__ __forceinline__ uint64_t lanes_with(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// base + the number of lanes of m below this one
+__device__ __forceinline__ int rank_in(uint64_t m, int base) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+__device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
+__device__ __forceinline__ float from_lane(float v, int lane) { return __int_as_float(from_lane(__float_as_int(v), lane)); }
+
 // Workgroup barrier.  A frame whose working set is in LDS only has to order LDS traffic;
 // outstanding HBM loads and stores (the next log-likelihood row, back-pointer records) keep flying.
 template <bool kLds> __device__ __forceinline__ void wg_barrier() {

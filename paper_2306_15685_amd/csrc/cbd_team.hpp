@@ -50,6 +50,17 @@ struct __attribute__((aligned(16))) TeamEntry {
 };
 static_assert(sizeof(TeamEntry) == 32, "queue entries are 32 bytes");
 
+// What a member needs of an announced long row with sorted arcs: in LDS from the end of phase 1, in the staging list of the
+// member's last wave.  A row that is pruned or not known has no arcs.
+struct __attribute__((aligned(16))) TeamRow {
+  int32_t perm0;      // start of the row's stretch of big_perm
+  int32_t g[4];       // the member's groups in it (TeamParams::big_group)
+  int32_t src;        // the row's token ...
+  float cost;         // ... and its cost
+  int32_t direct;     // (first entry) which row enters the table directly, -1: none
+};
+static_assert(sizeof(TeamRow) * kTeamBig <= 64 * sizeof(LiveToken), "the rows fit a wave's staging list");
+
 struct TeamClosureWin { int32_t idx; uint32_t arc; uint32_t parent_state; };
 
 // One frame's team-wide scalars (two copies, used by even and odd frames in turn).
@@ -89,7 +100,8 @@ struct TeamParams {
   // Rows with more than kBigRowArcs emitting arcs, known when the graph was loaded: for each, its arcs sorted by the
   // member that owns their destination (a member then expands the arcs it owns itself: nothing travels)
   const int4 *big_rows;    // [n_big_rows] x = state (ascending), y = first emitting arc, z = emitting arcs, w = start in big_perm
-  const int32_t *big_group;  // [n_big_rows][k + 1] where each member's arcs begin in the row's stretch of big_perm
+  const int32_t *big_group;  // [n_big_rows][3 k + 1] where each member's arcs begin in the row's stretch of big_perm: those with
+                             // a home slot to themselves, the others, those whose destination has a closure
   const int32_t *big_perm;   // library arc indices
   const ArcRec *big_recs;    // the same places: the arcs' records (null: they are read through big_perm)
   int32_t n_big_rows;
@@ -180,7 +192,7 @@ __device__ __forceinline__ void team_push(TeamEntry *q_base, unsigned long long 
   bool any = false;
 #pragma unroll
   for (int u = 0; u < U; ++u) any = any || act[u];
-  if (__ballot(any) == 0) return;   // uniform
+  if (lanes_with(any) == 0) return;   // uniform
   if (__hip_atomic_load(&sh->fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) return;
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long add[2] = {0, 0};
@@ -189,8 +201,8 @@ __device__ __forceinline__ void team_push(TeamEntry *q_base, unsigned long long 
   for (int u = 0; u < U; ++u) {
     rank[u] = 0;
     for (int o = 0; o < k; ++o) {   // uniform
-      const unsigned long long m = __ballot(act[u] && owner[u] == o);
-      if (owner[u] == o) rank[u] = (int)__popcll(m & below) + (int)((add[o >> 2] >> (16 * (o & 3))) & 0xFFFFull);
+      const unsigned long long m = lanes_with(act[u] && owner[u] == o);
+      if (owner[u] == o) rank[u] = rank_in(m, 0) + (int)((add[o >> 2] >> (16 * (o & 3))) & 0xFFFFull);
       add[o >> 2] += (unsigned long long)__popcll(m) << (16 * (o & 3));
     }
   }
@@ -240,11 +252,11 @@ __device__ __forceinline__ uint32_t team_find(const uint32_t *hkey, uint32_t slo
 // word end leads to the hub): if they all do, the wave's minimum is taken first and one lane commits it.
 __device__ __forceinline__ void team_min(uint64_t *hval, uint32_t *hkey, uint32_t slots, TeamShared *sh, bool act,
                                          uint32_t state, uint64_t key, int lane) {
-  const unsigned long long am = __ballot(act);
+  const unsigned long long am = lanes_with(act);
   if (am == 0) return;
   const int first = (int)__builtin_ctzll(am);
   const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)state, first);
-  if (__popcll(am) > 1 && __ballot(act && state == s0) == am) {
+  if (__popcll(am) > 1 && lanes_with(act && state == s0) == am) {
     const uint32_t hi = act ? (uint32_t)(key >> 32) : 0xFFFFFFFFu;
     const uint32_t mhi = wave_min_u32(hi);
     const uint32_t lo = (act && hi == mhi) ? (uint32_t)key : 0xFFFFFFFFu;
@@ -310,31 +322,46 @@ __device__ __forceinline__ void team_long_row(const TeamParams &tp, const Ctx &c
       act[u] = j < deg;
       a[u] = first + j;
       r[u] = team_arc(tp, act[u], a[u]);
-      n_emit += (uint32_t)__popcll(__ballot(act[u]));
+      n_emit += (uint32_t)__popcll(lanes_with(act[u]));
     }
     team_emit<4>(tp, cx, Lrow, sh, q1c, me, act, a, r, cost, src, lane, lmin);
   }
 }
 
-// One workgroup per long row: sorts the row's arcs by the member that owns their destination (counting sort; the
-// order inside a member's group does not matter).
+// One workgroup per long row: sorts the row's arcs by the member that owns their destination (counting sort), and a member's
+// by what they need of its table: (0) no closure and a home slot that no other arc of the row before them has, (1) no closure,
+// (2) a closure.  The order inside a group does not matter.  LDS: a bit per member and slot.
 __global__ __launch_bounds__(256) void team_prepare_rows_kernel(const ArcRec *arcs, const int4 *big_rows, int32_t *big_group,
-                                                                int32_t *big_perm, ArcRec *big_recs, int k) {
-  __shared__ int32_t count[kTeamMax + 1], fill[kTeamMax];
+                                                                int32_t *big_perm, ArcRec *big_recs, uint32_t slots, int k) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint32_t *taken = (uint32_t *)smem;
+  __shared__ int32_t count[3 * kTeamMax], fill[3 * kTeamMax];
+  const int words = (int)((slots + 31) / 32);
   const int4 row = big_rows[blockIdx.x];
-  if (threadIdx.x <= kTeamMax) count[threadIdx.x] = 0;
-  __syncthreads();
-  for (int j = threadIdx.x; j < row.z; j += blockDim.x) atomicAdd(&count[share_owner((uint32_t)arcs[row.y + j].dst, k)], 1);
+  int32_t *group = big_group + blockIdx.x * (3 * k + 1);
+  auto clear = [&]() {
+    for (int i = threadIdx.x; i < k * words; i += blockDim.x) taken[i] = 0;
+    __syncthreads();
+  };
+  auto bucket = [&](const ArcRec &r) {
+    const int o = share_owner((uint32_t)r.dst, k);
+    if (meta_cl(r.meta) != 0 || meta_ed(r.meta) == kEdEscape || meta_xd(r.meta) == kXdEscape) return 3 * o + 2;
+    const uint32_t h = share_home((uint32_t)r.dst, slots), bit = 1u << (h & 31u);
+    return 3 * o + ((atomicOr(&taken[o * words + (int)(h >> 5)], bit) & bit) ? 1 : 0);
+  };
+  if (threadIdx.x < 3 * kTeamMax) count[threadIdx.x] = 0;
+  clear();
+  for (int j = threadIdx.x; j < row.z; j += blockDim.x) atomicAdd(&count[bucket(arcs[row.y + j])], 1);
   __syncthreads();
   if (threadIdx.x == 0) {
     int run = 0;
-    for (int o = 0; o < k; ++o) { const int c = count[o]; big_group[blockIdx.x * (k + 1) + o] = run; fill[o] = run; run += c; }
-    big_group[blockIdx.x * (k + 1) + k] = run;
+    for (int o = 0; o < 3 * k; ++o) { const int c = count[o]; group[o] = run; fill[o] = run; run += c; }
+    group[3 * k] = run;
   }
-  __syncthreads();
+  clear();   // (who is first at a slot may be another arc this time; how many are is the same)
   for (int j = threadIdx.x; j < row.z; j += blockDim.x) {
     const ArcRec rec = arcs[row.y + j];
-    const int at = row.w + atomicAdd(&fill[share_owner((uint32_t)rec.dst, k)], 1);
+    const int at = row.w + atomicAdd(&fill[bucket(rec)], 1);
     big_perm[at] = row.y + j;
     if (big_recs) big_recs[at] = rec;
   }
@@ -506,40 +533,72 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       }
       return alive;
     };
-    // (asked for a round ahead and made into an entry afterwards; the record is read from a copy in the sorted order, 16
-    // lines of 64 bytes per wave, instead of through the arc's index, up to 64 lines behind another read: 64 channels x
-    // 100 frames of 20,000 words 8.43 -> 8.26 ms, 8 channels of 3,000 words the same)
-    auto long_load = [&](int perm0, int t, int t_end, int &a, ArcRec &rec) {
-      a = -1; rec.dst = 0; rec.weight = 0.0f; rec.row = 0; rec.meta = 0;
-      if (t < t_end) { a = tp.big_perm[perm0 + t]; rec = kRecs ? tp.big_recs[perm0 + t] : p.arcs[a]; }
-    };
-    auto long_entry = [&](int a, const ArcRec &rec, float cost, int src) {
-      TeamEntry e; e.dst = kEmptyKey; e.cost = 0.0f; e.arc = 0; e.from = 0; e.row = 0; e.meta = 0; e.pad[0] = 0; e.pad[1] = 0;
-      if (a >= 0) {
-        float w = rec.weight;
-        if (ctx_contains(cx, a)) w = w + cx.offset;   // Sec. 4.1
-        e.dst = (uint32_t)rec.dst; e.cost = (cost + w) - Lrow.at((rec.meta & 0xFFFFu) - 1u); e.arc = (uint32_t)a; e.from = src;
-        e.row = rec.row; e.meta = rec.meta & 0xFFFF0000u;
-      }
-      return e;
-    };
     const int nbig_prev = fprev->n_big < kTeamBig ? fprev->n_big : kTeamBig;
-    // every candidate this member owns of the announced long rows with sorted arcs, one per thread and round
-    auto for_owned_long_arcs = [&](auto &&fn) {
-      for (int r = 0; r < nbig_prev; ++r) {
-        const int id = fprev->big_id[r];
-        const float cost = fprev->big_cost[r];
-        if (id < 0 || !row_alive(cost)) continue;   // uniform
-        const int src = fprev->big_src[r];
-        const int4 row = tp.big_rows[id];
-        const int g0 = tp.big_group[id * (k + 1) + me], g1 = tp.big_group[id * (k + 1) + me + 1];
-        int a0, a1;
-        ArcRec r0, r1;
-        long_load(row.w, g0 + tid, g1, a0, r0);
-        for (int t0 = g0; t0 < g1; t0 += kBlock) {   // uniform
-          long_load(row.w, t0 + kBlock + tid, g1, a1, r1);
-          fn(long_entry(a0, r0, cost, src));
-          a0 = a1; r0 = r1;
+    TeamRow *rows = (TeamRow *)((LiveToken *)(smem + lay.stage) + (NW - 1) * 64);
+    int row_id = -1, row_src = 0;   // (the last wave: lane r looks after row r)
+    float row_cost = 0.0f;
+    if (wave == NW - 1 && lane < nbig_prev) { row_id = fprev->big_id[lane]; row_cost = fprev->big_cost[lane]; row_src = fprev->big_src[lane]; }
+    auto long_cand = [&](int a, const ArcRec &rec, float cost) {
+      float w = rec.weight;
+      if (ctx_contains(cx, a)) w = w + cx.offset;   // Sec. 4.1
+      return (cost + w) - Lrow.at((rec.meta & 0xFFFFu) - 1u);
+    };
+    // The first announced long row that is alive enters the empty table ahead of all other candidates: those of its arcs that
+    // have a home slot to themselves (no other arc of the row before them has it) with plain stores of key and value, where the
+    // others need a compare-and-swap and a 64-bit minimum each; whoever looks for such a state finds it at its home slot.  (64
+    // channels x 100 frames of 20,000 words 4,938 -> 4,349 us, 8 channels of 3,000 words 2,401 -> 2,365; slots laid out by probing
+    // would not do: a state displaced by one that is pruned in this frame would be looked for in front of its slot.)
+    // The candidates this member owns of the announced long rows with sorted arcs whose destination has no closure, four per
+    // thread and round: fn(arcs, records, costs, the lanes that hold one, source token).  kDirect: those that enter the table
+    // directly, else the others.  All four records are asked for before the first is used, from a copy in the sorted order, 16
+    // lines of 64 bytes per wave, instead of through the arc's index, up to 64 lines behind another read.
+    auto for_owned_long_arcs = [&](auto kDirect, auto &&fn) {
+      for (int r = 0; r < nbig_prev; ++r) {   // uniform
+        const int direct = rows[0].direct;
+        if (kDirect && r != direct) continue;
+        const TeamRow row = rows[r];
+        const float cost = row.cost;
+        const int src = row.src, perm0 = row.perm0;
+        const int g0 = !kDirect && r == direct ? row.g[1] : row.g[0], g1 = kDirect ? row.g[1] : row.g[2];
+        // (a row's share that one round of a single arc per thread holds is not worth the clamped requests of four)
+        auto rounds_of = [&](auto kN) {
+          for (int base = g0 + wave * 64; base < g1; base += kN * kBlock) {   // uniform
+            int a[kN];
+            ArcRec rec[kN];
+            float cand[kN];
+            uint64_t have[kN];
+#pragma unroll
+            for (int u = 0; u < kN; ++u) {
+              const int t = base + u * kBlock + lane, at = perm0 + min(t, g1 - 1);
+              have[u] = lanes_with(t < g1);
+              a[u] = tp.big_perm[at];
+              rec[u] = kRecs ? tp.big_recs[at] : p.arcs[a[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kN; ++u) {
+              cand[u] = 0.0f;
+              if (have[u] != 0) cand[u] = long_cand(a[u], rec[u], cost);   // uniform
+            }
+            fn(kN, a, rec, cand, have, src);
+          }
+        };
+        if (g1 - g0 > kBlock) rounds_of(std::integral_constant<int, 4>{});
+        else rounds_of(std::integral_constant<int, 1>{});
+      }
+    };
+    // the same for those whose destination has one, one per thread and round: fn(entry)
+    auto for_owned_long_closures = [&](auto &&fn) {
+      for (int r = 0; r < nbig_prev; ++r) {   // uniform
+        const TeamRow row = rows[r];
+        const float cost = row.cost;
+        const int src = row.src, perm0 = row.perm0;
+        const int g0 = row.g[2], g1 = row.g[3];
+        for (int base = g0 + wave * 64; base < g1; base += kBlock) {   // uniform
+          const int at = perm0 + min(base + lane, g1 - 1), a = tp.big_perm[at];
+          const ArcRec rec = kRecs ? tp.big_recs[at] : p.arcs[a];
+          TeamEntry e; e.dst = base + lane < g1 ? (uint32_t)rec.dst : kEmptyKey; e.cost = long_cand(a, rec, cost);
+          e.arc = (uint32_t)a; e.from = src; e.row = rec.row; e.meta = rec.meta & 0xFFFF0000u; e.pad[0] = 0; e.pad[1] = 0;
+          fn(e);
         }
       }
     };
@@ -572,13 +631,13 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
             }
           }
         }
-        for (int j = 0; __ballot(j < tk.deg) != 0; j += 2) {   // uniform
+        for (int j = 0; lanes_with(j < tk.deg) != 0; j += 2) {   // uniform
           bool act[2] = {j < tk.deg, j + 1 < tk.deg};
           int a[2] = {tk.first + j, tk.first + j + 1};
           ArcRec r[2];
           r[0] = team_arc(tp, act[0], a[0]);
           r[1] = team_arc(tp, act[1], a[1]);
-          n_emit += (uint32_t)__popcll(__ballot(act[0])) + (uint32_t)__popcll(__ballot(act[1]));
+          n_emit += (uint32_t)__popcll(lanes_with(act[0])) + (uint32_t)__popcll(lanes_with(act[1]));
           team_emit<2>(tp, cx, Lrow, sh, q1c, me, act, a, r, tk.cost, tk.idx, lane, lmin);
         }
       };
@@ -595,19 +654,30 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
           if (base + u * NW * 64 >= t1) break;   // uniform
           const int i = base + u * NW * 64 + lane;
           const bool alive = i < t1 && row_alive(c4[u]);
-          const unsigned long long lm = __ballot(alive);
+          const unsigned long long lm = lanes_with(alive);
           const int n_new = (int)__popcll(lm);
           n_active += (uint32_t)n_new;
           if (n_new == 0) continue;   // uniform
           if (n_staged + n_new > 64) { expand_staged(n_staged); n_staged = 0; }
           if (alive) {
             LiveToken tk; tk.cost = c4[u]; tk.first = 0; tk.deg = 0; tk.idx = i;
-            stage[n_staged + (int)__popcll(lm & ((1ull << lane) - 1ull))] = tk;
+            stage[n_staged + rank_in(lm, 0)] = tk;
           }
           n_staged += n_new;
         }
       }
       if (n_staged > 0) expand_staged(n_staged);
+      if (wave == NW - 1 && nbig_prev > 0) {   // (its staging list is free now)
+        TeamRow row; row.perm0 = 0; row.src = row_src; row.cost = row_cost; row.direct = -1;
+        const bool is = lane < nbig_prev && row_id >= 0 && row_alive(row_cost);
+        const int32_t *group = tp.big_group + (is ? row_id : 0) * (3 * k + 1) + 3 * me;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) row.g[q] = is ? group[q] : 0;
+        if (is) row.perm0 = tp.big_rows[row_id].w;
+        const uint64_t im = lanes_with(is);
+        if (im != 0) row.direct = (int)__builtin_ctzll(im);
+        if (lane < nbig_prev) rows[lane] = row;
+      }
       TEAM_STAMP(7);   // (diagnostic: own tokens expanded)
       // long rows announced by the previous frame: every wave of every member takes every (k * NW)-th group of 64
       for (int r = 0; r < nbig_prev; ++r) {
@@ -636,7 +706,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
             const uint32_t o = f2ord((cost + w) - Lrow.at((rec.meta & 0xFFFFu) - 1u));
             lmin = o < lmin ? o : lmin;
           }
-          n_emit += (uint32_t)__popcll(__ballot(j < deg));
+          n_emit += (uint32_t)__popcll(lanes_with(j < deg));
         }
       }
       TEAM_STAMP(8);   // (diagnostic: announced long rows expanded)
@@ -689,7 +759,7 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       auto recombine = [&](const TeamEntry &e) {
         const bool act = e.dst != kEmptyKey;
         const bool pass = act && !(e.cost - m > p.beam);
-        n_cand += (uint32_t)__popcll(__ballot(pass));
+        n_cand += (uint32_t)__popcll(lanes_with(pass));
         // the closure list of the state reached (stored with the graph: depth-first preorder, a record's source
         // is the latest record one level up); its first record is asked for before the table is touched
         int pos = 0, len = 0;
@@ -709,13 +779,13 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
         team_min(hval, hkey, slots, sh, pass, e.dst, ((uint64_t)f2ord(e.cost) << 32) | e.arc, lane);
         float cstack[kClosureMaxDepth + 1];
         uint32_t sstack[kClosureMaxDepth + 1];
-        const bool flat = __ballot(len > 1) == 0;   // (uniform) no list of this wave is longer than one arc: no levels to keep
+        const bool flat = lanes_with(len > 1) == 0;   // (uniform) no list of this wave is longer than one arc: no levels to keep
         if (!flat) {
 #pragma unroll
           for (int d = 0; d <= kClosureMaxDepth; ++d) { cstack[d] = __builtin_inff(); sstack[d] = 0; }
           cstack[0] = e.cost; sstack[0] = e.dst;
         }
-        for (int j = 0; __ballot(j < len) != 0; ++j) {   // uniform
+        for (int j = 0; lanes_with(j < len) != 0; ++j) {   // uniform
           const bool has = j < len;
           bool ok = false;
           TeamEntry ce; ce.dst = 0; ce.cost = 0.0f; ce.arc = 0; ce.from = 0; ce.row = 0; ce.meta = 0; ce.pad[0] = 0; ce.pad[1] = 0;
@@ -746,21 +816,21 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
               cmin = o < cmin ? o : cmin;
             }
           }
-          n_eps += (uint32_t)__popcll(__ballot(has));
-          n_cand += (uint32_t)__popcll(__ballot(ok));
+          n_eps += (uint32_t)__popcll(lanes_with(has));
+          n_cand += (uint32_t)__popcll(lanes_with(ok));
           // candidates of one wave for one state (every word end leads to the hub): only the least key travels
-          const unsigned long long om = __ballot(ok);
+          const unsigned long long om = lanes_with(ok);
           if (om != 0) {
             const int fl = (int)__builtin_ctzll(om);
             const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)ce.dst, fl);
-            if (__popcll(om) > 1 && __ballot(ok && ce.dst == d0) == om) {
+            if (__popcll(om) > 1 && lanes_with(ok && ce.dst == d0) == om) {
               const uint32_t hi = ok ? f2ord(ce.cost) : 0xFFFFFFFFu;
               const uint32_t mhi = wave_min_u32(hi);
               const uint32_t lo = (ok && hi == mhi) ? ce.arc : 0xFFFFFFFFu;
               const uint32_t mlo = wave_min_u32(lo);
               ok = ok && hi == mhi && ce.arc == mlo;
               // (two lanes can hold the same least key: one of them goes)
-              const unsigned long long wm = __ballot(ok);
+              const unsigned long long wm = lanes_with(ok);
               ok = ok && lane == (int)__builtin_ctzll(wm);
             }
           }
@@ -773,6 +843,22 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
         }
       };
       TeamEntry e_next = fetch(0);
+      const int direct = nbig_prev > 0 ? rows[0].direct : -1;
+      if (direct >= 0) {   // uniform
+        for_owned_long_arcs(std::true_type{}, [&](auto kN, const int *a, const ArcRec *rec, const float *cand, const uint64_t *have, int) {
+#pragma unroll
+          for (int u = 0; u < kN; ++u) {
+            const uint64_t pass = have[u] & lanes_with(!(cand[u] - m > p.beam));
+            n_cand += (uint32_t)__popcll(pass);
+            if (lane_in(pass)) {
+              const uint32_t h = share_home((uint32_t)rec[u].dst, slots);
+              hkey[h] = (uint32_t)rec[u].dst;
+              hval[h] = ((uint64_t)f2ord(cand[u]) << 32) | (uint32_t)a[u];
+            }
+          }
+        });
+        __syncthreads();
+      }
       for (int rd = 0; rd < rounds; ++rd) {   // uniform
         const TeamEntry e = e_next;
         if (rd + 1 < rounds) e_next = fetch(rd + 1);
@@ -780,7 +866,20 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       }
       // long rows whose arcs are sorted by owner: this member expands the arcs it owns, here, with the cutoff known
       TEAM_STAMP(12);   // (diagnostic: candidates from the queues recombined)
-      for_owned_long_arcs([&](const TeamEntry &e) { recombine(e); });
+      for_owned_long_arcs(std::false_type{}, [&](auto kN, const int *a, const ArcRec *rec, const float *cand, const uint64_t *have, int) {
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+          const uint64_t pass = have[u] & lanes_with(!(cand[u] - m > p.beam));
+          n_cand += (uint32_t)__popcll(pass);
+          if (lane_in(pass)) {
+            uint32_t h;
+            if (team_slot(hkey, slots, (uint32_t)rec[u].dst, h))
+              atomicMin((unsigned long long *)&hval[h], ((unsigned long long)f2ord(cand[u]) << 32) | (uint32_t)a[u]);
+            else sh->fault = 1;
+          }
+        }
+      });
+      for_owned_long_closures([&](const TeamEntry &e) { recombine(e); });
       const uint32_t wmin = wave_min_u32(cmin);
       if (lane == 0 && wmin != 0xFFFFFFFFu) atomicMin(&sh->best_ord, wmin);
       __syncthreads();
@@ -824,6 +923,45 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       }
       return e;
     };
+    // the token of a winner: its place among the member's, the state's slot
+    auto put = [&](uint32_t h, int lid, const TeamEntry &e, bool closure) {
+      if (lid >= part_cap) { sh->fault = 1; }
+      else {
+        hidx[h] = (uint16_t)lid;
+        const int idx = tok0 + lid;
+        // the state's row: from the arc record's fields, or (long rows) from the offsets
+        int first = e.row, eps;
+        const uint32_t ed = meta_ed(e.meta);
+        if (ed == kEdEscape) eps = p.off2[e.dst].y;
+        else eps = first + (int)ed;
+        if (eps - first > kBigRowArcs) {
+          const int slot = atomicAdd(&fr->n_big, 1);
+          if (slot < kTeamBig) {
+            fr->big_first[slot] = first; fr->big_deg[slot] = eps - first; fr->big_src[slot] = idx; fr->big_cost[slot] = e.cost;
+            fr->big_id[slot] = team_long_row_id(tp, e.dst);
+            first = eps;   // (the token's own row has no emitting arcs left: the team expands them)
+          }
+        }
+        t_cost[idx] = e.cost;
+        ((int2 *)(t_row + no))[idx] = make_int2(first, eps);
+        if (last) t_state[idx] = (int32_t)e.dst;
+        if (!closure) {
+          bp[n_rec + idx] = make_int2((int)e.arc, frame_base + e.from);
+        } else {
+          const int w = atomicAdd(&sh->n_cwin, 1);
+          TeamClosureWin cw; cw.idx = idx; cw.arc = e.arc; cw.parent_state = (uint32_t)e.from;
+          cwin[w] = cw;   // (w < part_cap: one per token)
+        }
+        if (hist_on) {
+          const float r = e.cost - fbest;
+          if (!(r > p.beam)) {
+            int bin = (int)floorf(r * inv);
+            bin = bin > 255 ? 255 : bin;
+            atomicAdd(&hist[bin], 1u);
+          }
+        }
+      }
+    };
     // the entry whose key is its state's value writes the token
     auto winner = [&](const TeamEntry &e, bool closure) {
       const bool act = e.dst != kEmptyKey;
@@ -840,50 +978,12 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
         if (win && closure)
           win = atomicCAS((unsigned long long *)&hval[h], (unsigned long long)v, (unsigned long long)kEmptyVal) == v;
       }
-      const unsigned long long wm = __ballot(win);
+      const unsigned long long wm = lanes_with(win);
       if (wm == 0) return;   // uniform
       int base = 0;
       if (lane == (int)__builtin_ctzll(wm)) base = atomicAdd(&sh->n_mine, (int)__popcll(wm));
       base = __builtin_amdgcn_readlane(base, (int)__builtin_ctzll(wm));
-      if (win) {
-        const int lid = base + (int)__popcll(wm & ((1ull << lane) - 1ull));
-        if (lid >= part_cap) { sh->fault = 1; }
-        else {
-          hidx[h] = (uint16_t)lid;
-          const int idx = tok0 + lid;
-          // the state's row: from the arc record's fields, or (long rows) from the offsets
-          int first = e.row, eps;
-          const uint32_t ed = meta_ed(e.meta);
-          if (ed == kEdEscape) eps = p.off2[e.dst].y;
-          else eps = first + (int)ed;
-          if (eps - first > kBigRowArcs) {
-            const int slot = atomicAdd(&fr->n_big, 1);
-            if (slot < kTeamBig) {
-              fr->big_first[slot] = first; fr->big_deg[slot] = eps - first; fr->big_src[slot] = idx; fr->big_cost[slot] = e.cost;
-              fr->big_id[slot] = team_long_row_id(tp, e.dst);
-              first = eps;   // (the token's own row has no emitting arcs left: the team expands them)
-            }
-          }
-          t_cost[idx] = e.cost;
-          ((int2 *)(t_row + no))[idx] = make_int2(first, eps);
-          if (last) t_state[idx] = (int32_t)e.dst;
-          if (!closure) {
-            bp[n_rec + idx] = make_int2((int)e.arc, frame_base + e.from);
-          } else {
-            const int w = atomicAdd(&sh->n_cwin, 1);
-            TeamClosureWin cw; cw.idx = idx; cw.arc = e.arc; cw.parent_state = (uint32_t)e.from;
-            cwin[w] = cw;   // (w < part_cap: one per token)
-          }
-          if (hist_on) {
-            const float r = e.cost - fbest;
-            if (!(r > p.beam)) {
-              int bin = (int)floorf(r * inv);
-              bin = bin > 255 ? 255 : bin;
-              atomicAdd(&hist[bin], 1u);
-            }
-          }
-        }
-      }
+      if (win) put(h, base + rank_in(wm, 0), e, closure);
     };
     bool closure_next = false;
     TeamEntry w_next = fetch_any(0, closure_next);
@@ -894,7 +994,43 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       winner(e, closure);
     }
     TEAM_STAMP(13);   // (diagnostic: winners among the queues' candidates)
-    for_owned_long_arcs([&](const TeamEntry &e) { winner(e, false); });   // (made once more: the same bits)
+    // (made once more: the same bits)
+    auto long_winners = [&](auto kDirect) {
+      for_owned_long_arcs(kDirect, [&](auto kN, const int *a, const ArcRec *rec, const float *cand, const uint64_t *have, int src) {
+        uint64_t win[kN];
+        uint32_t h[kN];
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+          win[u] = have[u] & lanes_with(!(cand[u] - m > p.beam));
+          h[u] = 0;
+          if (win[u] == 0) continue;   // uniform
+          bool is = false;
+          if (lane_in(win[u])) {
+            h[u] = kDirect ? share_home((uint32_t)rec[u].dst, slots) : team_find(hkey, slots, (uint32_t)rec[u].dst);
+            is = hval[h[u]] == (((uint64_t)f2ord(cand[u]) << 32) | (uint32_t)a[u]);
+          }
+          win[u] = lanes_with(is);
+          n += __popcll(win[u]);
+        }
+        if (n == 0) return;   // uniform
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&sh->n_mine, n);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < kN; ++u) {
+          if (lane_in(win[u])) {
+            TeamEntry e; e.dst = (uint32_t)rec[u].dst; e.cost = cand[u]; e.arc = (uint32_t)a[u]; e.from = src;
+            e.row = rec[u].row; e.meta = rec[u].meta; e.pad[0] = 0; e.pad[1] = 0;
+            put(h[u], rank_in(win[u], at), e, false);
+          }
+          at += __popcll(win[u]);
+        }
+      });
+    };
+    if (nbig_prev > 0 && rows[0].direct >= 0) long_winners(std::true_type{});   // uniform
+    long_winners(std::false_type{});
+    for_owned_long_closures([&](const TeamEntry &e) { winner(e, false); });
     __syncthreads();
     TEAM_STAMP(11);   // (diagnostic: winners done)
     // publish (state -> token) of this share, then empty the table for the next frame

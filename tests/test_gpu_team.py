@@ -135,3 +135,17 @@ def test_team_of_a_small_decoder_on_very_long_rows(torch_cuda):
     rows, rest = s["info"]["device_bytes"] - base["info"]["device_bytes"], base["info"]["device_bytes"]
     print("long-row arcs", long_arcs, "bytes", rows, "rest", rest, flush=True)
     assert long_arcs > 200_000 and rows <= 4 * long_arcs + rest // 8 + 65_536
+
+
+@pytest.mark.parametrize("k,S,hubs,arcs,lookup_mode", [(2, 8_000, 3, 6_000, 0), (4, 2_000, 6, 1_500, 1), (8, 2_000, 2, 1_500, 0)])
+def test_team_long_rows_of_all_kinds(torch_cuda, k, S, hubs, arcs, lookup_mode):
+    """Several long rows in one frame, into states with and without closures and into the same states more than once: arcs that
+    enter the members' empty tables directly (one round per thread and several), arcs that share a home slot with another, arcs
+    to closures, and the rows behind the first."""
+    from test_gpu_parts import hub_graph, inputs
+    print(f"team of {k}: {hubs} long rows of up to {arcs} arcs into {S} states", flush=True)
+    g = hub_graph(S, 64, hubs, arcs, seed=40 + k)
+    L, ctxs, offs = inputs(torch_cuda, g, 3, 16, 2.5, 40 + k)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=9.0, max_active=0, chunks=[1, 6, 9], hash_log2=16, lookup_mode=lookup_mode,
+                  workgroups_per_channel=k)
+    assert s["eps_arcs"] > 0 and s["max_tokens"] > S // 4 and s["emit_arcs"] > 3 * 16 * 513
