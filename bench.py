@@ -30,12 +30,12 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # profiled build: a run whose own launch time is more than 5 % away from it is another kernel (or another machine
 # state) and reports no traffic instead of a stale one.
 MEASURED_TRAFFIC = {  # workload: (bytes per launch, ms per launch that bench.py reported in the profiled runs)
-    "large": (1250044412, 0.6156),
-    "stress": (14224662745, 4.9539),
-    "dynamic": (4625691914, 1.8659),
-    "medium": (438157735, 2.2768),
-    "words": (523528186, 0.5160),
-    "e2e": (4250525025, 4.0906),   # teams of four workgroups per channel
+    "large": (1231535685, 0.5326),
+    "stress": (14145467131, 4.2707),
+    "dynamic": (4625358301, 1.6072),
+    "medium": (438450170, 1.6481),
+    "words": (524449381, 0.4351),
+    "e2e": (5145601586, 2.0611),   # teams of four workgroups per channel
 }
 TRAFFIC_TOLERANCE = 0.05
 
