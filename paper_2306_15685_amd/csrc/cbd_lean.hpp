@@ -172,13 +172,14 @@ struct LeanEmit {
   uint64_t act[2];    // the lanes that hold one (uniform)
 };
 
-// Which of the arcs a[] are listed, for lanes in act[] (lane masks; uniform).  A wave waits for LDS once per step for both
-// slots, and the number of steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with
-// no lanes dropping out.  (One arc after the other with a search that ends per lane: a wave waited twice per step and for the
-// arc records before its second test.  32 channels x 333 frames behind the plain search 2.414 -> 2.393 ms, 8 channels x 1,000
-// frames 8.59 -> 8.50, where runs differ by 0.3 %; 2,048 channels with 1,000-arc lists behind the filter within the spread.)
+// Which lanes' arcs a[] are listed.  Every lane asks, those beyond the list of candidates too: they hold its last arc once
+// more, and the costs made of it enter the frame's minimum.  A wave waits for LDS once per step for both slots, and the number
+// of steps depends on the list's length alone, so a step is a read, a compare and a select per arc, with no lanes dropping out.
+// (One arc after the other with a search that ends per lane: a wave waited twice per step and for the arc records before its
+// second test.  32 channels x 333 frames behind the plain search 2.414 -> 2.393 ms, 8 channels x 1,000 frames 8.59 -> 8.50,
+// where runs differ by 0.3 %; 2,048 channels with 1,000-arc lists behind the filter within the spread.)
 template <int kSlots>
-__device__ __forceinline__ void lean_listed(const Ctx &cx, const int (&a)[2], const uint64_t (&act)[2], uint64_t (&in)[2]) {
+__device__ __forceinline__ void lean_listed(const Ctx &cx, const int (&a)[2], uint64_t (&in)[2]) {
   uint64_t any = 0;
 #pragma unroll
   for (int q = 0; q < kSlots; ++q) in[q] = 0;
@@ -192,11 +193,11 @@ __device__ __forceinline__ void lean_listed(const Ctx &cx, const int (&a)[2], co
       w[q] = cx.bitmap[bloom_word(h)];
     }
 #pragma unroll
-    for (int q = 0; q < kSlots; ++q) { in[q] = act[q] & lanes_with((w[q] & m[q]) == m[q]); any |= in[q]; }
+    for (int q = 0; q < kSlots; ++q) { in[q] = lanes_with((w[q] & m[q]) == m[q]); any |= in[q]; }
     if (any == 0) return;
   } else {
 #pragma unroll
-    for (int q = 0; q < kSlots; ++q) in[q] = act[q];
+    for (int q = 0; q < kSlots; ++q) in[q] = ~0ull;
   }
   if (!cx.in_lds) {
 #pragma unroll
@@ -237,7 +238,7 @@ __device__ __forceinline__ uint32_t lean_costs(const AdvanceParams &p, const Ctx
   for (int q = 0; q < kSlots; ++q) E.rec[q] = p.arcs[E.arc[q]];
   // the bias test needs the arcs' numbers only: it runs while the records are on their way
   uint64_t listed[2];
-  lean_listed<kSlots>(cx, E.arc, E.act, listed);
+  lean_listed<kSlots>(cx, E.arc, listed);
   float ll[kSlots];
   if (kRowFromLds && Lrow.staged) {
 #pragma unroll
@@ -253,7 +254,7 @@ __device__ __forceinline__ uint32_t lean_costs(const AdvanceParams &p, const Ctx
     float w = E.rec[q].weight;
     w = lane_in(listed[q]) ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
     E.cand[q] = (own_cost[q] + w) - ll[q];
-    lmin = umin32(lmin, f2ord(E.cand[q]));   // (lanes beyond the list: the last arc's once more)
+    lmin = umin32(lmin, f2ord(E.cand[q]));   // (lanes beyond the list have the last arc's candidate once more, offset and all)
   }
   return lmin;
 }
@@ -494,9 +495,8 @@ __device__ __forceinline__ void lean_commit(const AdvanceParams &p, const Mem<tr
   W.n_eps += total;
   const int depth = (int)(rec.meta & 0xFu);   // 1..kClosureMaxDepth
   const int plane = (o_start - 1 + (int)((rec.meta >> 4) & 0x3Fu)) & 63;   // the lane that holds the parent record
-  const uint64_t acts[2] = {act, 0};
   uint64_t listed[2];
-  lean_listed<1>(cx, can, acts, listed);
+  lean_listed<1>(cx, can, listed);
   float w = rec.weight;
   w = lane_in(listed[0]) ? w + cx.offset : w;   // Sec. 4.1: boosted weight = weight + discount
   const uint64_t d1 = act & lanes_with(depth == 1);
