@@ -10,6 +10,7 @@ SRC = os.path.join(HERE, "csrc", "cbd.hip")
 DEPS = [SRC, os.path.join(HERE, "csrc", "cbd_device.hpp"), os.path.join(HERE, "csrc", "cbd_lean.hpp"), os.path.join(HERE, "csrc", "cbd_parts.hpp"), os.path.join(HERE, "csrc", "cbd_team.hpp"), os.path.join(HERE, "csrc", "word_index.hpp"), os.path.join(HERE, "..", "include", "cbd.h")]
 LIB = os.path.join(HERE, "libcbdec.so")
 LIB_PROFILE = os.path.join(HERE, "libcbdec_prof.so")   # diagnostic build: phase stamps in the lean frame code
+LIB_SPREAD = os.path.join(HERE, "libcbdec_spread.so")   # test build: teams of workgroups as if spread over several dies
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
@@ -21,15 +22,17 @@ HIPCC_FLAGS = [
 ]
 
 
-def build(force: bool = True, verbose: bool = False, profile: bool = False) -> str:
+def build(force: bool = True, verbose: bool = False, profile: bool = False, spread: bool = False) -> str:
     """Compile libcbdec.so.  With force=False only when a source is newer than the library.
     profile=True builds libcbdec_prof.so instead: the same code with -DCBD_PROFILE, in which thread 0 of every
-    workgroup stamps the phases of the lean frames (bench.py --phases reads the sums); not the product build."""
-    lib = LIB_PROFILE if profile else LIB
+    workgroup stamps the phases of the lean frames (bench.py --phases reads the sums); not the product build.
+    spread=True builds libcbdec_spread.so: the same code with -DCBD_TEAM_SPREAD, in which teams use device-wide barriers
+    throughout (tests/test_gpu_team.py); not the product build either."""
+    lib = LIB_PROFILE if profile else LIB_SPREAD if spread else LIB
     if not force and os.path.exists(lib) and all(os.path.getmtime(lib) >= os.path.getmtime(d) for d in DEPS):
         return lib
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *(["-DCBD_PROFILE"] if profile else []), "-o", lib + ".tmp", SRC]
+    cmd = [hipcc, *HIPCC_FLAGS, *(["-DCBD_PROFILE"] if profile else []), *(["-DCBD_TEAM_SPREAD"] if spread else []), "-o", lib + ".tmp", SRC]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
@@ -63,4 +66,4 @@ def resource_usage() -> dict:
 
 
 if __name__ == "__main__":
-    print(build(force=True, verbose=True, profile="--profile" in sys.argv[1:]))
+    print(build(force=True, verbose=True, profile="--profile" in sys.argv[1:], spread="--spread" in sys.argv[1:]))

@@ -149,14 +149,15 @@ __host__ __device__ inline TeamLayout team_layout(int num_pdfs_staged, int ctx_l
 // on its way to barrier n sets the mark of n's parity before it arrives, and whoever leaves barrier n looks at that
 // mark only (a member that is already on its way to barrier n + 1 sets the other one).  Returns false if the team
 // has to give up waiting (then abort_flag is set); `failed` receives the failure, if any, met before this barrier.
-// near: all members run on one die (XCC_ID), behind one L2.  What a member wrote is then where the others look for it once
-// its waves' stores have been acknowledged (vmcnt, every wave for itself, ahead of the workgroup barrier), and nothing has to
-// be written back; the acquire side, which drops what the compute unit's L1 holds, is the same.  (64 channels x 100 frames
+// Every wave waits for its own stores to be acknowledged by the die's L2 (vmcnt) ahead of the workgroup barrier: thread 0's
+// fence waits for those of its own wave only.
+// near: all members run on one die (XCC_ID), behind one L2.  What a member wrote is then where the others look for it, and
+// nothing has to be written back; the acquire side, which drops what the compute unit's L1 holds, is the same.  (64 channels x 100 frames
 // of 20,000 words, 25 MB of queue entries and tokens per frame: with a full fence on both sides, as there was, 8.24 ms, with a
 // release and an acquire 6.41, without the write-back 4.95; 8 channels of 3,000 words 2.48 / 2.42 / 2.40.)
 constexpr uint32_t kTeamCountMask = 0x3FFFFFFFu;
 __device__ __forceinline__ bool team_barrier(TeamChan *tc, TeamShared *sh, int k, bool near, int &seq, int &failed) {
-  if (near) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no store moves past it)
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint32_t mark = 0x40000000u << (seq & 1);
@@ -500,6 +501,9 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
   near = true;   // (every member reads the same k numbers)
   for (int q = 1; q < k; ++q) near = near && tc->xcc[q] == tc->xcc[0];
   near = __builtin_amdgcn_readfirstlane(near ? 1 : 0) != 0;
+#ifdef CBD_TEAM_SPREAD
+  near = false;   // (test build: the grid order leaves no team spread over several dies, whose barriers this build uses throughout)
+#endif
   if (failed != 0 && status == kStatusOk) status = failed;
   const bool hist_on = p.max_active > 0 && p.beam > 0.0f && p.beam < __builtin_inff();
   const float inv = 256.0f / p.beam;

@@ -149,3 +149,26 @@ def test_team_long_rows_of_all_kinds(torch_cuda, k, S, hubs, arcs, lookup_mode):
     s = run_batch(torch_cuda, g, L, ctxs, offs, beam=9.0, max_active=0, chunks=[1, 6, 9], hash_log2=16, lookup_mode=lookup_mode,
                   workgroups_per_channel=k)
     assert s["eps_arcs"] > 0 and s["max_tokens"] > S // 4 and s["emit_arcs"] > 3 * 16 * 513
+
+
+@pytest.fixture
+def spread_library(monkeypatch):
+    """The build in which a team's barriers are those of members on several dies (the grid order leaves no such team)."""
+    from paper_2306_15685_amd import build
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "LIB_PATH", build.LIB_SPREAD)
+    B.lib()
+
+
+@pytest.mark.parametrize("k", [2, 4, 8])
+def test_team_spread_over_dies(torch_cuda, spread_library, k):
+    from test_gpu_parts import hub_graph, inputs
+    print(f"team of {k}: device-wide barriers", flush=True)
+    g, L, ctxs, offs = mid_inputs(torch_cuda)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=13.0, max_active=150, chunks=[1, 7, 40], hash_log2=16, workgroups_per_channel=k)
+    assert s["eps_arcs"] > 0 and s["frames"] == L.shape[0] * L.shape[1] and s["max_tokens"] > 150
+    g = hub_graph(2_000, 64, 2, 1_500, seed=60 + k)
+    L, ctxs, offs = inputs(torch_cuda, g, 16, 24, 2.5, 60 + k)
+    s = run_batch(torch_cuda, g, L, ctxs, offs, beam=9.0, max_active=0, chunks=[2, 22], hash_log2=16, lookup_mode=1,
+                  workgroups_per_channel=k)
+    assert s["eps_arcs"] > 0 and s["max_tokens"] > 500 and s["emit_arcs"] > 16 * 24 * 513
