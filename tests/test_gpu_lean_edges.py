@@ -42,6 +42,16 @@ def test_sizes(torch_cuda, S, deg, eps_every):  # noqa: F811
     listed = np.arange(0, g.num_arcs, 7, dtype=np.int32)[:50]
     s = run_batch(torch_cuda, g, L, [listed, listed[::2]], [-2.0, 1.5], beam=60.0, max_active=0, chunks=[5, 11])
     assert s["status"] == 0 and s["max_tokens"] >= 0.9 * S
+    # Who decodes the frames in which all states are tokens: rows of 63 arcs or more, and waves that log more than 256 commits
+    # (on average, so one of them does), go to the general code; the lean code takes all frames of sizes that stay clear of its
+    # limits (256 commits, and 64 closure records in 128 arcs, by four and five standard deviations of a Poisson count).
+    arcs = (S + 15) // 16 * deg
+    closures, in_round = (arcs / eps_every, min(arcs, 128) / eps_every) if eps_every else (0, 0)
+    print("lean frames", s["lean_frames"], "of", s["frames"], flush=True)
+    if deg >= 63 or arcs + closures > 256:
+        assert s["lean_frames"] < s["frames"]
+    elif arcs + closures + 4 * closures ** 0.5 <= 256 and in_round + 5 * in_round ** 0.5 <= 64:
+        assert s["lean_frames"] == s["frames"]
 
 
 def boosted_graph(S, deg, short_every, listed_per_row, offset, beam, eps_every, seed):
