@@ -195,7 +195,6 @@ __device__ __forceinline__ void team_push(TeamEntry *q_base, unsigned long long 
   for (int u = 0; u < U; ++u) any = any || act[u];
   if (lanes_with(any) == 0) return;   // uniform
   if (__hip_atomic_load(&sh->fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) return;
-  const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long add[2] = {0, 0};
   int rank[U];
 #pragma unroll
@@ -686,14 +685,9 @@ __global__ __launch_bounds__(kBlock) void advance_team_kernel(TeamParams tp) {
       // long rows announced by the previous frame: every wave of every member takes every (k * NW)-th group of 64
       for (int r = 0; r < nbig_prev; ++r) {
         const float cost = fprev->big_cost[r];
-        const float rr = cost - best;
-        bool alive = !(rr > p.beam) && cost < __builtin_inff();
-        if (alive && cut_bin < 255) {
-          int bin = (int)floorf(rr * inv);
-          bin = bin > 255 ? 255 : bin;
-          alive = bin <= cut_bin;
-        }
-        if (!alive) continue;   // uniform (the token itself is counted where it lives, with an empty row)
+        // (the test that also picks the row which enters the tables directly; the token itself is counted where it lives, with
+        // an empty row)
+        if (!row_alive(cost)) continue;   // uniform
         const int first = fprev->big_first[r], deg = fprev->big_deg[r], src = fprev->big_src[r];
         if (fprev->big_id[r] < 0) {
           team_long_row(tp, cx, Lrow, sh, q1c, me, first, deg, cost, src, (me * NW + wave) * 64, k * NW * 64, lane, lmin, n_emit);
