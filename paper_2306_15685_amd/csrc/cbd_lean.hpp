@@ -20,9 +20,10 @@
 // or log) sets Shared::redo (before the first barrier) or the wave's count in Shared::wcount to more than any table holds
 // (between the barriers); each is read by all waves after the barrier that follows, and the frame is then decoded again by
 // run_frame(), which handles everything.
-// What bounds it: of four waves on a SIMD, all in the same phase, the instructions, and between them the chain of dependent
-// LDS and device-memory reads.  So a wave goes through straight-line code for the 64 or 128 arcs it has (one or two slots per
-// lane), and what lanes do is kept in lane masks.  Against the same steps with a flag per lane, an owner search by running
+// What bounds it: the chain of dependent LDS and device-memory reads of a frame's slowest wave, with its instructions between
+// them, and three barriers at which the others wait for it (256 channels: the vector unit is active 40 % of the time its
+// workgroup is resident, and waves wait for an issue slot 12 % of theirs).  So a wave goes through straight-line code for the
+// 64 or 128 arcs it has (one or two slots per lane), and what lanes do is kept in lane masks.  Against the same steps with a flag per lane, an owner search by running
 // maximum and shuffles for the emitting arcs, and one code for one and two slots (us): one channel x 100 frames 656 -> 562,
 // 32 x 333 2,120 -> 1,792, 100 x 151 1,352 -> 1,211, 256 x 500 6,028 -> 5,625, 512 x 400 7,793 -> 7,187, 2,048 x 100 9,932 ->
 // 9,048.
